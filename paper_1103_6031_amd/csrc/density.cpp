@@ -47,11 +47,8 @@ struct DensPlan {
     int nl = 0;
     std::vector<DensLevel> L;
     double* reg = nullptr;       // gathered parent region (max n^3)
-    double2* csp = nullptr;      // its spectrum
-    double* a = nullptr;         // convolution inputs / outputs on D' (max (2n)^3)
-    double* b = nullptr;
-    double* c = nullptr;
-    double* zbase = nullptr;     // base noise with the first patch's cells zeroed (N^3)
+    double2* csp = nullptr;      // its spectrum (half of the modes)
+    double* b = nullptr;         // a convolution's output on D' (max (2n)^3)
     double* carry0 = nullptr;    // the base's coarse contribution (N^3)
     double* carryA = nullptr;    // coarse contributions on patches (max n^3), ping-pong
     double* carryB = nullptr;
@@ -104,46 +101,33 @@ int dens_plan(const mg_hier* H, void* ws, DensPlan& P) {
         off += bytes;
         return p;
     };
-    size_t w1 = 0, w2 = 0, maxn = 0, maxd = 0;
+    size_t w = 0, maxn = 0, maxd = 0, maxs = 0;
     for (int l = 0; l < P.nl; ++l) {
         DensLevel& D = P.L[l];
         int rc = spec_grid_init(D.D, 0, D.G);
         if (rc) return rc;
         spec_grid_carve(D.G, base, off);
-        size_t a1, a2;
-        spec_grid_work(D.G, a1, a2);
-        w1 = std::max(w1, a1);
-        w2 = std::max(w2, a2);
+        w = std::max(w, D.G.field());
         D.mu = (double*)take(sizeof(double) * cells3(D.D));
         D.T = (double*)take(sizeof(double) * cells3(D.D));
         if (l) {
             rc = spec_grid_init(D.n, 0, D.R);
             if (rc) return rc;
             spec_grid_carve(D.R, base, off);
-            spec_grid_work(D.R, a1, a2);
-            w1 = std::max(w1, a1);
-            w2 = std::max(w2, a2);
+            w = std::max(w, D.R.field());
+            maxs = std::max(maxs, D.R.field());
             maxn = std::max(maxn, cells3(D.n));
             maxd = std::max(maxd, cells3(D.D));
         }
     }
-    double2* W1 = (double2*)take(sizeof(double2) * w1);
-    double2* W2 = (double2*)take(sizeof(double2) * w2);
-    double2* W3 = (double2*)take(sizeof(double2) * w2);
-    for (DensLevel& D : P.L) {
-        D.G.W1 = D.R.W1 = W1;
-        D.G.W2 = D.R.W2 = W2;
-        D.G.W3 = D.R.W3 = W3;
-    }
+    double2* W = (double2*)take(sizeof(double2) * w);
+    for (DensLevel& D : P.L) D.G.W = D.R.W = W;
     const size_t nb = cells3(P.L[0].D);
-    P.zbase = (double*)take(sizeof(double) * nb);
     P.carry0 = (double*)take(sizeof(double) * nb);
     if (P.nl > 1) {
         P.reg = (double*)take(sizeof(double) * maxn);
-        P.csp = (double2*)take(sizeof(double2) * maxn);
-        P.a = (double*)take(sizeof(double) * maxd);
+        P.csp = (double2*)take(sizeof(double2) * maxs);
         P.b = (double*)take(sizeof(double) * maxd);
-        P.c = (double*)take(sizeof(double) * maxd);
         P.carryA = (double*)take(sizeof(double) * maxn);
         P.carryB = (double*)take(sizeof(double) * maxn);
     }
@@ -189,25 +173,29 @@ int run_density(const DensPlan& P, const double* table, double dr, int subgrid, 
             const DensLevel& Q = P.L[l - 1];
             DN_HIP(launch_kernel_restrict(Q.T, Q.D, Q.h, D.T, D.D, table, dr, st));
         }
-        DN_HIP(spec_grid_prepare(D.G, 0, 2, 4, st));
-        DN_HIP(spec_forward_zy(D.G, D.T, nullptr, st));
-        DN_HIP(spec_x_pass(D.G, kFftForward, kFftOutRe, 0, 1.0, nullptr, nullptr, nullptr, D.T, st));
+        DN_HIP(spec_grid_prepare(D.G, l > 0 ? kSpecReplace : 0, 2, 4, st));
+        DN_HIP(spec_forward_zy(D.G, D.T, SpecField(D.D), nullptr, st));
+        DN_HIP(spec_x_spectrum(D.G, kFftRe, D.T, st));
     }
     // ---- noise: scale, refine top-down (mode replacement), then reverse Hoffman-Ribak bottom-up
     DN_HIP(launch_divide(P.L[0].mu, xi[0], cells3(P.L[0].D), std::pow(P.L[0].h, 1.5), st));
     for (int l = 1; l <= top; ++l) {
         const DensLevel& D = P.L[l];
-        DN_HIP(launch_divide(D.mu, xi[l], cells3(D.D), std::pow(D.h, 1.5), st));
         int lo[3];
         for (int a = 0; a < 3; ++a) lo[a] = D.off[a] - D.n[a] / 4;
         DN_HIP(launch_gather(P.reg, D.n, P.L[l - 1].mu, parent_box(P, l, lo), st));
         DN_HIP(spec_grid_prepare(D.R, 0, 2, 4, st));
-        DN_HIP(spec_forward_zy(D.R, P.reg, nullptr, st));
-        DN_HIP(spec_x_pass(D.R, kFftForward, kFftOutCplx, 0, 1.0, nullptr, nullptr, nullptr, P.csp, st));
-        DN_HIP(spec_grid_prepare(D.G, kSpecReplace, 2, 4, st));
-        DN_HIP(spec_forward_zy(D.G, D.mu, nullptr, st));
-        DN_HIP(spec_x_pass(D.G, kFftFwdSymInv, 0, kSymReplace, 1.0, nullptr, P.csp, D.n, nullptr, st));
-        DN_HIP(spec_inverse_yz(D.G, D.mu, nullptr, false, st));
+        DN_HIP(spec_forward_zy(D.R, P.reg, SpecField(D.n), nullptr, st));
+        DN_HIP(spec_x_spectrum(D.R, kFftForward, P.csp, st));
+        const SpecField F(D.D);
+        SpecMul m;   // the noise's own scale rides on the modes that it keeps
+        m.sym = kSymReplace;
+        m.csp = P.csp;
+        m.coarse = &D.R;
+        m.fine_scale = 1.0 / std::pow(D.h, 1.5);
+        DN_HIP(spec_forward_zy(D.G, xi[l], F, nullptr, st));
+        DN_HIP(spec_x_pass(D.G, kFftFwdSymInv, m, F, F, st));
+        DN_HIP(spec_inverse_yz(D.G, &D.mu, 1, F, false, st));
     }
     for (int l = top; l >= 1; --l) {
         const DensLevel& D = P.L[l];
@@ -216,46 +204,67 @@ int run_density(const DensPlan& P, const double* table, double dr, int subgrid, 
         DN_HIP(launch_restrict_mean(P.L[l - 1].mu, parent_box(P, l, D.off), m, D.mu, D.D, co, st));
     }
     // ---- convolutions
+    auto convolve = [&](const DensLevel& D, const SpecField& in, const double* mu, const ConvPrep* prep,
+                        const SpecField& to, double* out, bool add) -> hipError_t {
+        SpecMul m;
+        m.sym = kSymTable;
+        m.scale = D.h * D.h * D.h;
+        m.tab = D.T;
+        hipError_t e = spec_forward_zy(D.G, mu, in, prep, st);
+        if (e == hipSuccess) e = spec_x_pass(D.G, kFftFwdSymInv, m, in, to, st);
+        if (e == hipSuccess) e = spec_inverse_yz(D.G, &out, 1, to, add, st);
+        return e;
+    };
     {
         const DensLevel& B = P.L[0];
-        DN_HIP(spec_grid_prepare(B.G, 0, 2, 4, st));
-        if (top >= 1) {
-            const int m[3] = {P.L[1].n[0] / 2, P.L[1].n[1] / 2, P.L[1].n[2] / 2};
-            DN_HIP(launch_zero_box(P.zbase, B.mu, B.D, P.L[1].off, m, st));
-            DN_HIP(spec_forward_zy(B.G, B.mu, P.zbase, st));
-        } else {
-            DN_HIP(spec_forward_zy(B.G, B.mu, nullptr, st));
+        const SpecField F(B.D);
+        DN_HIP(convolve(B, F, B.mu, nullptr, F, delta[0], false));
+        if (top >= 1) {   // the noise outside the first patch, for what the patches receive
+            ConvPrep open;
+            open.mode = kPrepOpen;
+            for (int a = 0; a < 3; ++a) {
+                open.lo[a] = P.L[1].off[a];
+                open.hi[a] = P.L[1].off[a] + P.L[1].n[a] / 2;
+            }
+            DN_HIP(convolve(B, F, B.mu, &open, F, P.carry0, false));
         }
-        DN_HIP(spec_x_pass(B.G, kFftFwdSymInv, 0, kSymTable, B.h * B.h * B.h, B.T, nullptr, nullptr, nullptr, st));
-        DN_HIP(spec_inverse_yz(B.G, delta[0], top >= 1 ? P.carry0 : nullptr, false, st));
     }
     const double* src = P.carry0;
     double* dst = P.carryA;
     for (int l = 1; l <= top; ++l) {
         const DensLevel& D = P.L[l];
-        int lo[3];
-        for (int a = 0; a < 3; ++a) lo[a] = D.off[a] - D.n[a] / 4;
+        int lo[3], half[3];
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = D.off[a] - D.n[a] / 4;
+            half[a] = D.n[a] / 2;
+        }
         const bool next = l < top;
-        int nm[3] = {0, 0, 0};
-        if (next)
-            for (int a = 0; a < 3; ++a) nm[a] = P.L[l + 1].n[a] / 2;
-        DN_HIP(launch_conv_prep(P.a, P.b, next ? P.c : nullptr, D.mu, D.n, P.L[l - 1].mu, parent_box(P, l, lo),
-                                next ? P.L[l + 1].off : nullptr, next ? nm : nullptr, st));
-        DN_HIP(spec_grid_prepare(D.G, 0, 2, 4, st));
-        const double v = D.h * D.h * D.h;
-        DN_HIP(spec_forward_zy(D.G, P.a, P.b, st));
-        DN_HIP(spec_x_pass(D.G, kFftFwdSymInv, 0, kSymTable, v, D.T, nullptr, nullptr, nullptr, st));
-        DN_HIP(spec_inverse_yz(D.G, P.a, P.b, false, st));
-        // coarse contributions carried down, then this level's density
-        DN_HIP(launch_interp_cons(dst, D.n, src, parent_plain_box(P, l, D.off), st));
-        DN_HIP(launch_patch_add(delta[l], P.a, dst, D.n, st));
+        const SpecField F(D.D), own(D.n, half, D.n);   // D', and the patch's cells in it
+        // coarse contributions carried down; the noise inside the patch and minus its parent's on the
+        // padding adds this level's density to them
+        DN_HIP(launch_interp_cons(delta[l], next ? dst : nullptr, D.n, src, parent_plain_box(P, l, D.off), st));
+        ConvPrep prep;
+        prep.mode = kPrepSelf;
+        prep.par = P.L[l - 1].mu;
+        prep.pb = parent_box(P, l, lo);
+        for (int a = 0; a < 3; ++a) {
+            prep.lo[a] = half[a];
+            prep.hi[a] = half[a] + D.n[a];
+        }
+        DN_HIP(convolve(D, F, D.mu, &prep, own, delta[l], true));
         // delta_bnd restricted onto the parent cells under D' that the patch does not cover
+        prep.mode = kPrepBnd;
+        DN_HIP(convolve(D, F, D.mu, &prep, F, P.b, false));
         DN_HIP(launch_restrict_add(delta[l - 1], parent_plain_box(P, l, lo), P.b, D.n, st));
-        if (next) {
-            DN_HIP(spec_forward_zy(D.G, P.c, nullptr, st));
-            DN_HIP(spec_x_pass(D.G, kFftFwdSymInv, 0, kSymTable, v, D.T, nullptr, nullptr, nullptr, st));
-            DN_HIP(spec_inverse_yz(D.G, P.c, nullptr, false, st));
-            DN_HIP(launch_patch_add(dst, P.c, dst, D.n, st));
+        if (next) {   // the noise inside the patch and outside the next one, for what that receives
+            ConvPrep open;
+            open.mode = kPrepOpen;
+            for (int a = 0; a < 3; ++a) {
+                open.lo[a] = half[a] + P.L[l + 1].off[a];
+                open.hi[a] = open.lo[a] + P.L[l + 1].n[a] / 2;
+            }
+            const double* mu = D.mu + ((size_t)half[0] * D.D[1] + half[1]) * D.D[2] + half[2];
+            DN_HIP(convolve(D, SpecField(D.n, half, D.D), mu, &open, own, dst, true));
             src = dst;
             dst = dst == P.carryA ? P.carryB : P.carryA;
         }

@@ -202,47 +202,6 @@ __global__ void k_restrict_mean(double* __restrict__ parent, Box B, int m0, int 
     parent[box_at(B, x, y, z)] = s / 8.0;
 }
 
-// base noise with the cells of the first patch zeroed
-__global__ void k_zero_box(double* __restrict__ out, const double* __restrict__ in, int n0, int n1, int n2, int lx,
-                           int ly, int lz, int mx, int my, int mz) {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)n0 * n1 * n2) return;
-    int x, y, z;
-    unflat(idx, n1, n2, x, y, z);
-    const bool cov = x >= lx && x < lx + mx && y >= ly && y < ly + my && z >= lz && z < lz + mz;
-    out[idx] = cov ? 0.0 : in[idx];
-}
-
-// the inputs of a patch level's convolutions on D' (2n per axis):
-//   a = the noise inside the patch, noise minus its parent's value on the padding
-//   b = 0 inside the patch, noise minus its parent's value on the padding
-//   c = the noise inside the patch except the next patch's covered cells, 0 on the padding
-__global__ void k_conv_prep(double* __restrict__ a, double* __restrict__ b, double* __restrict__ c,
-                            const double* __restrict__ mu, int n0, int n1, int n2, const double* __restrict__ par,
-                            Box B, int nx0, int ny0, int nz0, int nmx, int nmy, int nmz) {
-    const int d0 = 2 * n0, d1 = 2 * n1, d2 = 2 * n2;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)d0 * d1 * d2) return;
-    int x, y, z;
-    unflat(idx, d1, d2, x, y, z);
-    const bool inside = x >= n0 / 2 && x < n0 / 2 + n0 && y >= n1 / 2 && y < n1 / 2 + n1 && z >= n2 / 2 &&
-                        z < n2 / 2 + n2;
-    const double m = mu[idx];
-    if (inside) {
-        a[idx] = m;
-        b[idx] = 0.0;
-    } else {
-        const double d = m - par[box_at(B, x >> 1, y >> 1, z >> 1)];
-        a[idx] = d;
-        b[idx] = d;
-    }
-    if (c) {
-        const int px = x - n0 / 2, py = y - n1 / 2, pz = z - n2 / 2;
-        const bool nxt = px >= nx0 && px < nx0 + nmx && py >= ny0 && py < ny0 + nmy && pz >= nz0 && pz < nz0 + nmz;
-        c[idx] = (inside && !nxt) ? m : 0.0;
-    }
-}
-
 // Section 2.3.4: conservative tri-cubic interpolation of the parent field U (box B gives the
 // parent cell of the patch's first child) onto the patch (n per axis), one thread per parent cell.
 // Child (cx, cy, cz) takes the cubic Lagrange interpolant through the 4 parent nodes on its side
@@ -250,7 +209,9 @@ __global__ void k_conv_prep(double* __restrict__ a, double* __restrict__ b, doub
 // cell, so the thread walks them once: for each (oz, oy) the 5 values along x give both children's
 // x-sums, which are added into the y-sums of the children whose nodes include oy, and those, once
 // complete for an oz, into the z-sums: the same operations in the same order for every child.
-__global__ void k_interp_cons(double* __restrict__ out, int n0, int n1, int n2, const double* __restrict__ U, Box B) {
+// Written to out and, unless it is NULL, out2.
+__global__ void k_interp_cons(double* __restrict__ out, double* __restrict__ out2, int n0, int n1, int n2,
+                              const double* __restrict__ U, Box B) {
     const int m0 = n0 / 2, m1 = n1 / 2, m2 = n2 / 2;
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (size_t)m0 * m1 * m2) return;
@@ -296,18 +257,11 @@ __global__ void k_interp_cons(double* __restrict__ out, int n0, int n1, int n2, 
     const double shift = U[box_at(B, X, Y, Z)] - mean / 8.0;
     for (int cx = 0; cx < 2; ++cx)
         for (int cy = 0; cy < 2; ++cy)
-            for (int cz = 0; cz < 2; ++cz)
-                out[((size_t)(2 * X + cx) * n1 + (2 * Y + cy)) * n2 + (2 * Z + cz)] = v[(cx * 2 + cy) * 2 + cz] + shift;
-}
-
-// out[n^3] = D'[patch] + C; out may be C itself
-__global__ void k_patch_add(double* out, const double* __restrict__ d, const double* C, int n0, int n1, int n2) {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (size_t)n0 * n1 * n2) return;
-    int x, y, z;
-    unflat(idx, n1, n2, x, y, z);
-    const size_t di = ((size_t)(x + n0 / 2) * (2 * n1) + (y + n1 / 2)) * (2 * n2) + (z + n2 / 2);
-    out[idx] = d[di] + C[idx];
+            for (int cz = 0; cz < 2; ++cz) {
+                const size_t at = ((size_t)(2 * X + cx) * n1 + (2 * Y + cy)) * n2 + (2 * Z + cz);
+                out[at] = v[(cx * 2 + cy) * 2 + cz] + shift;
+                if (out2) out2[at] = v[(cx * 2 + cy) * 2 + cz] + shift;
+            }
 }
 
 // the parent cells under D' (n per axis, box B) that the patch does not cover (the central n/2):
@@ -390,32 +344,10 @@ hipError_t launch_restrict_mean(double* parent, const DensBox& b, const int* m, 
     return hipGetLastError();
 }
 
-hipError_t launch_zero_box(double* out, const double* in, const int* n, const int* lo, const int* m, hipStream_t st) {
-    const size_t c = (size_t)n[0] * n[1] * n[2];
-    k_zero_box<<<grid_for(c), kBlock, 0, st>>>(out, in, n[0], n[1], n[2], lo[0], lo[1], lo[2], m[0], m[1], m[2]);
-    return hipGetLastError();
-}
-
-hipError_t launch_conv_prep(double* a, double* b, double* c, const double* mu, const int* n, const double* par,
-                            const DensBox& pb, const int* next_lo, const int* next_m, hipStream_t st) {
-    const size_t cnt = (size_t)8 * n[0] * n[1] * n[2];
-    const int zero[3] = {0, 0, 0};
-    const int* nl = next_lo ? next_lo : zero;
-    const int* nm = next_m ? next_m : zero;
-    k_conv_prep<<<grid_for(cnt), kBlock, 0, st>>>(a, b, c, mu, n[0], n[1], n[2], par, mkbox(pb), nl[0], nl[1], nl[2],
-                                                  nm[0], nm[1], nm[2]);
-    return hipGetLastError();
-}
-
-hipError_t launch_interp_cons(double* out, const int* n, const double* U, const DensBox& b, hipStream_t st) {
+hipError_t launch_interp_cons(double* out, double* out2, const int* n, const double* U, const DensBox& b,
+                              hipStream_t st) {
     const size_t c = (size_t)(n[0] / 2) * (n[1] / 2) * (n[2] / 2);
-    k_interp_cons<<<grid_for(c), kBlock, 0, st>>>(out, n[0], n[1], n[2], U, mkbox(b));
-    return hipGetLastError();
-}
-
-hipError_t launch_patch_add(double* out, const double* d, const double* C, const int* n, hipStream_t st) {
-    const size_t c = (size_t)n[0] * n[1] * n[2];
-    k_patch_add<<<grid_for(c), kBlock, 0, st>>>(out, d, C, n[0], n[1], n[2]);
+    k_interp_cons<<<grid_for(c), kBlock, 0, st>>>(out, out2, n[0], n[1], n[2], U, mkbox(b));
     return hipGetLastError();
 }
 

@@ -1,22 +1,37 @@
-// Three-dimensional complex FFTs for gfx950 and the spectral multipliers of Section 3.5 (finite-
-// volume and sub-grid deconvolution, the hybrid Poisson correction) and of the real-space
+// Three-dimensional FFTs of real fields for gfx950 and the spectral multipliers of Section 3.5
+// (finite-volume and sub-grid deconvolution, the hybrid Poisson correction) and of the real-space
 // transfer-function convolution of Section 2.2, fused into the transform's middle pass.
 //
-// A 3-D transform is three launches of batched 1-D transforms, one per axis.  A workgroup loads a
-// tile of nl lines into LDS, zero-extending lines that are stored shorter than the transform (the
-// zero padding of isolated boundaries is never materialised), runs a Stockham autosort FFT
-// (radix 8, with one radix-2 or radix-4 stage first when log2 N is not a multiple of 3;
-// Govindaraju et al. 2008, "High performance discrete Fourier transforms on graphics
-// processors") with an LDS exchange between stages, and stores the first m_out points of each
-// line.  Lines along z are contiguous in memory: the tile
-// loads each line as one run.  Along y and x a tile holds nl lines that are consecutive in z, so
-// every global access is a run of nl consecutive elements.  In LDS the tile is interleaved, point
-// i of line l at i * (nl + 1) + l: lane-consecutive lines are address-consecutive during the
-// stages, and the odd stride keeps the contiguous-line loads free of bank conflicts.  The N
-// twiddles of the transform length follow the tile in LDS.
+// The spectrum of a real field is Hermitian, so only its modes kz = 0 .. M, M = P2 / 2, are formed
+// and stored: rows of zs >= M + 1 complex points, half the bytes of a complex transform in every
+// pass.  A 3-D transform is three launches of batched 1-D transforms:
+//   z  (k_fft_zf / k_fft_zi)  a line of 2M reals is read as M complex points (even, odd), run
+//      through a complex transform of length M and separated into M + 1 modes (and back);
+//   y, x  (k_fft_lines)  complex lines, strided in memory, transformed in place.
+// Between the passes the field stays in one buffer: every workgroup reads all of its lines before
+// it writes the same lines back, and at 256^3 that buffer (142 MB) stays in the Infinity Cache.
 //
-// The x pass can run forward, multiply every element by a multiplier of its (kx, ky, kz), and
-// run the inverse in the same launch: the spectrum of the x pass never goes to memory.
+// A workgroup transforms a tile of T threads x 8 points by a Stockham autosort FFT (radix 8, with
+// one radix-2 or radix-4 stage when log2 N is not a multiple of 3; Govindaraju et al. 2008, "High
+// performance discrete Fourier transforms on graphics processors").  Every thread holds its 8
+// points in registers: the first stage takes them straight from global memory and the last stage
+// stores them there, so LDS carries only the exchanges between stages (two for N = 256).  The
+// stages run small radix first forwards and last backwards: the points that a thread holds after
+// the forward transform are those that it needs for the inverse, so the x pass forms the spectrum,
+// multiplies it and transforms it back without an exchange, a store or a load in between.
+//
+// Tiles of the strided passes hold NL lines that are consecutive in kz (8 at N = 256: runs of 128
+// bytes).  The lines kz < M of all rows are numbered through, M per row; the Nyquist lines kz = M
+// follow after them, so that no tile is left nearly empty for the odd mode.
+//
+// Bound: the plain passes by the Infinity Cache (a 64 MB device copy reaches 6.9 TB/s), the fused x
+// passes by LDS exchanges and FP64 arithmetic at 4-5 waves per SIMD.  Measured at 256^3 (MI355X), per
+// field, against the same passes with complex fields through W1, W2, W3 and an LDS round trip per
+// stage: z forward 87 -> 58 us, y forward 116 -> 50 us (5.6 TB/s), y inverse 107 -> 45 us, z inverse
+// stored 92 (two fields) -> 52 us, table multiplier 193 (two fields) -> 65 us, hybrid correction
+// 175 + 164 -> 150 us.  Radix-16 stages (16 points per thread, one exchange at N = 256) measured slower:
+// 130-180 VGPRs leave 3 waves per SIMD (y 50 -> 58 us, z inverse 52 -> 65 us).  Holding the hybrid
+// kernel to 128 VGPRs spills 72 of them: 150 -> 205 us.
 
 #include "spec_internal.h"
 
@@ -76,93 +91,125 @@ __device__ __forceinline__ void dft(double2* v) {
     }
 }
 
-// One Stockham stage on a tile of nl interleaved lines of length N = 2^lgN.  Butterfly j of a
-// line reads points j + r N/R, twiddles them by w^(r k N / (Ns R)) with k = j mod Ns, and writes
-// the radix-R DFT to points (j - k) R + k + r Ns.  twl holds e^{-2 pi i t / N}, t < N, in LDS.
-template <int R, bool INV>
-__device__ __forceinline__ void fft_stage(double2* lds, const double2* twl, int lgN, int lgnl, int lgNs) {
-    constexpr int kIt = kFftTile / (R * kBlock);
-    constexpr int lgR = R == 8 ? 3 : (R == 4 ? 2 : 1);
-    const int nl = 1 << lgnl, LS = nl + 1;
-    const int P = 1 << (lgN - lgR);
-    const int items = nl * P;
-    const int Ns = 1 << lgNs;
-    const int tws = lgN - lgNs - lgR;   // k * N / (Ns R) = k << tws
-    double2 v[kIt][R];
-    int dst[kIt];
+// ---- the stages --------------------------------------------------------------------------------
+// log2 radix and log2 of the sub-transform length before stage s of a length-2^LGN transform: the
+// remainder stage (radix 2^(LGN % 3)) first, or last (REV)
+template <int LGN>
+struct Stages {
+    static constexpr int lgF = LGN % 3;
+    static constexpr int count = LGN / 3 + (lgF ? 1 : 0);
+    static constexpr int lg_radix(bool rev, int s) {
+        if (!lgF) return 3;
+        return s == (rev ? count - 1 : 0) ? lgF : 3;
+    }
+    static constexpr int lg_ns(bool rev, int s) {
+        int t = 0;
+        for (int i = 0; i < s; ++i) t += lg_radix(rev, i);
+        return t;
+    }
+};
+
+// threads and lines of a strided tile: 8 points per thread; at N = 512 and 1024 twice the threads,
+// so that a tile still holds runs of 8 (4) lines
+template <int LGN>
+constexpr int kFftThreads = LGN >= 9 ? 512 : 256;
+template <int LGN>
+constexpr int kFftLgLines = (LGN >= 9 ? 12 : 11) - LGN;
+
+// where point i of line l sits in LDS (in complex points), and which line and butterfly item q of a
+// stage with P = 2^lgP butterflies per line is.  Strided tiles interleave their lines at an odd
+// stride (consecutive lanes are consecutive lines); contiguous ones (LINES = false) keep a line
+// together with one point of padding after every 8 (consecutive lanes are consecutive points, and
+// a radix-8 stage writes at a stride of 8).
+template <int LGN, int LGNL, bool STRIDED>
+struct Tile {
+    static constexpr int kRow = STRIDED ? (1 << LGNL) + 1 : (1 << LGN) + ((1 << LGN) >> 3);
+    static constexpr int kPoints = STRIDED ? (kRow << LGN) : (kRow << LGNL);
+    __device__ static __forceinline__ int at(int l, int i) { return STRIDED ? i * kRow + l : l * kRow + i + (i >> 3); }
+    __device__ static __forceinline__ void item(int q, int lgP, int& l, int& j) {
+        if (STRIDED) {
+            l = q & ((1 << LGNL) - 1);
+            j = q >> LGNL;
+        } else {
+            l = q >> lgP;
+            j = q & ((1 << lgP) - 1);
+        }
+    }
+};
+
+// Stage S on the thread's 8 points (8 / R butterflies): twiddle point r of butterfly j by
+// w^(r k N / (Ns R)), k = j mod Ns, then the radix-R DFT.  twl holds e^{-2 pi i t / N} in LDS.
+template <int LGN, int LGNL, bool STRIDED, bool REV, bool INV, int S, int T>
+__device__ __forceinline__ void stage_dft(double2* v, const double2* twl) {
+    constexpr int lgR = Stages<LGN>::lg_radix(REV, S), R = 1 << lgR, lgNs = Stages<LGN>::lg_ns(REV, S);
 #pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int q = (int)threadIdx.x + it * kBlock;
-        if (q < items) {
-            const int l = q & (nl - 1), j = q >> lgnl;
-            const int k = j & (Ns - 1);
-#pragma unroll
-            for (int r = 0; r < R; ++r) v[it][r] = lds[(j + r * P) * LS + l];
-            const int step = k << tws;
+    for (int it = 0; it < 8 / R; ++it) {
+        if (lgNs > 0) {
+            int l, j;
+            Tile<LGN, LGNL, STRIDED>::item((int)threadIdx.x + it * T, LGN - lgR, l, j);
+            const int step = (j & ((1 << lgNs) - 1)) << (LGN - lgNs - lgR);
 #pragma unroll
             for (int r = 1; r < R; ++r) {
                 double2 w = twl[r * step];
                 if (INV) w.y = -w.y;
-                v[it][r] = cmul(v[it][r], w);
+                v[it * R + r] = cmul(v[it * R + r], w);
             }
-            dft<R, INV>(v[it]);
-            dst[it] = ((j - k) << lgR) + k;
         }
+        dft<R, INV>(v + it * R);
     }
-    __syncthreads();
+}
+
+// point r of butterfly j before stage S, and where the stage's DFT puts it
+template <int LGN, bool REV, int S>
+__device__ __forceinline__ int point_in(int j, int r) {
+    return j + (r << (LGN - Stages<LGN>::lg_radix(REV, S)));
+}
+template <int LGN, bool REV, int S>
+__device__ __forceinline__ int point_out(int j, int r) {
+    constexpr int lgR = Stages<LGN>::lg_radix(REV, S), lgNs = Stages<LGN>::lg_ns(REV, S);
+    const int k = j & ((1 << lgNs) - 1);
+    return ((j - k) << lgR) + k + (r << lgNs);
+}
+
+// calls f(slot, line, point) for the 8 points that the thread holds before (OUT: after) stage S
+template <int LGN, int LGNL, bool STRIDED, bool REV, int S, bool OUT, int T, typename F>
+__device__ __forceinline__ void each_point(F&& f) {
+    constexpr int lgR = Stages<LGN>::lg_radix(REV, S), R = 1 << lgR;
 #pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int q = (int)threadIdx.x + it * kBlock;
-        if (q < items) {
-            const int l = q & (nl - 1);
+    for (int it = 0; it < 8 / R; ++it) {
+        int l, j;
+        Tile<LGN, LGNL, STRIDED>::item((int)threadIdx.x + it * T, LGN - lgR, l, j);
 #pragma unroll
-            for (int r = 0; r < R; ++r) lds[(dst[it] + r * Ns) * LS + l] = v[it][r];
-        }
+        for (int r = 0; r < R; ++r)
+            f(it * R + r, l, OUT ? point_out<LGN, REV, S>(j, r) : point_in<LGN, REV, S>(j, r));
     }
+}
+
+// exchange through LDS: the points after stage S become those before stage S + 1
+template <int LGN, int LGNL, bool STRIDED, bool REV, int S, int T>
+__device__ __forceinline__ void exchange(double2* v, double2* lds) {
+    __syncthreads();   // the previous use of lds is over
+    each_point<LGN, LGNL, STRIDED, REV, S, true, T>(
+        [&](int s, int l, int i) { lds[Tile<LGN, LGNL, STRIDED>::at(l, i)] = v[s]; });
     __syncthreads();
+    each_point<LGN, LGNL, STRIDED, REV, S + 1, false, T>(
+        [&](int s, int l, int i) { v[s] = lds[Tile<LGN, LGNL, STRIDED>::at(l, i)]; });
 }
 
-template <bool INV>
-__device__ __forceinline__ void fft_tile(double2* lds, const double2* twl, int lgN, int lgnl) {
-    int lgNs = 0;
-    const int rem = lgN % 3;
-    if (rem == 1) {
-        fft_stage<2, INV>(lds, twl, lgN, lgnl, 0);
-        lgNs = 1;
-    } else if (rem == 2) {
-        fft_stage<4, INV>(lds, twl, lgN, lgnl, 0);
-        lgNs = 2;
-    }
-    for (; lgNs < lgN; lgNs += 3) fft_stage<8, INV>(lds, twl, lgN, lgnl, lgNs);
-}
-
-template <int IN>
-__device__ __forceinline__ double2 load_in(const FftPass& A, long long idx) {
-    if (IN == kFftInCplx) return ((const double2*)A.in0)[idx];
-    if (IN == kFftInRe) return make_double2(((const double*)A.in0)[idx], 0.0);
-    return make_double2(((const double*)A.in0)[idx], ((const double*)A.in1)[idx]);
-}
-
-template <int OUT>
-__device__ __forceinline__ void store_out(const FftPass& A, long long idx, double2 v) {
-    if (OUT == kFftOutCplx) {
-        ((double2*)A.out0)[idx] = v;
-    } else if (OUT == kFftOutRe) {
-        ((double*)A.out0)[idx] = v.x;
-    } else if (OUT == kFftOutRePairStore) {
-        ((double*)A.out0)[idx] = v.x;
-        if (A.out1) ((double*)A.out1)[idx] = v.y;
-    } else {   // kFftOutRePairAdd
-        double* o0 = (double*)A.out0;
-        o0[idx] = o0[idx] + v.x;
-        if (A.out1) {
-            double* o1 = (double*)A.out1;
-            o1[idx] = o1[idx] + v.y;
+// the whole transform of the 8 points in v: before, those of stage 0; after, those of the last stage
+template <int LGN, int LGNL, bool STRIDED, bool INV, int T, int S = 0>
+__device__ __forceinline__ void fft_regs(double2* v, double2* lds, const double2* twl) {
+    if constexpr (S < Stages<LGN>::count) {
+        stage_dft<LGN, LGNL, STRIDED, INV, INV, S, T>(v, twl);
+        if constexpr (S + 1 < Stages<LGN>::count) {
+            exchange<LGN, LGNL, STRIDED, INV, S, T>(v, lds);
+            fft_regs<LGN, LGNL, STRIDED, INV, T, S + 1>(v, lds, twl);
         }
     }
 }
 
-// the multiplier of spectral element (kx, ky, kz) = (i, a, b), applied to v
+// ---- multipliers -------------------------------------------------------------------------------
+// the multiplier of spectral element (kx, ky, kz) = (i, a, b), b <= P2 / 2, applied to v
 template <int SYM>
 __device__ __forceinline__ double2 apply_sym(const FftPass& A, int i, int a, int b, double2 v) {
     const double c = A.sym_scale;
@@ -181,156 +228,346 @@ __device__ __forceinline__ double2 apply_sym(const FftPass& A, int i, int a, int
         const double m = c / lam;
         return make_double2(v.x * m, v.y * m);
     }
-    if (SYM == kSymReplace) {
-        // modes below the coarse grid's Nyquist on every axis take 8 C(m) prod_a e^{-i pi m_a / P_a}
-        // (per-axis phase tables hold cos, sin pairs); the rest keep the fine spectrum
-        const int px = A.sym_n[0], py = A.sym_n[1], pz = A.sym_n[2];
-        const int mx = i < px / 2 ? i : i - px, my = a < py / 2 ? a : a - py, mz = b < pz / 2 ? b : b - pz;
-        const int cx = A.cn[0], cy = A.cn[1], cz = A.cn[2];
-        if (2 * abs(mx) < cx && 2 * abs(my) < cy && 2 * abs(mz) < cz) {
-            const int ix = mx < 0 ? mx + cx : mx, iy = my < 0 ? my + cy : my, iz = mz < 0 ? mz + cz : mz;
-            const double2 C = A.csp[((long long)ix * cy + iy) * cz + iz];
-            double2 w = make_double2(8.0 * C.x, 8.0 * C.y);
-            w = cmul(w, make_double2(A.tab_x[2 * i], A.tab_x[2 * i + 1]));
-            w = cmul(w, make_double2(A.tab_y[2 * a], A.tab_y[2 * a + 1]));
-            w = cmul(w, make_double2(A.tab_z[2 * b], A.tab_z[2 * b + 1]));
-            v = w;
-        }
-        return make_double2(v.x * c, v.y * c);
+    // kSymReplace: modes below the coarse grid's Nyquist on every axis take 8 C(m) prod_a
+    // e^{-i pi m_a / P_a} (per-axis phase tables hold cos, sin pairs); the rest keep the fine spectrum
+    const int px = A.sym_n[0], py = A.sym_n[1];
+    const int mx = i < px / 2 ? i : i - px, my = a < py / 2 ? a : a - py;
+    const int cx = A.cn[0], cy = A.cn[1], cz = A.cn[2];
+    if (2 * abs(mx) < cx && 2 * abs(my) < cy && 2 * b < cz) {
+        const int ix = mx < 0 ? mx + cx : mx, iy = my < 0 ? my + cy : my;
+        const double2 C = A.csp[((long long)ix * cy + iy) * A.csp_zs + b];
+        double2 w = make_double2(8.0 * C.x, 8.0 * C.y);
+        w = cmul(w, make_double2(A.tab_x[2 * i], A.tab_x[2 * i + 1]));
+        w = cmul(w, make_double2(A.tab_y[2 * a], A.tab_y[2 * a + 1]));
+        w = cmul(w, make_double2(A.tab_z[2 * b], A.tab_z[2 * b + 1]));
+        return make_double2(w.x * c, w.y * c);
     }
-    // hybrid correction: per-axis blocks [k^2 | lambda_1d | k (0 on Nyquist) | g (0 on Nyquist)]
-    const double* X = A.tab_x;
-    const double* Y = A.tab_y;
-    const double* Z = A.tab_z;
-    const int px = A.sym_n[0], py = A.sym_n[1], pz = A.sym_n[2];
-    const double k2 = (X[i] + Y[a]) + Z[b];
-    if (k2 == 0.0) return make_double2(0.0, 0.0);
-    const double lam = (X[px + i] + Y[py + a]) + Z[pz + b];
-    if (SYM == kSymHybridXY) {
-        // components x and y packed as one complex field: (i s_x - s_y) f~
-        const double sx = -X[2 * px + i] / k2 - X[3 * px + i] / lam;
-        const double sy = -Y[2 * py + a] / k2 - Y[3 * py + a] / lam;
-        return cmul(v, make_double2(-sy * c, sx * c));
-    }
-    const double sz = -Z[2 * pz + b] / k2 - Z[3 * pz + b] / lam;
-    return cmul(v, make_double2(0.0, sz * c));
+    return make_double2(v.x * A.fine_scale, v.y * A.fine_scale);
 }
 
-// One pass of 1-D transforms of length N = 2^lgN over the lines (a, b) of a 3-D array.
-// CONTIG: lines are contiguous (si = 1), a tile is nl consecutive a (b unused).
-// Otherwise: a tile is one a and nl consecutive b (sb = 1).
-// Tile point e (of nl N) is line e >> lgN, point e & (N - 1) (CONTIG), or line e & (nl - 1), point
-// e >> lgnl: consecutive lanes touch consecutive global addresses either way.  Every lane issues
-// all of its loads before it writes any of them to LDS.
-template <bool CONTIG>
-__device__ __forceinline__ void tile_coords(int e, int lgN, int lgnl, int& l, int& i) {
-    if (CONTIG) {
-        l = e >> lgN;
-        i = e & ((1 << lgN) - 1);
-    } else {
-        l = e & ((1 << lgnl) - 1);
-        i = e >> lgnl;
+// ---- strided passes ----------------------------------------------------------------------------
+// The lines of a pass: kz < M of every row a < na, M per row, then kz = M of every row.
+__device__ __forceinline__ bool line_at(const FftPass& A, long long L, int& a, int& b) {
+    const long long reg = (long long)A.na << A.lgM;
+    if (L < reg) {
+        a = (int)(L >> A.lgM);
+        b = (int)(L & ((1 << A.lgM) - 1));
+        return true;
     }
+    a = (int)(L - reg);
+    b = 1 << A.lgM;
+    return a < A.na;
 }
 
-template <bool CONTIG, int IN, int OUT, int OP, int SYM>
-__global__ __launch_bounds__(kBlock) void k_fft_pass(FftPass A) {
+// One pass over lines of length N = 2^LGN, field blockIdx.y.  OP: kFftForward, kFftInverse; kFftRe
+// forward with the real part stored into a table; kFftFwdSymInv forward, multiply, inverse in one
+// launch; kFftHybrid the same with the three components of the hybrid correction, from one input
+// into fields 0, 1, 2 (the spectrum stays in registers between them).
+template <int LGN, int OP, int SYM>
+__global__ __launch_bounds__(kFftThreads<LGN>) void k_fft_lines(FftPass A) {
+    constexpr int T = kFftThreads<LGN>, LGNL = kFftLgLines<LGN>, NL = 1 << LGNL, N = 1 << LGN;
+    constexpr bool kInv = OP == kFftInverse;
+    using TL = Tile<LGN, LGNL, true>;
     extern __shared__ __align__(16) unsigned char fft_smem[];
-    constexpr int kLd = kFftTile / kBlock;
-    const int lgnl = A.lgnl, nl = 1 << lgnl, LS = nl + 1, lgN = A.lgN, N = 1 << lgN;
     double2* lds = (double2*)fft_smem;
-    double2* twl = lds + N * LS;
-    int a, b0;
-    if (CONTIG) {
-        a = (int)blockIdx.x << lgnl;
-        b0 = 0;
+    double2* twl = lds + TL::kPoints;
+    const double2* in = (const double2*)A.in + (long long)blockIdx.y * A.fs;
+    double2* out = (double2*)A.out + (long long)blockIdx.y * A.fs;
+    // the lines of this thread's points: one (NL <= T), or one per butterfly
+    constexpr int kL = NL > T ? NL / T : 1;
+    int la[kL], lb[kL];
+    bool ok[kL];
+#pragma unroll
+    for (int t = 0; t < kL; ++t)
+        ok[t] = line_at(A, ((long long)blockIdx.x << LGNL) + (((int)threadIdx.x + t * T) & (NL - 1)), la[t], lb[t]);
+    auto slot_line = [](int s) { return kL == 1 ? 0 : s >> LGN; };   // kL > 1: one butterfly a line
+    double2 v[8];
+    each_point<LGN, LGNL, true, kInv, 0, false, T>([&](int s, int l, int i) {
+        const int t = slot_line(s);
+        v[s] = make_double2(0.0, 0.0);
+        if (ok[t] && i >= A.in_lo && i < A.in_hi)
+            v[s] = in[(long long)la[t] * A.in_sa + lb[t] + (long long)i * A.in_si];
+    });
+    for (int t = (int)threadIdx.x; t < N; t += T) twl[t] = A.tw[t << (A.lgtw - LGN)];
+    constexpr int kLast = Stages<LGN>::count - 1;
+    auto store = [&](double2* to) {
+        each_point<LGN, LGNL, true, true, kLast, true, T>([&](int s, int l, int i) {
+            const int t = slot_line(s);
+            if (ok[t] && i >= A.out_lo && i < A.out_hi)
+                to[(long long)la[t] * A.out_sa + lb[t] + (long long)i * A.out_si] = v[s];
+        });
+    };
+    if constexpr (kInv) {
+        fft_regs<LGN, LGNL, true, true, T>(v, lds, twl);
+        store(out);
     } else {
-        const int nbt = (A.nb + nl - 1) >> lgnl;
-        a = (int)blockIdx.x / nbt;
-        b0 = ((int)blockIdx.x - a * nbt) << lgnl;
-    }
-    const int total = nl << lgN;
-    // load (zero beyond m_in and for lines past the end), with this length's twiddles
-    {
-        double2 r[kLd];
+        fft_regs<LGN, LGNL, true, false, T>(v, lds, twl);
+        if constexpr (OP == kFftForward || OP == kFftRe) {
+            each_point<LGN, LGNL, true, false, kLast, true, T>([&](int s, int l, int i) {
+                const int t = slot_line(s);
+                if (!ok[t] || i >= A.out_hi) return;
+                const long long at = (long long)la[t] * A.out_sa + lb[t] + (long long)i * A.out_si;
+                if (OP == kFftRe) ((double*)A.out)[at] = v[s].x;
+                else out[at] = v[s];
+            });
+        } else if constexpr (OP == kFftFwdSymInv) {
+            each_point<LGN, LGNL, true, false, kLast, true, T>([&](int s, int l, int i) {
+                const int t = slot_line(s);
+                if (ok[t]) v[s] = apply_sym<SYM>(A, i, la[t], lb[t], v[s]);
+            });
+            fft_regs<LGN, LGNL, true, true, T>(v, lds, twl);
+            store(out);
+        } else {
+            // hybrid correction, component c: i s_c f~, s_c = -k_c / k^2 - g_c / lambda; per-axis
+            // blocks [k^2 | lambda_1d | k (0 on Nyquist) | g (0 on Nyquist)]
+            const int px = A.sym_n[0], py = A.sym_n[1], pz = A.sym_n[2];
+            double2 f[8];
+            double rk[8], rl[8];   // -scale / k^2 and -scale / lambda, shared by the components
+            each_point<LGN, LGNL, true, false, kLast, true, T>([&](int s, int l, int i) {
+                const int t = slot_line(s);
+                f[s] = v[s];
+                rk[s] = rl[s] = 0.0;
+                if (!ok[t]) return;
+                const double k2 = (A.tab_x[i] + A.tab_y[la[t]]) + A.tab_z[lb[t]];
+                if (k2 == 0.0) return;
+                rk[s] = -A.sym_scale / k2;
+                rl[s] = -A.sym_scale / ((A.tab_x[px + i] + A.tab_y[py + la[t]]) + A.tab_z[pz + lb[t]]);
+            });
 #pragma unroll
-        for (int k = 0; k < kLd; ++k) {
-            const int e = (int)threadIdx.x + k * kBlock;
-            r[k] = make_double2(0.0, 0.0);
-            if (e < total) {
-                int l, i;
-                tile_coords<CONTIG>(e, lgN, lgnl, l, i);
-                if (CONTIG) {
-                    if (a + l < A.na && i < A.m_in) r[k] = load_in<IN>(A, (long long)(a + l) * A.in_sa + i);
-                } else {
-                    if (b0 + l < A.nb && i < A.m_in)
-                        r[k] = load_in<IN>(A, (long long)a * A.in_sa + b0 + l + (long long)i * A.in_si);
-                }
-            }
-        }
-        for (int t = (int)threadIdx.x; t < N; t += kBlock) twl[t] = A.tw[t << (A.lgtw - lgN)];
-#pragma unroll
-        for (int k = 0; k < kLd; ++k) {
-            const int e = (int)threadIdx.x + k * kBlock;
-            if (e < total) {
-                int l, i;
-                tile_coords<CONTIG>(e, lgN, lgnl, l, i);
-                lds[i * LS + l] = r[k];
-            }
-        }
-    }
-    __syncthreads();
-    if (OP == kFftInverse) {
-        fft_tile<true>(lds, twl, lgN, lgnl);
-    } else {
-        fft_tile<false>(lds, twl, lgN, lgnl);
-        if (OP == kFftFwdSymInv) {
-#pragma unroll
-            for (int k = 0; k < kLd; ++k) {
-                const int e = (int)threadIdx.x + k * kBlock;
-                if (e < total) {
-                    const int l = e & (nl - 1), i = e >> lgnl;
-                    if (b0 + l < A.nb) lds[i * LS + l] = apply_sym<SYM>(A, i, a, b0 + l, lds[i * LS + l]);
-                }
-            }
-            __syncthreads();
-            fft_tile<true>(lds, twl, lgN, lgnl);
-        }
-    }
-    // store the first m_out points of every line
-#pragma unroll
-    for (int k = 0; k < kLd; ++k) {
-        const int e = (int)threadIdx.x + k * kBlock;
-        if (e < total) {
-            int l, i;
-            tile_coords<CONTIG>(e, lgN, lgnl, l, i);
-            if (i < A.m_out) {
-                if (CONTIG) {
-                    if (a + l < A.na) store_out<OUT>(A, (long long)(a + l) * A.out_sa + i, lds[i * LS + l]);
-                } else {
-                    if (b0 + l < A.nb)
-                        store_out<OUT>(A, (long long)a * A.out_sa + b0 + l + (long long)i * A.out_si, lds[i * LS + l]);
-                }
+            for (int c = 0; c < 3; ++c) {
+                each_point<LGN, LGNL, true, false, kLast, true, T>([&](int s, int l, int i) {
+                    const int t = slot_line(s);
+                    if (!ok[t]) return;
+                    const int a = la[t], b = lb[t];
+                    const double kc = c == 0 ? A.tab_x[2 * px + i] : (c == 1 ? A.tab_y[2 * py + a] : A.tab_z[2 * pz + b]);
+                    const double gc = c == 0 ? A.tab_x[3 * px + i] : (c == 1 ? A.tab_y[3 * py + a] : A.tab_z[3 * pz + b]);
+                    const double m = kc * rk[s] + gc * rl[s];
+                    v[s] = make_double2(-f[s].y * m, f[s].x * m);
+                });
+                fft_regs<LGN, LGNL, true, true, T>(v, lds, twl);
+                store((double2*)A.out + (long long)c * A.fs);
             }
         }
     }
 }
 
-// e^{-2 pi i t / 2^lg} for t < 2^lg
-__global__ void k_fft_twiddles(double2* tw, int lg) {
-    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (t >= (1 << lg)) return;
-    double s, c;
-    sincospi(2.0 * (double)t / (double)(1 << lg), &s, &c);
-    tw[t] = make_double2(c, -s);
+// ---- z passes ----------------------------------------------------------------------------------
+constexpr int kZThreads = 256;
+template <int LGM>
+constexpr int kZLgLines = 11 - LGM;
+
+// line L is row y = L % rows of x plane L / rows, counted from the first row of the pass
+struct ZLine {
+    int x, y;
+    __device__ __forceinline__ ZLine(const FftPass& A, int L) {
+        x = (int)((unsigned)L / (unsigned)A.rows);
+        y = L - x * A.rows;
+    }
+    __device__ __forceinline__ long long spectrum(const FftPass& A) const { return ((long long)x * A.plane + y) * A.zs; }
+    __device__ __forceinline__ long long real(const FftPass& A) const { return x * A.rsx + y * A.rsy; }
+};
+
+// points z, z + 1 of the input of a multi-scale convolution on a patch's padded domain D' (the
+// patch at [n/2, 3n/2) of it), formed from the noise mu and its parent's par:
+//   kPrepSelf   the noise inside the patch, noise minus its parent's value on the padding
+//   kPrepBnd    0 inside the patch, noise minus its parent's value on the padding
+//   kPrepOpen   the noise, 0 in the cells that the next patch covers
+__device__ __forceinline__ double2 conv_input(const ConvPrep& C, int x, int y, int z, double2 m) {
+    if (C.mode == kPrepOpen) {
+        if (x >= C.lo[0] && x < C.hi[0] && y >= C.lo[1] && y < C.hi[1]) {
+            if (z >= C.lo[2] && z < C.hi[2]) m.x = 0.0;
+            if (z + 1 >= C.lo[2] && z + 1 < C.hi[2]) m.y = 0.0;
+        }
+        return m;
+    }
+    // the patch's bounds are even along z: both points lie inside, or both outside
+    if (x >= C.lo[0] && x < C.hi[0] && y >= C.lo[1] && y < C.hi[1] && z >= C.lo[2] && z < C.hi[2])
+        return C.mode == kPrepSelf ? m : make_double2(0.0, 0.0);
+    int p[3] = {C.pb.lo[0] + (x >> 1), C.pb.lo[1] + (y >> 1), C.pb.lo[2] + (z >> 1)};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (C.pb.wrap) {   // D' covers at most the whole base: one turn is enough
+            if (p[a] < 0) p[a] += C.pb.wrap;
+            if (p[a] >= C.pb.wrap) p[a] -= C.pb.wrap;
+        }
+        p[a] += C.pb.po[a];
+    }
+    const double v = C.par[((long long)p[0] * C.pb.pd[1] + p[1]) * C.pb.pd[2] + p[2]];
+    return make_double2(m.x - v, m.y - v);
+}
+
+// Forward z pass: the reals in_lo <= z < in_hi of every line, zero-extended to N = 2M = 2^(LGM + 1),
+// to modes 0 .. M.  PREP: the reals are formed by conv_input.
+// With Z the transform of the complex line (x_2i + i x_2i+1), E = (Z[k] + conj Z[M-k]) / 2 and
+// O = (Z[k] - conj Z[M-k]) / 2:  X[k] = E - i w^k O and X[M-k] = conj(E + i w^k O), w = e^{-2 pi i / N}.
+template <int LGM, bool PREP>
+__global__ __launch_bounds__(kZThreads) void k_fft_zf(FftPass A, ConvPrep C) {
+    constexpr int T = kZThreads, LGNL = kZLgLines<LGM>, M = 1 << LGM;
+    using TL = Tile<LGM, LGNL, false>;
+    extern __shared__ __align__(16) unsigned char fft_smem[];
+    double2* lds = (double2*)fft_smem;
+    double2* twl = lds + TL::kPoints;
+    const double* in = (const double*)A.rin[blockIdx.y];
+    double2* out = (double2*)A.out + (long long)blockIdx.y * A.fs;
+    const int L0 = (int)blockIdx.x << LGNL;
+    const bool pairs = A.vec & (1 << blockIdx.y);
+    double2 v[8];
+    auto load = [&](int s, int l, int i) {
+        const int L = L0 + l, z = 2 * i;
+        v[s] = make_double2(0.0, 0.0);
+        if (L < A.na && z >= A.in_lo && z < A.in_hi) {
+            const ZLine zl(A, L);
+            const double* p = in + zl.real(A) + (z - A.in_lo);
+            if (pairs) {
+                v[s] = *(const double2*)p;
+            } else {
+                v[s].x = p[0];
+                if (z + 1 < A.in_hi) v[s].y = p[1];
+            }
+            if (PREP) v[s] = conv_input(C, zl.x + C.x0, zl.y + C.y0, z, v[s]);
+        }
+    };
+    if constexpr (LGM == 0) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int l = (int)threadIdx.x + s * T, L = L0 + l;
+            load(s, l, 0);
+            if (L < A.na) {
+                const long long at = ZLine(A, L).spectrum(A);
+                out[at] = make_double2(v[s].x + v[s].y, 0.0);
+                out[at + 1] = make_double2(v[s].x - v[s].y, 0.0);
+            }
+        }
+    } else {
+        each_point<LGM, LGNL, false, false, 0, false, T>(load);
+        for (int t = (int)threadIdx.x; t < M; t += T) twl[t] = A.tw[t << (A.lgtw - LGM)];
+        fft_regs<LGM, LGNL, false, false, T>(v, lds, twl);
+        __syncthreads();
+        each_point<LGM, LGNL, false, false, Stages<LGM>::count - 1, true, T>(
+            [&](int s, int l, int i) { lds[TL::at(l, i)] = v[s]; });
+        __syncthreads();
+        constexpr int kItems = 1 << (LGM - 1 + LGNL);
+#pragma unroll
+        for (int q = (int)threadIdx.x; q < kItems; q += T) {
+            const int l = q >> (LGM - 1), k = q & (M / 2 - 1), L = L0 + l;
+            if (L >= A.na) continue;
+            double2* row = out + ZLine(A, L).spectrum(A);
+            const double2 a = lds[TL::at(l, k)];
+            if (k == 0) {
+                row[0] = make_double2(a.x + a.y, 0.0);
+                row[M] = make_double2(a.x - a.y, 0.0);
+                const double2 h = lds[TL::at(l, M / 2)];
+                row[M / 2] = make_double2(h.x, -h.y);
+                continue;
+            }
+            const double2 b = lds[TL::at(l, M - k)];
+            const double2 E = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
+            const double2 O = make_double2(0.5 * (a.x - b.x), 0.5 * (a.y + b.y));
+            const double2 w = A.tw[k << (A.lgtw - LGM - 1)];
+            const double2 wo = cmul(w, O);
+            const double2 t = make_double2(wo.y, -wo.x);   // -i w O
+            row[k] = cadd(E, t);
+            row[M - k] = make_double2(E.x - t.x, t.y - E.y);
+        }
+    }
+}
+
+// Inverse z pass: modes 0 .. M to the reals out_lo <= z < out_hi of every line, stored or added.
+// 2 Z[k] = E + O and 2 Z[M-k] = conj(E - O), E = X[k] + conj X[M-k], O = i conj(w^k) (X[k] - conj X[M-k]).
+template <int LGM, bool ADD>
+__global__ __launch_bounds__(kZThreads) void k_fft_zi(FftPass A) {
+    constexpr int T = kZThreads, LGNL = kZLgLines<LGM>, M = 1 << LGM;
+    using TL = Tile<LGM, LGNL, false>;
+    extern __shared__ __align__(16) unsigned char fft_smem[];
+    double2* lds = (double2*)fft_smem;
+    double2* twl = lds + TL::kPoints;
+    const double2* in = (const double2*)A.in + (long long)blockIdx.y * A.fs;
+    double* out = (double*)A.rout[blockIdx.y];
+    const int L0 = (int)blockIdx.x << LGNL;
+    const bool pairs = A.vec & (1 << blockIdx.y);
+    double2 v[8];
+    auto store = [&](int s, int l, int i) {
+        const int L = L0 + l, z = 2 * i - A.out_lo;
+        const int m = A.out_hi - A.out_lo;
+        if (L >= A.na || z < 0 || z >= m) return;
+        double* p = out + ZLine(A, L).real(A) + z;
+        if (pairs) {
+            double2 o = v[s];
+            if (ADD) o = cadd(*(const double2*)p, o);
+            *(double2*)p = o;
+        } else {
+            p[0] = ADD ? p[0] + v[s].x : v[s].x;
+            if (z + 1 < m) p[1] = ADD ? p[1] + v[s].y : v[s].y;
+        }
+    };
+    if constexpr (LGM == 0) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int l = (int)threadIdx.x + s * T, L = L0 + l;
+            if (L < A.na) {
+                const long long at = ZLine(A, L).spectrum(A);
+                const double2 x0 = in[at], x1 = in[at + 1];
+                v[s] = make_double2(x0.x + x1.x, x0.x - x1.x);
+                store(s, l, 0);
+            }
+        }
+    } else {
+        constexpr int kItems = 1 << (LGM - 1 + LGNL);
+        constexpr int kPer = kItems / T;
+        double2 x[kPer], y[kPer], xh[kPer];
+#pragma unroll
+        for (int n = 0; n < kPer; ++n) {
+            const int q = (int)threadIdx.x + n * T;
+            const int l = q >> (LGM - 1), k = q & (M / 2 - 1), L = L0 + l;
+            x[n] = y[n] = xh[n] = make_double2(0.0, 0.0);
+            if (L < A.na) {
+                const double2* row = in + ZLine(A, L).spectrum(A);
+                x[n] = row[k];
+                y[n] = row[M - k];
+                if (k == 0) xh[n] = row[M / 2];
+            }
+        }
+        for (int t = (int)threadIdx.x; t < M; t += T) twl[t] = A.tw[t << (A.lgtw - LGM)];
+#pragma unroll
+        for (int n = 0; n < kPer; ++n) {
+            const int q = (int)threadIdx.x + n * T;
+            const int l = q >> (LGM - 1), k = q & (M / 2 - 1);
+            if (k == 0) {
+                lds[TL::at(l, 0)] = make_double2(x[n].x + y[n].x, x[n].x - y[n].x);
+                lds[TL::at(l, M / 2)] = make_double2(2.0 * xh[n].x, -2.0 * xh[n].y);
+            } else {
+                const double2 E = make_double2(x[n].x + y[n].x, x[n].y - y[n].y);
+                const double2 D = make_double2(x[n].x - y[n].x, x[n].y + y[n].y);
+                const double2 w = A.tw[k << (A.lgtw - LGM - 1)];
+                const double2 wd = cmul(make_double2(w.x, -w.y), D);
+                const double2 O = make_double2(-wd.y, wd.x);   // i conj(w) D
+                lds[TL::at(l, k)] = cadd(E, O);
+                lds[TL::at(l, M - k)] = make_double2(E.x - O.x, O.y - E.y);
+            }
+        }
+        __syncthreads();
+        each_point<LGM, LGNL, false, true, 0, false, T>(
+            [&](int s, int l, int i) { v[s] = lds[TL::at(l, i)]; });
+        fft_regs<LGM, LGNL, false, true, T>(v, lds, twl);
+        each_point<LGM, LGNL, false, true, Stages<LGM>::count - 1, true, T>(store);
+    }
 }
 
 // Per-axis multiplier tables.  Mode m of an axis of P points (m = t for t < P/2, t - P above) has
 // kh = 2 pi m / P.  kind kSymFv: 1 / sinc(kh/2); kSymSg: 1 / cos(kh/4); hybrid: the four blocks
 // [kh^2 | Laplacian symbol of the order | kh, 0 on Nyquist | gradient symbol g, 0 on Nyquist].
-__global__ void k_spec_tables(double* t0, double* t1, double* t2, int p0, int p1, int p2, int kind, int lap_order,
-                              int grad_order) {
+// kind 0: none.  The first 2^lg threads write the twiddles e^{-2 pi i t / 2^lg}.
+__global__ void k_spec_tables(double2* tw, int lg, double* t0, double* t1, double* t2, int p0, int p1, int p2,
+                              int kind, int lap_order, int grad_order) {
     int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t < (1 << lg)) {
+        double s, c;
+        sincospi(2.0 * (double)t / (double)(1 << lg), &s, &c);
+        tw[t] = make_double2(c, -s);
+        return;
+    }
+    t -= 1 << lg;
+    if (kind == 0) return;
     double* tab;
     int P;
     if (t < p0) {
@@ -395,79 +632,106 @@ __global__ void k_spec_tables(double* t0, double* t1, double* t2, int p0, int p1
     tab[3 * P + t] = nyq ? 0.0 : g;
 }
 
-template <bool CONTIG, int IN, int OUT, int OP, int SYM>
-hipError_t run_pass(const FftPass& A, hipStream_t st) {
-    const int nl = 1 << A.lgnl;
-    const unsigned lds = (unsigned)((1u << A.lgN) * (unsigned)(nl + 2) * sizeof(double2));
-    const void* fn = (const void*)k_fft_pass<CONTIG, IN, OUT, OP, SYM>;
-    static bool raised = false;
-    if (!raised) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFftMaxLds);
-        if (e != hipSuccess) return e;
-        raised = true;
-    }
-    unsigned blocks;
-    if (CONTIG) blocks = (unsigned)((A.na + nl - 1) / nl);
-    else blocks = (unsigned)A.na * (unsigned)((A.nb + nl - 1) / nl);
+
+// ---- launches ----------------------------------------------------------------------------------
+hipError_t raise_lds(const void* fn, unsigned lds) {
+    if (lds <= 65536u) return hipSuccess;
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+template <int LGN, int OP, int SYM>
+hipError_t run_lines(const FftPass& A, hipStream_t st) {
+    constexpr int LGNL = kFftLgLines<LGN>;
+    const unsigned lds = (unsigned)((Tile<LGN, LGNL, true>::kPoints + (1 << LGN)) * sizeof(double2));
+    const hipError_t e = raise_lds((const void*)k_fft_lines<LGN, OP, SYM>, lds);
+    if (e != hipSuccess) return e;
+    const long long lines = ((long long)A.na << A.lgM) + A.na;
+    const unsigned blocks = (unsigned)((lines + (1 << LGNL) - 1) >> LGNL);
     if (blocks == 0) return hipSuccess;
-    k_fft_pass<CONTIG, IN, OUT, OP, SYM><<<blocks, kBlock, lds, st>>>(A);
+    k_fft_lines<LGN, OP, SYM><<<dim3(blocks, (unsigned)A.nf), kFftThreads<LGN>, lds, st>>>(A);
     return hipGetLastError();
+}
+
+// DIR 0: forward, 1: inverse stored, 2: inverse added, 3: forward of a convolution's input
+template <int LGM, int DIR>
+hipError_t run_z(const FftPass& A, const ConvPrep& C, hipStream_t st) {
+    constexpr int LGNL = kZLgLines<LGM>;
+    const unsigned lds = (unsigned)((Tile<LGM, LGNL, false>::kPoints + (1 << LGM)) * sizeof(double2));
+    const unsigned blocks = (unsigned)(((long long)A.na + (1 << LGNL) - 1) >> LGNL);
+    if (blocks == 0) return hipSuccess;
+    const dim3 grid(blocks, (unsigned)A.nf);
+    if constexpr (DIR == 0) k_fft_zf<LGM, false><<<grid, kZThreads, lds, st>>>(A, C);
+    else if constexpr (DIR == 1) k_fft_zi<LGM, false><<<grid, kZThreads, lds, st>>>(A);
+    else if constexpr (DIR == 2) k_fft_zi<LGM, true><<<grid, kZThreads, lds, st>>>(A);
+    else k_fft_zf<LGM, true><<<grid, kZThreads, lds, st>>>(A, C);
+    return hipGetLastError();
+}
+
+template <int OP, int SYM>
+hipError_t lines_of_length(const FftPass& A, hipStream_t st) {
+    switch (A.lgN) {
+        case 1: return run_lines<1, OP, SYM>(A, st);
+        case 2: return run_lines<2, OP, SYM>(A, st);
+        case 3: return run_lines<3, OP, SYM>(A, st);
+        case 4: return run_lines<4, OP, SYM>(A, st);
+        case 5: return run_lines<5, OP, SYM>(A, st);
+        case 6: return run_lines<6, OP, SYM>(A, st);
+        case 7: return run_lines<7, OP, SYM>(A, st);
+        case 8: return run_lines<8, OP, SYM>(A, st);
+        case 9: return run_lines<9, OP, SYM>(A, st);
+        case 10: return run_lines<10, OP, SYM>(A, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+template <int DIR>
+hipError_t z_of_length(const FftPass& A, const ConvPrep& C, hipStream_t st) {
+    switch (A.lgM) {
+        case 0: return run_z<0, DIR>(A, C, st);
+        case 1: return run_z<1, DIR>(A, C, st);
+        case 2: return run_z<2, DIR>(A, C, st);
+        case 3: return run_z<3, DIR>(A, C, st);
+        case 4: return run_z<4, DIR>(A, C, st);
+        case 5: return run_z<5, DIR>(A, C, st);
+        case 6: return run_z<6, DIR>(A, C, st);
+        case 7: return run_z<7, DIR>(A, C, st);
+        case 8: return run_z<8, DIR>(A, C, st);
+        case 9: return run_z<9, DIR>(A, C, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
 
-int fft_lines_per_tile(int lgN) {   // log2 of the tile's line count: nl * N <= kFftTile, nl <= 16
-    int lg = 4;
-    while (lg > 0 && (1 << (lg + lgN)) > kFftTile) --lg;
-    return lg;
-}
-
-hipError_t launch_fft_twiddles(double2* tw, int lg, hipStream_t st) {
-    k_fft_twiddles<<<((1 << lg) + kBlock - 1) / kBlock, kBlock, 0, st>>>(tw, lg);
+hipError_t launch_spec_tables(double2* tw, int lg, double* t0, double* t1, double* t2, const int P[3], int kind,
+                              int lap_order, int grad_order, hipStream_t st) {
+    const int total = (1 << lg) + (kind ? P[0] + P[1] + P[2] : 0);
+    k_spec_tables<<<(total + kBlock - 1) / kBlock, kBlock, 0, st>>>(tw, lg, t0, t1, t2, P[0], P[1], P[2], kind,
+                                                                     lap_order, grad_order);
     return hipGetLastError();
 }
 
-hipError_t launch_spec_tables(double* t0, double* t1, double* t2, const int P[3], int kind, int lap_order,
-                              int grad_order, hipStream_t st) {
-    const int total = P[0] + P[1] + P[2];
-    k_spec_tables<<<(total + kBlock - 1) / kBlock, kBlock, 0, st>>>(t0, t1, t2, P[0], P[1], P[2], kind, lap_order,
-                                                                     grad_order);
-    return hipGetLastError();
+hipError_t launch_fft_z_forward(const FftPass& A, const ConvPrep* prep, hipStream_t st) {
+    return prep ? z_of_length<3>(A, *prep, st) : z_of_length<0>(A, ConvPrep(), st);
 }
 
-// dispatch on the combinations the host pipelines use
-hipError_t launch_fft_pass(const FftPass& A, bool contig, int in, int out, int op, int sym, hipStream_t st) {
-    if (contig) {
-        if (op == kFftForward && in == kFftInRe && out == kFftOutCplx)
-            return run_pass<true, kFftInRe, kFftOutCplx, kFftForward, 0>(A, st);
-        if (op == kFftForward && in == kFftInRePair && out == kFftOutCplx)
-            return run_pass<true, kFftInRePair, kFftOutCplx, kFftForward, 0>(A, st);
-        if (op == kFftForward && in == kFftInCplx && out == kFftOutCplx)
-            return run_pass<true, kFftInCplx, kFftOutCplx, kFftForward, 0>(A, st);
-        if (op == kFftInverse && in == kFftInCplx && out == kFftOutRePairStore)
-            return run_pass<true, kFftInCplx, kFftOutRePairStore, kFftInverse, 0>(A, st);
-        if (op == kFftInverse && in == kFftInCplx && out == kFftOutRePairAdd)
-            return run_pass<true, kFftInCplx, kFftOutRePairAdd, kFftInverse, 0>(A, st);
-        if (op == kFftInverse && in == kFftInCplx && out == kFftOutCplx)
-            return run_pass<true, kFftInCplx, kFftOutCplx, kFftInverse, 0>(A, st);
-        return hipErrorInvalidValue;
+hipError_t launch_fft_z_inverse(const FftPass& A, bool add, hipStream_t st) {
+    return add ? z_of_length<2>(A, ConvPrep(), st) : z_of_length<1>(A, ConvPrep(), st);
+}
+
+hipError_t launch_fft_lines(const FftPass& A, int op, int sym, hipStream_t st) {
+    if (op == kFftForward) return lines_of_length<kFftForward, 0>(A, st);
+    if (op == kFftInverse) return lines_of_length<kFftInverse, 0>(A, st);
+    if (op == kFftRe) return lines_of_length<kFftRe, 0>(A, st);
+    if (op == kFftHybrid) return lines_of_length<kFftHybrid, 0>(A, st);
+    if (op != kFftFwdSymInv) return hipErrorInvalidValue;
+    switch (sym) {
+        case kSymSeparable: return lines_of_length<kFftFwdSymInv, kSymSeparable>(A, st);
+        case kSymTable: return lines_of_length<kFftFwdSymInv, kSymTable>(A, st);
+        case kSymReplace: return lines_of_length<kFftFwdSymInv, kSymReplace>(A, st);
+        case kSymInvLap: return lines_of_length<kFftFwdSymInv, kSymInvLap>(A, st);
+        default: return hipErrorInvalidValue;
     }
-    if (in != kFftInCplx) return hipErrorInvalidValue;
-    if (op == kFftForward && out == kFftOutCplx) return run_pass<false, kFftInCplx, kFftOutCplx, kFftForward, 0>(A, st);
-    if (op == kFftForward && out == kFftOutRe) return run_pass<false, kFftInCplx, kFftOutRe, kFftForward, 0>(A, st);
-    if (op == kFftInverse && out == kFftOutCplx) return run_pass<false, kFftInCplx, kFftOutCplx, kFftInverse, 0>(A, st);
-    if (op == kFftFwdSymInv && out == kFftOutCplx) {
-        switch (sym) {
-            case kSymSeparable: return run_pass<false, kFftInCplx, kFftOutCplx, kFftFwdSymInv, kSymSeparable>(A, st);
-            case kSymTable: return run_pass<false, kFftInCplx, kFftOutCplx, kFftFwdSymInv, kSymTable>(A, st);
-            case kSymHybridXY: return run_pass<false, kFftInCplx, kFftOutCplx, kFftFwdSymInv, kSymHybridXY>(A, st);
-            case kSymHybridZ: return run_pass<false, kFftInCplx, kFftOutCplx, kFftFwdSymInv, kSymHybridZ>(A, st);
-            case kSymReplace: return run_pass<false, kFftInCplx, kFftOutCplx, kFftFwdSymInv, kSymReplace>(A, st);
-            case kSymInvLap: return run_pass<false, kFftInCplx, kFftOutCplx, kFftFwdSymInv, kSymInvLap>(A, st);
-            default: return hipErrorInvalidValue;
-        }
-    }
-    return hipErrorInvalidValue;
 }
 
 }  // namespace mgic

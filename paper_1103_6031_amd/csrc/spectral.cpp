@@ -3,13 +3,14 @@
 // three-pass FFT of k_fft.hip.
 //
 // Pipeline for a real field f of n0 x n1 x n2 cells transformed on P0 x P1 x P2 points (P = n on
-// periodic grids, the zero-padded isolated length otherwise), z contiguous:
-//   z pass   f            -> W1 [n0][n1][P2]   (lines zero-extended from n2 to P2)
-//   y pass   W1           -> W2 [n0][P1][P2]
-//   x pass   W2 -> forward, multiplier, inverse -> W3 [n0][P1][P2]   (one launch)
-//   y pass   W3 (inverse) -> W1 [n0][n1][P2]
-//   z pass   W1 (inverse) -> real output [n0][n1][n2]
-// Only the first n points of each axis are ever stored: lines that are zero by padding are not
+// periodic grids, the zero-padded isolated length otherwise), z contiguous; the spectrum of a real
+// field is Hermitian, so W holds its modes kz = 0 .. P2 / 2 only, in rows of zs points:
+//   z pass   f -> W [n0][n1 of P1][zs]   (lines zero-extended from n2 to P2)
+//   y pass   W in place                  (n1 rows zero-extended to P1)
+//   x pass   W in place: forward, multiplier, inverse   (one launch)
+//   y pass   W in place, inverse
+//   z pass   W (inverse) -> real output [n0][n1][n2]
+// Only the first n points of x and z are ever stored: lines that are zero by padding are not
 // transformed, and output points outside the patch are not computed past the axis they lie on.
 
 #include <hip/hip_runtime.h>
@@ -42,13 +43,56 @@ int pad_len(int n) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-FftPass pass_base(const SpecGrid& S, int axis) {
+FftPass pass_base(const SpecGrid& S, int axis, int nf) {
     FftPass A;
     A.lgN = S.lg[axis];
-    A.lgnl = fft_lines_per_tile(A.lgN);
+    A.lgM = S.lg[2] - 1;
     A.lgtw = S.lgtw;
     A.tw = S.tw;
+    A.nf = nf;
+    A.zs = S.zs;
+    A.fs = (long long)S.field();
+    A.in = S.W;
+    A.out = S.W;
     return A;
+}
+
+// x planes lo0 <= x < hi0 of the field
+FftPass pass_y(const SpecGrid& S, const SpecField& f, int nf) {
+    FftPass A = pass_base(S, 1, nf);
+    A.na = f.hi[0] - f.lo[0];
+    A.in_sa = A.out_sa = (long long)S.P[1] * S.zs;
+    A.in_si = A.out_si = S.zs;
+    A.in = A.out = S.W + (long long)f.lo[0] * S.P[1] * S.zs;
+    return A;
+}
+
+FftPass pass_x(const SpecGrid& S) {
+    FftPass A = pass_base(S, 0, 1);
+    A.na = S.P[1];
+    A.in_sa = A.out_sa = S.zs;
+    A.in_si = A.out_si = (long long)S.P[1] * S.zs;
+    A.tab_x = S.tab[0];
+    A.tab_y = S.tab[1];
+    A.tab_z = S.tab[2];
+    for (int a = 0; a < 3; ++a) A.sym_n[a] = S.P[a];
+    return A;
+}
+
+FftPass pass_z(const SpecGrid& S, const SpecField& f, int nf) {
+    FftPass A = pass_base(S, 2, nf);
+    A.rows = f.hi[1] - f.lo[1];
+    A.na = (f.hi[0] - f.lo[0]) * A.rows;
+    A.plane = S.P[1];
+    A.rsx = f.sx;
+    A.rsy = f.sy;
+    A.in = A.out = S.W + ((long long)f.lo[0] * S.P[1] + f.lo[1]) * S.zs;
+    return A;
+}
+
+// whether the real lines of a field can be read and written as 16-byte pairs of points
+bool by_pairs(const SpecField& f, const double* p) {
+    return f.sx % 2 == 0 && f.sy % 2 == 0 && f.hi[2] % 2 == 0 && (((uintptr_t)p) & 15) == 0;
 }
 
 struct SpecPlan {
@@ -62,18 +106,9 @@ int spec_plan(const int* n, int isolated, void* ws, SpecPlan& S) {
     if (rc) return rc;
     size_t off = 0;
     spec_grid_carve(S.G, (char*)ws, off);
-    size_t w1, w2;
-    spec_grid_work(S.G, w1, w2);
-    char* base = (char*)ws;
-    auto take = [&](size_t bytes) -> void* {
-        off = align256(off);
-        void* p = base ? (void*)(base + off) : nullptr;
-        off += bytes;
-        return p;
-    };
-    S.G.W1 = (double2*)take(sizeof(double2) * w1);
-    S.G.W2 = (double2*)take(sizeof(double2) * w2);
-    S.G.W3 = (double2*)take(sizeof(double2) * w2);
+    off = align256(off);
+    S.G.W = ws ? (double2*)((char*)ws + off) : nullptr;
+    off += kFftMaxFields * sizeof(double2) * S.G.field();   // the hybrid correction's components
     S.bytes = align256(off);
     return MG_OK;
 }
@@ -101,6 +136,9 @@ int spec_grid_init(const int* n, int isolated, SpecGrid& S) {
         S.lg[a] = lg;
     }
     S.lgtw = std::max(S.lg[0], std::max(S.lg[1], S.lg[2]));
+    // rows start on 128-byte lines, and their length is no power of two
+    const int M = S.P[2] / 2;
+    S.zs = M < 16 ? M + 1 : M + 8;
     return MG_OK;
 }
 
@@ -115,102 +153,94 @@ void spec_grid_carve(SpecGrid& S, char* base, size_t& off) {
     for (int a = 0; a < 3; ++a) S.tab[a] = (double*)take(4 * sizeof(double) * (size_t)S.P[a]);
 }
 
-void spec_grid_work(const SpecGrid& S, size_t& w1, size_t& w2) {
-    w1 = (size_t)S.n[0] * S.n[1] * S.P[2];
-    w2 = (size_t)S.n[0] * S.P[1] * S.P[2];
-}
-
 hipError_t spec_grid_prepare(const SpecGrid& S, int kind, int lap_order, int grad_order, hipStream_t st) {
-    hipError_t e = launch_fft_twiddles(S.tw, S.lgtw, st);
-    if (e != hipSuccess) return e;
-    if (kind == 0) return hipSuccess;
-    return launch_spec_tables(S.tab[0], S.tab[1], S.tab[2], S.P, kind, lap_order, grad_order, st);
+    return launch_spec_tables(S.tw, S.lgtw, S.tab[0], S.tab[1], S.tab[2], S.P, kind, lap_order, grad_order, st);
 }
 
-// z then y forward passes of a real field (in1 != nullptr: a second real field as the imaginary
-// part) into W2
-hipError_t spec_forward_zy(const SpecGrid& S, const double* in0, const double* in1, hipStream_t st) {
-    FftPass z = pass_base(S, 2);
-    z.na = S.n[0] * S.n[1];
-    z.m_in = S.n[2];
-    z.m_out = S.P[2];
-    z.in_sa = S.n[2];
-    z.out_sa = S.P[2];
-    z.in0 = in0;
-    z.in1 = in1;
-    z.out0 = S.W1;
-    hipError_t e = launch_fft_pass(z, true, in1 ? kFftInRePair : kFftInRe, kFftOutCplx, kFftForward, 0, st);
+// z then y forward passes of a real field into W (prep: formed from the field while it is read)
+hipError_t spec_forward_zy(const SpecGrid& S, const double* in, const SpecField& f, const ConvPrep* prep,
+                           hipStream_t st) {
+    FftPass z = pass_z(S, f, 1);
+    z.in_lo = f.lo[2];
+    z.in_hi = f.hi[2];
+    z.rin[0] = in;
+    z.vec = by_pairs(f, in) ? 1 : 0;
+    ConvPrep C;
+    if (prep) {
+        C = *prep;
+        C.x0 = f.lo[0];
+        C.y0 = f.lo[1];
+    }
+    const hipError_t e = launch_fft_z_forward(z, prep ? &C : nullptr, st);
     if (e != hipSuccess) return e;
-    FftPass y = pass_base(S, 1);
-    y.na = S.n[0];
-    y.nb = S.P[2];
-    y.m_in = S.n[1];
-    y.m_out = S.P[1];
-    y.in_sa = (long long)S.n[1] * S.P[2];
-    y.in_si = S.P[2];
-    y.out_sa = (long long)S.P[1] * S.P[2];
-    y.out_si = S.P[2];
-    y.in0 = S.W1;
-    y.out0 = S.W2;
-    return launch_fft_pass(y, false, kFftInCplx, kFftOutCplx, kFftForward, 0, st);
+    FftPass y = pass_y(S, f, 1);
+    y.in_lo = f.lo[1];
+    y.in_hi = f.hi[1];
+    y.out_hi = S.P[1];
+    return launch_fft_lines(y, kFftForward, 0, st);
 }
 
-// x pass on W2.  op kFftFwdSymInv: forward, multiply (sym), inverse, the first n0 points of every
-// line into W3.  op kFftForward: the spectrum itself (every point) into out, complex
-// (out_kind kFftOutCplx) or its real part (kFftOutRe), layout [P0][P1][P2].
-hipError_t spec_x_pass(const SpecGrid& S, int op, int out_kind, int sym, double scale, const double* tab,
-                       const double2* csp, const int* cn, void* out, hipStream_t st) {
-    FftPass x = pass_base(S, 0);
-    x.na = S.P[1];
-    x.nb = S.P[2];
-    x.m_in = S.n[0];
-    x.m_out = op == kFftFwdSymInv ? S.n[0] : S.P[0];
-    x.in_sa = S.P[2];
-    x.in_si = (long long)S.P[1] * S.P[2];
-    x.out_sa = S.P[2];
-    x.out_si = x.in_si;
-    x.in0 = S.W2;
-    x.out0 = op == kFftFwdSymInv ? (void*)S.W3 : out;
-    x.tab_x = S.tab[0];
-    x.tab_y = S.tab[1];
-    x.tab_z = S.tab[2];
-    for (int a = 0; a < 3; ++a) x.sym_n[a] = S.P[a];
-    x.tab = tab;
-    x.tab_si = (long long)S.P[1] * S.P[2];
-    x.tab_sa = S.P[2];
-    x.csp = csp;
-    if (cn)
-        for (int a = 0; a < 3; ++a) x.cn[a] = cn[a];
+// forward x pass: the spectrum (every point) into out, complex (op kFftForward) or its real part
+// (kFftRe), layout [P0][P1][zs]
+hipError_t spec_x_spectrum(const SpecGrid& S, int op, void* out, hipStream_t st) {
+    FftPass x = pass_x(S);
+    x.in_hi = S.n[0];
+    x.out_hi = S.P[0];
+    x.out = out;
+    return launch_fft_lines(x, op, 0, st);
+}
+
+// x pass in place: forward from the field's planes `in`, multiply, inverse to the planes of `out`
+// (op kFftFwdSymInv; kFftHybrid: into the three components of the correction, W and the two fields
+// after it)
+hipError_t spec_x_pass(const SpecGrid& S, int op, const SpecMul& m, const SpecField& in, const SpecField& out,
+                       hipStream_t st) {
+    FftPass x = pass_x(S);
+    x.in_lo = in.lo[0];
+    x.in_hi = in.hi[0];
+    x.out_lo = out.lo[0];
+    x.out_hi = out.hi[0];
+    x.tab = m.tab;
+    x.tab_si = (long long)S.P[1] * S.zs;
+    x.tab_sa = S.zs;
+    if (m.coarse) {
+        x.csp = m.csp;
+        x.csp_zs = m.coarse->zs;
+        for (int a = 0; a < 3; ++a) x.cn[a] = m.coarse->P[a];
+    }
     // the inverse transform's 1 / (P0 P1 P2) rides on the multiplier
-    x.sym_scale = scale / ((double)S.P[0] * (double)S.P[1] * (double)S.P[2]);
-    return launch_fft_pass(x, false, kFftInCplx, op == kFftFwdSymInv ? kFftOutCplx : out_kind, op, sym, st);
+    x.sym_scale = m.scale / ((double)S.P[0] * (double)S.P[1] * (double)S.P[2]);
+    x.fine_scale = m.fine_scale / ((double)S.P[0] * (double)S.P[1] * (double)S.P[2]);
+    return launch_fft_lines(x, op, m.sym, st);
 }
 
-// y then z inverse passes, W3 -> real output(s) [n0][n1][n2] (real part -> out0, imaginary -> out1)
-hipError_t spec_inverse_yz(const SpecGrid& S, double* out0, double* out1, bool add, hipStream_t st) {
-    FftPass y = pass_base(S, 1);
-    y.na = S.n[0];
-    y.nb = S.P[2];
-    y.m_in = S.P[1];
-    y.m_out = S.n[1];
-    y.in_sa = (long long)S.P[1] * S.P[2];
-    y.in_si = S.P[2];
-    y.out_sa = (long long)S.n[1] * S.P[2];
-    y.out_si = S.P[2];
-    y.in0 = S.W3;
-    y.out0 = S.W1;
-    hipError_t e = launch_fft_pass(y, false, kFftInCplx, kFftOutCplx, kFftInverse, 0, st);
+// y then z inverse passes of the nf fields in W -> real outputs, stored or added
+hipError_t spec_inverse_yz(const SpecGrid& S, double* const* out, int nf, const SpecField& f, bool add,
+                           hipStream_t st) {
+    // Fields that fit the 256 MB Infinity Cache together share their launches; larger ones go one
+    // after the other, so that the z pass finds in the cache what the y pass has just written.
+    if (nf > 1 && sizeof(double2) * S.field() * nf > ((size_t)192 << 20)) {
+        SpecGrid one = S;
+        for (int k = 0; k < nf; ++k, one.W += S.field()) {
+            const hipError_t e = spec_inverse_yz(one, out + k, 1, f, add, st);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    FftPass y = pass_y(S, f, nf);
+    y.in_hi = S.P[1];
+    y.out_lo = f.lo[1];
+    y.out_hi = f.hi[1];
+    const hipError_t e = launch_fft_lines(y, kFftInverse, 0, st);
     if (e != hipSuccess) return e;
-    FftPass z = pass_base(S, 2);
-    z.na = S.n[0] * S.n[1];
-    z.m_in = S.P[2];
-    z.m_out = S.n[2];
-    z.in_sa = S.P[2];
-    z.out_sa = S.n[2];
-    z.in0 = S.W1;
-    z.out0 = out0;
-    z.out1 = out1;
-    return launch_fft_pass(z, true, kFftInCplx, add ? kFftOutRePairAdd : kFftOutRePairStore, kFftInverse, 0, st);
+    FftPass z = pass_z(S, f, nf);
+    z.out_lo = f.lo[2];
+    z.out_hi = f.hi[2];
+    for (int k = 0; k < nf; ++k) {
+        z.rout[k] = out[k];
+        z.vec |= by_pairs(f, out[k]) ? 1 << k : 0;
+    }
+    return launch_fft_z_inverse(z, add, st);
 }
 
 }  // namespace mgic
@@ -237,9 +267,12 @@ int spec_deconvolve(const int n[3], int kind, int isolated, const double* f, dou
     spec_plan(n, isolated, ws, S);
     const SpecGrid& G = S.G;
     SP_HIP(spec_grid_prepare(G, kind == SPEC_FV_DECONV ? kSpecFv : kSpecSg, 2, 4, st));
-    SP_HIP(spec_forward_zy(G, f, nullptr, st));
-    SP_HIP(spec_x_pass(G, kFftFwdSymInv, 0, kSymSeparable, 1.0, nullptr, nullptr, nullptr, nullptr, st));
-    SP_HIP(spec_inverse_yz(G, out, nullptr, false, st));
+    SpecMul m;
+    m.sym = kSymSeparable;
+    const SpecField F(G.n);
+    SP_HIP(spec_forward_zy(G, f, F, nullptr, st));
+    SP_HIP(spec_x_pass(G, kFftFwdSymInv, m, F, F, st));
+    SP_HIP(spec_inverse_yz(G, &out, 1, F, false, st));
     return MG_OK;
 }
 
@@ -256,9 +289,13 @@ int spec_poisson(const int n[3], double h, int order, const double* f, double* u
     spec_plan(n, 0, ws, S);
     const SpecGrid& G = S.G;
     SP_HIP(spec_grid_prepare(G, kSpecPoisson, order, 4, st));
-    SP_HIP(spec_forward_zy(G, f, nullptr, st));
-    SP_HIP(spec_x_pass(G, kFftFwdSymInv, 0, kSymInvLap, h * h, nullptr, nullptr, nullptr, nullptr, st));
-    SP_HIP(spec_inverse_yz(G, u, nullptr, false, st));
+    SpecMul m;
+    m.sym = kSymInvLap;
+    m.scale = h * h;
+    const SpecField F(G.n);
+    SP_HIP(spec_forward_zy(G, f, F, nullptr, st));
+    SP_HIP(spec_x_pass(G, kFftFwdSymInv, m, F, F, st));
+    SP_HIP(spec_inverse_yz(G, &u, 1, F, false, st));
     return MG_OK;
 }
 
@@ -278,12 +315,12 @@ int lpt_hybrid_correction(const int n[3], double h, int isolated, int lap_order,
     spec_plan(n, isolated, ws, S);
     const SpecGrid& G = S.G;
     SP_HIP(spec_grid_prepare(G, kSpecHybrid, lap_order, grad_order, st));
-    SP_HIP(spec_forward_zy(G, f, nullptr, st));
-    // components x and y in one complex field, then z
-    SP_HIP(spec_x_pass(G, kFftFwdSymInv, 0, kSymHybridXY, scale * h, nullptr, nullptr, nullptr, nullptr, st));
-    SP_HIP(spec_inverse_yz(G, out3[0], out3[1], true, st));
-    SP_HIP(spec_x_pass(G, kFftFwdSymInv, 0, kSymHybridZ, scale * h, nullptr, nullptr, nullptr, nullptr, st));
-    SP_HIP(spec_inverse_yz(G, out3[2], nullptr, true, st));
+    SpecMul m;
+    m.scale = scale * h;
+    const SpecField F(G.n);
+    SP_HIP(spec_forward_zy(G, f, F, nullptr, st));
+    SP_HIP(spec_x_pass(G, kFftHybrid, m, F, F, st));
+    SP_HIP(spec_inverse_yz(G, out3, 3, F, true, st));
     return MG_OK;
 }
 
