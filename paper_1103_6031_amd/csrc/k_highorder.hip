@@ -357,6 +357,139 @@ __global__ __launch_bounds__(kBlock) void k_ho_fill(T* __restrict__ a, unsigned 
     if (t < n) a[t] = v;
 }
 
+// The levels from 2^lgt <= 16 cells per axis down to one cell, a whole V-cycle of them, by one
+// workgroup in LDS: u and f (FAS right-hand side) of every level, uold of the coarser ones.
+// Launched one by one these levels cost 8 half-sweeps and 3 transfer kernels each, at 1.5-3 us for a
+// few hundred cells: bound by launches.  Here every step is a loop over the level's cells
+// between two barriers; a half-sweep forms its values from the cells before it in registers and then
+// writes them in place.  Every value is formed by the operations of the one-step kernels in their
+// order (same bits).  u: the iterate of level lgt, in and out; f: its right-hand side (fas: the
+// restricted residual, L u is added as k_ho_fas does).  From 16^3 down the pyramid takes 80 KB of
+// LDS in FP64.  Measured (MI355X, order 4): one launch of 38 us in FP64, where a solve spent 60 us
+// (256^3, the host ahead of the device) to 120 us (16^3 - 64^3) per V-cycle: solves to 1e-10 of
+// 16^3 1557 -> 480 us, 64^3 2363 -> 1277 us, 128^3 3026 -> 2185 us, 256^3 11.28 -> 10.78 ms.
+constexpr int kHoTailLg = 4;
+constexpr int kHoTailThreads = 1024;
+
+template <int R, class T>
+__global__ __launch_bounds__(kHoTailThreads) void k_ho_tail(T* __restrict__ u, const T* __restrict__ f, int lgt,
+                                                            double h, int nu1, int nu2, int fas) {
+    extern __shared__ __align__(16) unsigned char ho_smem[];
+    T* smem = (T*)ho_smem;
+    const unsigned tid = threadIdx.x;
+    // level k (2^(lgt - k) cells per axis): u, f, uold, each padded to 16 bytes
+    auto cells = [&](int k) { return 1u << (3 * (lgt - k)); };
+    auto pad = [&](int k) { return (cells(k) + 3u) & ~3u; };
+    auto base = [&](int k) {
+        unsigned o = 0;
+        for (int i = 0; i < k; ++i) o += 3 * pad(i);
+        return smem + o;
+    };
+    auto h2_of = [&](int k) {
+        const double hk = ldexp(h, k);
+        return (T)(hk * hk);
+    };
+    auto sweeps = [&](T* U, const T* F, int lg, T h2, int nu) {
+        const unsigned m = (1u << lg) - 1, pairs = 1u << (3 * lg - 1);
+        constexpr int kV = (1 << (3 * kHoTailLg - 1)) / kHoTailThreads;
+        for (int c = 0; c < 2 * nu; ++c) {
+            T v[kV];
+#pragma unroll
+            for (int k = 0; k < kV; ++k) {
+                const unsigned t0 = 2 * (tid + k * kHoTailThreads);
+                if (t0 < 2 * pairs) {
+                    const unsigned z0 = t0 & m, y = (t0 >> lg) & m, x = t0 >> (2 * lg);
+                    const unsigned q = (x + y + (unsigned)(c & 1)) & 1u;
+                    v[k] = (h2 * F[t0 + q] - ho_off<R>(U, x, y, z0 + q, lg, m)) / ((T)3 * (T)HoW<R>::w0);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kV; ++k) {
+                const unsigned t0 = 2 * (tid + k * kHoTailThreads);
+                if (t0 < 2 * pairs) {
+                    const unsigned y = (t0 >> lg) & m, x = t0 >> (2 * lg);
+                    U[t0 + ((x + y + (unsigned)(c & 1)) & 1u)] = v[k];
+                }
+            }
+            __syncthreads();
+        }
+    };
+    // f = rc + L u, each thread its own cells
+    auto add_lu = [&](const T* U, T* F, int lg, T h2) {
+        const unsigned m = (1u << lg) - 1;
+        for (unsigned t = tid; t < (1u << (3 * lg)); t += kHoTailThreads)
+            F[t] = F[t] + (ho_off<R>(U, t >> (2 * lg), (t >> lg) & m, t & m, lg, m) + (T)3 * (T)HoW<R>::w0 * U[t]) / h2;
+    };
+    {
+        T* U = base(0);
+        T* F = U + pad(0);
+        for (unsigned t = tid; t < cells(0); t += kHoTailThreads) {
+            U[t] = u[t];
+            F[t] = f[t];
+        }
+        __syncthreads();
+        if (fas) {
+            add_lu(U, F, lgt, h2_of(0));
+            __syncthreads();
+        }
+    }
+    for (int k = 0; k < lgt; ++k) {
+        const int lg = lgt - k, lgc = lg - 1;
+        T* U = base(k);
+        T* F = U + pad(k);
+        T* Uc = base(k + 1);
+        T* Fc = Uc + pad(k + 1);
+        T* Oc = Fc + pad(k + 1);
+        const T h2 = h2_of(k);
+        sweeps(U, F, lg, h2, nu1);
+        // restriction: 4 lanes per coarse cell, one pair of children (2X + a, 2Y + b, 2Z .. 2Z + 1) each;
+        // the sums run over the lanes in the order of k_ho_resid_restrict
+        const unsigned m = (1u << lg) - 1, mc = (1u << lgc) - 1, items = 4u << (3 * lgc);
+        for (unsigned t = tid; t < items; t += kHoTailThreads) {
+            const unsigned p = t >> 2, Z = p & mc, Y = (p >> lgc) & mc, X = p >> (2 * lgc);
+            v2_t<T> uv;
+            const v2_t<T> r = ho_pair_resid<R, T>(U, F, 2 * X + ((t >> 1) & 1u), 2 * Y + (t & 1u), 2 * Z, lg, m, h2, &uv);
+            T rs = 0, us = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                rs += __shfl(r.x, j, 4);
+                us += __shfl(uv.x, j, 4);
+                rs += __shfl(r.y, j, 4);
+                us += __shfl(uv.y, j, 4);
+            }
+            if ((t & 3u) == 0) {
+                const T um = us * (T)0.125;
+                Uc[p] = um;
+                Oc[p] = um;
+                Fc[p] = rs * (T)0.125;
+            }
+        }
+        __syncthreads();
+        if (lgc > 0) {   // the single cell's equation is not used: u = 0 there
+            add_lu(Uc, Fc, lgc, h2_of(k + 1));
+            __syncthreads();
+        }
+    }
+    if (tid == 0) base(lgt)[0] = (T)0;
+    __syncthreads();
+    for (int k = lgt - 1; k >= 0; --k) {
+        const int lg = lgt - k, lgc = lg - 1;
+        T* U = base(k);
+        const T* Uc = base(k + 1);
+        const T* Oc = Uc + 2 * pad(k + 1);
+        const unsigned m = (1u << lg) - 1;
+        for (unsigned t = tid; t < cells(k); t += kHoTailThreads) {
+            const unsigned p = ho_idx((t >> (2 * lg)) >> 1, ((t >> lg) & m) >> 1, (t & m) >> 1, lgc);
+            U[t] = U[t] + (Uc[p] - Oc[p]);
+        }
+        __syncthreads();
+        sweeps(U, U + pad(k), lg, h2_of(k), nu2);
+    }
+    const T* U = base(0);
+    for (unsigned t = tid; t < cells(0); t += kHoTailThreads) u[t] = U[t];
+}
+
 // deterministic block sum (wave64 shuffle, then the waves in order); valid on thread 0
 __device__ double ho_block_sum(double v) {
     __shared__ double s_w[kBlock / 64];
@@ -545,13 +678,31 @@ void launch_ho_fill(T* a, int lg, T v, hipStream_t st) {
     k_ho_fill<T><<<grid_for(n), kBlock, 0, st>>>(a, n, v);
 }
 
+int ho_tail_lg() { return kHoTailLg; }
+
+template <class T>
+hipError_t launch_ho_tail(T* u, const T* f, int lg, double h, int order, int nu1, int nu2, bool fas, hipStream_t st) {
+    if (lg < 1 || lg > kHoTailLg) return hipErrorInvalidValue;
+    unsigned lds = 0;
+    for (int k = 0; k <= lg; ++k) lds += 3 * (((1u << (3 * k)) + 3u) & ~3u) * (unsigned)sizeof(T);
+    const void* fns[3] = {(const void*)k_ho_tail<1, T>, (const void*)k_ho_tail<2, T>, (const void*)k_ho_tail<3, T>};
+    const int R = order / 2;
+    const hipError_t e = hipFuncSetAttribute(fns[R - 1], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    if (R == 1) k_ho_tail<1, T><<<1, kHoTailThreads, lds, st>>>(u, f, lg, h, nu1, nu2, fas);
+    else if (R == 2) k_ho_tail<2, T><<<1, kHoTailThreads, lds, st>>>(u, f, lg, h, nu1, nu2, fas);
+    else k_ho_tail<3, T><<<1, kHoTailThreads, lds, st>>>(u, f, lg, h, nu1, nu2, fas);
+    return hipGetLastError();
+}
+
 #define HO_INST(T)                                                                                          \
     template void launch_ho_half<T>(const T*, T*, const T*, int, double, int, int, hipStream_t, hipEvent_t,    \
                                     hipEvent_t);                                                            \
     template void launch_ho_resid_restrict<T>(const T*, const T*, T*, T*, T*, int, double, int, hipStream_t); \
     template void launch_ho_fas<T>(const T*, T*, int, double, int, hipStream_t);                              \
     template void launch_ho_prolong<T>(T*, const T*, const T*, int, hipStream_t);                             \
-    template void launch_ho_fill<T>(T*, int, T, hipStream_t);
+    template void launch_ho_fill<T>(T*, int, T, hipStream_t);                                                 \
+    template hipError_t launch_ho_tail<T>(T*, const T*, int, double, int, int, int, bool, hipStream_t);
 HO_INST(double)
 HO_INST(float)
 

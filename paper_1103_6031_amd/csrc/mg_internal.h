@@ -378,6 +378,11 @@ void launch_ho_resid_restrict(const T* u, const T* f, T* uc, T* uold, T* rc, int
 template <class T> void launch_ho_fas(const T* uc, T* fc, int lgc, double hc, int order, hipStream_t st);
 template <class T> void launch_ho_prolong(T* u, const T* uc, const T* uold, int lg, hipStream_t st);
 template <class T> void launch_ho_fill(T* a, int lg, T v, hipStream_t st);
+// one V-cycle of the levels from 2^lg <= 2^ho_tail_lg() cells per axis down, in one launch: u in and
+// out, f its right-hand side (fas: the restricted residual, to which L u is added); h: its spacing
+int ho_tail_lg();
+template <class T>
+hipError_t launch_ho_tail(T* u, const T* f, int lg, double h, int order, int nu1, int nu2, bool fas, hipStream_t st);
 // mixed precision: r32 = f - L u (FP64) with out[0] = sum r^2; u += e32
 void launch_ho_resid32(const double* u, const double* f, float* r32, int lg, double h, int order, double* part,
                        double* out, hipStream_t st);

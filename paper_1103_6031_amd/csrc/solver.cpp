@@ -1951,21 +1951,23 @@ static void ho_smooth(HoPlan& P, const HoArr<T>& A, int l, int sweeps, hipStream
 }
 
 template <class T>
-static void ho_vcycle(HoPlan& P, int nu1, int nu2, hipStream_t st) {
+static hipError_t ho_vcycle(HoPlan& P, int nu1, int nu2, hipStream_t st) {
     const HoArr<T> A = ho_arr(P, T(0));
-    const int L = P.nlev - 1;   // the single-cell level
+    const int L = std::max(0, P.lg - ho_tail_lg());   // the first level of the single-launch tail
     for (int l = 0; l < L; ++l) {
         ho_smooth<T>(P, A, l, nu1, st);
         const int lgc = P.lg - l - 1;
         launch_ho_resid_restrict<T>(A.u[l], A.f[l], A.u[l + 1], A.uold[l + 1], A.f[l + 1], lgc, std::ldexp(P.h, l),
                                     P.order, st);
-        launch_ho_fas<T>(A.u[l + 1], A.f[l + 1], lgc, std::ldexp(P.h, l + 1), P.order, st);
+        if (l + 1 < L) launch_ho_fas<T>(A.u[l + 1], A.f[l + 1], lgc, std::ldexp(P.h, l + 1), P.order, st);
     }
-    launch_ho_fill<T>(A.u[L], 0, T(0), st);   // one cell: u = 0
+    const hipError_t e = launch_ho_tail<T>(A.u[L], A.f[L], P.lg - L, std::ldexp(P.h, L), P.order, nu1, nu2, L > 0, st);
+    if (e != hipSuccess) return e;
     for (int l = L - 1; l >= 0; --l) {
         launch_ho_prolong<T>(A.u[l], A.u[l + 1], A.uold[l + 1], P.lg - l, st);
         ho_smooth<T>(P, A, l, nu2, st);
     }
+    return hipSuccess;
 }
 
 extern "C" {
@@ -2048,7 +2050,7 @@ int mg_solve_level_ho(int n, double h, int order, const double* f, double* u, co
             else if (c == MG_EDIVERGED) status = MG_EDIVERGED;   // a NaN or Inf guess
         }
         while (status == MG_ENOCONV && cycles < o->max_cycles) {
-            ho_vcycle<double>(P, o->nu1, o->nu2, st);
+            MG_HIP(ho_vcycle<double>(P, o->nu1, o->nu2, st));
             ++cycles;
             S.cell_updates += upc;
             if (fixed) continue;
@@ -2077,7 +2079,7 @@ int mg_solve_level_ho(int n, double h, int order, const double* f, double* u, co
             launch_ho_fill<float>(P.e32[0], lg, 0.0f, st);
             const int k = std::min(inner, o->max_cycles - cycles);
             for (int i = 0; i < k; ++i) {
-                ho_vcycle<float>(P, o->nu1, o->nu2, st);
+                MG_HIP(ho_vcycle<float>(P, o->nu1, o->nu2, st));
                 ++cycles;
                 S.cell_updates += upc;
             }
@@ -2269,11 +2271,8 @@ static void hoz_smooth(HozPlan& Z, int p, int sweeps, hipStream_t st, int first 
 // kept: every patch's parent part is still the one kept by its post-smoothing in the previous
 // V-cycle (a patch's parent changes only between its pre- and post-smoothing: by the parent's own
 // smoothing and correction; restrictions write covered parent cells, which no ghost reads)
-static void hoz_vcycle(HozPlan& Z, int p, int nu1, int nu2, hipStream_t st, bool kept = false) {
-    if (p == 0) {
-        ho_vcycle<double>(Z.base, nu1, nu2, st);
-        return;
-    }
+static hipError_t hoz_vcycle(HozPlan& Z, int p, int nu1, int nu2, hipStream_t st, bool kept = false) {
+    if (p == 0) return ho_vcycle<double>(Z.base, nu1, nu2, st);
     HozLevel& L = Z.pat[p - 1];
     hoz_smooth(Z, p, nu1, st, kept ? 2 : 1);                                       // step 2
     launch_hoz_ghost(hoz_pu(Z, p), L.u, L.g, L.P, Z.W, Z.order, 1, st, L.gpart, nu1 > 0 || kept ? 2 : 0);
@@ -2283,9 +2282,11 @@ static void hoz_vcycle(HozPlan& Z, int p, int nu1, int nu2, hipStream_t st, bool
     const int nb3[3] = {Z.N0, Z.N0, Z.N0};
     launch_hoz_fas(hoz_pu(Z, p), hoz_pf(Z, p), p == 1 ? nb3 : Z.pat[p - 2].P.n, p == 1, lo, cn, 2.0 * L.P.h, Z.order,
                    st);                                                            // step 6
-    hoz_vcycle(Z, p - 1, nu1, nu2, st, kept);                                      // step 7
+    const hipError_t e = hoz_vcycle(Z, p - 1, nu1, nu2, st, kept);                 // step 7
+    if (e != hipSuccess) return e;
     launch_hoz_prolong(L.u, L.P, hoz_pu(Z, p), L.uold, st);                        // step 8
     hoz_smooth(Z, p, nu2, st);                                                     // step 9
+    return hipSuccess;
 }
 
 static int hoz_read(const double* dev, int count, double* out, hipStream_t st) { return ho_read(dev, count, out, st); }
@@ -2379,7 +2380,7 @@ int mg_solve_hierarchy_ho(const mg_hier* hier, int order, const double* const* f
         if (c == MG_OK || c == MG_EDIVERGED) status = c;
     }
     while (status == MG_ENOCONV && cycles < o->max_cycles) {
-        hoz_vcycle(Z, Z.np, o->nu1, o->nu2, st, kept);
+        MG_HIP(hoz_vcycle(Z, Z.np, o->nu1, o->nu2, st, kept));
         kept = o->nu2 > 0;
         ++cycles;
         S.cell_updates += upc;
