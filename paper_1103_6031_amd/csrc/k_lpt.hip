@@ -14,6 +14,8 @@
 // division (every array has fewer than 2^31 cells).  Periodic levels take groups of rows, and
 // where the tile divides the level, x-marched tiles with a ring of plane slabs in LDS.
 
+#include <initializer_list>
+
 #include "mg_internal.h"
 
 namespace mgic {
@@ -332,32 +334,79 @@ __global__ void __launch_bounds__(256) k_lla_rows(const double* __restrict__ a0,
 }
 
 // ----------------------------------------------------------------------------------------------
-// Large periodic levels by tiles marched along x.  A block owns 4 rows x 64 z of 32 consecutive
-// planes, one cell per thread and plane.  Each plane's slab (the tile plus 2 cells each side in y
-// and z, every component the kernel reads) is loaded into LDS once, into a ring of four slabs:
-// the loads of plane x + 3 are issued before plane x is computed and stored into the slot of plane
-// x - 1 after it (one barrier per plane).  The y / z stencil values of plane x come from its slab,
-// the x-stencil values from a register window of 5 planes filled from the slabs' own cells.
+// Large periodic levels by tiles marched along x.  A block owns 16 rows x 64 z of `cx` consecutive
+// planes; a thread owns a pair of z-neighbours and keeps their planes x - 2 .. x + 2 of every
+// component with an x-stencil in registers.  The y and z stencils of plane x read one slab in LDS:
+// every thread writes its own pair of plane x there, and 160 threads a pair of the halo (2 rows and
+// 2 cells on each side, without corners), loaded one plane ahead like the own pairs of plane x + 3.
+// Two slabs are used in turn, so one barrier per plane orders them.  Per component and cell that is
+// 1.125 own loads (cx = 32) and 0.31 halo loads, all of 16 bytes where the arrays allow it.
 // Consecutive blocks go to the 8 XCDs in turn, so the tiles are renumbered for each XCD to take a
 // contiguous run, whose halos are then its own neighbours' cells (in its L2).  Each kernel has
 // the same operations in the same order as its row-group version (bit-identical results).
+// Bound: HBM.  Measured at 256^3 (MI355X) against tiles of 4 rows with every slab of the x-window
+// in LDS (2.1 loads of 8 bytes per cell): LLA of two sets 328 -> 261 us
+// (3.6 TB/s of its compulsory bytes; 154 VGPRs, one block of 8 waves per CU), tau 179 -> 153 us,
+// gradient 126 -> 100 us (5.4 TB/s); at 128^3 39 -> 20, 35 -> 20 and 28 -> 15 us.  Tiles of 8 rows (three
+// LLA blocks per CU) took 278, 154 and 103 us at 256^3.
 // ----------------------------------------------------------------------------------------------
-constexpr int kLtY = 4, kLtZ = 64, kLtX = 32;
-constexpr int kSZ = kLtZ + 4, kNS = (kLtY + 4) * kSZ, kPer = (kNS + 255) / 256;
+constexpr int kLtY = 16, kLtZ = 64, kLtX = 32, kLtThreads = kLtY * kLtZ / 2;
+constexpr int kSZ = kLtZ + 4, kNS = (kLtY + 4) * kSZ;
 
 static bool lpt_tiled(Dims d) {
     return d.x % kLtX == 0 && d.y % kLtY == 0 && d.z % kLtZ == 0 && d.cells() >= ((size_t)1 << 21);
 }
+// planes per block: two blocks fit a CU, so the march is shortened (at the price of its 4 extra
+// planes) until there are 512 blocks or 8 planes are left
+static int tiles_planes(Dims d) {
+    const size_t columns = (size_t)(d.y / kLtY) * (size_t)(d.z / kLtZ);
+    int cx = kLtX;
+    while (cx > 8 && columns * (size_t)(d.x / cx) < 512) cx /= 2;
+    return cx;
+}
 static unsigned tiles_grid(Dims d) {
-    return (unsigned)(d.x / kLtX) * (unsigned)(d.y / kLtY) * (unsigned)(d.z / kLtZ);
+    return (unsigned)(d.x / tiles_planes(d)) * (unsigned)(d.y / kLtY) * (unsigned)(d.z / kLtZ);
+}
+static bool pairs_aligned(std::initializer_list<const void*> ps) {
+    uintptr_t a = 0;
+    for (const void* p : ps) a |= (uintptr_t)p;
+    return (a & 15) == 0;
 }
 
-// Marches the block's tile: val(c, q) is component c at linear index q; NW components (the first
-// ones) keep an x-window; plane(x, y, z, slab, me, w) computes and stores the cell (x, y, z) from
-// its plane's slab (slab[c][me +- k], me = the cell's slab index) and the windows w[c][0..4]
-// (planes x - 2 .. x + 2).
+template <bool VEC>
+__device__ __forceinline__ double2 load_pair(const double* __restrict__ p, unsigned q) {
+    if constexpr (VEC) return *(const double2*)(p + q);
+    else return make_double2(p[q], p[q + 1]);
+}
+template <bool VEC>
+__device__ __forceinline__ void store_pair(double* __restrict__ p, unsigned q, double2 v) {
+    if constexpr (VEC) {
+        *(double2*)(p + q) = v;
+    } else {
+        p[q] = v.x;
+        p[q + 1] = v.y;
+    }
+}
+
+// one component around the thread's pair in the current plane: its slab, the own pair's place in it
+// and the own pair's planes x - 2 .. x + 2 (components without an x-stencil: w[2] only)
+struct PairView {
+    const double* s;
+    int me;
+    const double2* w;
+    __device__ __forceinline__ double2 y(int k) const { return *(const double2*)(s + me + k * kSZ); }
+    // the neighbours -2, -1, +1, +2 along z of cell c of the pair
+    __device__ __forceinline__ void z(double (*n)[4]) const {
+        const double2 l = *(const double2*)(s + me - 2), r = *(const double2*)(s + me + 2), o = w[2];
+        n[0][0] = l.x; n[0][1] = l.y; n[0][2] = o.y; n[0][3] = r.x;
+        n[1][0] = l.y; n[1][1] = o.x; n[1][2] = r.x; n[1][3] = r.y;
+    }
+};
+
+// Marches the block's tile: val(c, q) is the pair of component c at linear index q; NW components
+// (the first ones) keep an x-window; plane(q, views) computes and stores the pair at q.
 template <int NC, int NW, class V, class F>
-__device__ __forceinline__ void march_tiles(Dims d, double (*sl)[NC][kNS], V val, F plane) {
+__device__ __forceinline__ void march_tiles(Dims d, int cx, double (*sl)[NC][kNS], V val, F plane) {
     const unsigned ny = (unsigned)d.y, nz = (unsigned)d.z;
     const unsigned nty = ny / kLtY, ntz = nz / kLtZ;
     unsigned b = blockIdx.x;
@@ -365,144 +414,235 @@ __device__ __forceinline__ void march_tiles(Dims d, double (*sl)[NC][kNS], V val
     const unsigned zt = b % ntz;
     b /= ntz;
     const unsigned yt = b % nty;
-    const unsigned x0 = (b / nty) * kLtX;
-    const int tz = (int)(threadIdx.x & 63), ty = (int)(threadIdx.x >> 6);
-    const unsigned z = zt * kLtZ + tz, y = yt * kLtY + ty;
-    const int me = (ty + 2) * kSZ + tz + 2;
-    // this thread's share of a slab: entries t = threadIdx.x + 256 r (t < kNS); their in-plane
-    // offsets do not depend on the plane (an index past the end is clamped, its value unused)
-    unsigned off[kPer];
-#pragma unroll
-    for (int r = 0; r < kPer; ++r) {
-        const int t = min((int)threadIdx.x + 256 * r, kNS - 1);
-        const int sy = t / kSZ, sz = t - sy * kSZ;
-        off[r] = wrap1((int)(yt * kLtY) + sy - 2, d.y) * nz + wrap1((int)(zt * kLtZ) + sz - 2, d.z);
+    const unsigned x0 = (b / nty) * cx;
+    const int tz = (int)(threadIdx.x & 31), ty = (int)(threadIdx.x >> 5);
+    const unsigned own = (yt * kLtY + ty) * nz + zt * kLtZ + 2 * tz;
+    const int me = (ty + 2) * kSZ + 2 * tz + 2;
+    // this thread's pair of the halo: rows -2, -1, 16, 17 (32 pairs each), then the two sides of a row
+    const int t = (int)threadIdx.x;
+    const bool edge = t < 128 + 2 * kLtY;
+    int hy, hz;   // row and cell of the slab
+    if (t < 128) {
+        hy = (t >> 5) < 2 ? (t >> 5) : (t >> 5) + kLtY;
+        hz = 2 * (t & 31) + 2;
+    } else {
+        hy = ((t - 128) >> 1) + 2;
+        hz = t & 1 ? kSZ - 2 : 0;
     }
-    double reg[kPer][NC];
-    auto fetch = [&](unsigned xp) {
-        const unsigned base = xp * ny * nz;
+    if (!edge) hy = hz = 2;   // unused
+    const unsigned hoff = wrap1((int)(yt * kLtY) + hy - 2, d.y) * nz + wrap1((int)(zt * kLtZ) + hz - 2, d.z);
+    const int hme = hy * kSZ + hz;
+    const unsigned np = ny * nz;
+    double2 w[NC][5], hv[NC];
 #pragma unroll
-        for (int r = 0; r < kPer; ++r)
+    for (int c = 0; c < NC; ++c) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) reg[r][c] = val(c, base + off[r]);
-    };
-    auto store = [&](int slot) {
+        for (int k = 0; k < 5; ++k)
+            w[c][k] = c < NW || k == 2 ? val(c, wrap1((int)x0 - 2 + k, d.x) * np + own) : make_double2(0.0, 0.0);
+        hv[c] = edge ? val(c, x0 * np + hoff) : make_double2(0.0, 0.0);
+    }
+    for (int i = 0; i < cx; ++i) {
+        double (*s)[kNS] = sl[i & 1];
 #pragma unroll
-        for (int r = 0; r < kPer; ++r) {
-            const int t = (int)threadIdx.x + 256 * r;
-            if (t < kNS)
-#pragma unroll
-                for (int c = 0; c < NC; ++c) sl[slot][c][t] = reg[r][c];
+        for (int c = 0; c < NC; ++c) {
+            *(double2*)(s[c] + me) = w[c][2];
+            if (edge) *(double2*)(s[c] + hme) = hv[c];
         }
-    };
-    double w[NW][5];
+        const bool more = i + 1 < cx;
+        double2 nw[NC];
+        if (more) {
+            const unsigned p1 = wrap1((int)x0 + i + 1, d.x) * np, p3 = wrap1((int)x0 + i + 3, d.x) * np;
 #pragma unroll
-    for (int c = 0; c < NW; ++c) {
-        w[c][1] = val(c, (wrap1((int)x0 - 2, d.x) * ny + y) * nz + z);
-        w[c][2] = val(c, (wrap1((int)x0 - 1, d.x) * ny + y) * nz + z);
-    }
-    for (int k = 0; k < 3; ++k) {   // planes x0, x0 + 1, x0 + 2 into slots 0, 1, 2
-        fetch(wrap1((int)x0 + k, d.x));
-        store(k);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NW; ++c) {
-        w[c][3] = sl[0][c][me];
-        w[c][4] = sl[1][c][me];
-    }
-    for (int i = 0; i < kLtX; ++i) {
-        const unsigned x = x0 + i;
-        const bool more = i + 3 < kLtX + 2;   // the slabs run to plane x0 + kLtX + 1
-        if (more) fetch(wrap1((int)x + 3, d.x));
-#pragma unroll
-        for (int c = 0; c < NW; ++c) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) w[c][k] = w[c][k + 1];
-            w[c][4] = sl[(i + 2) & 3][c][me];
+            for (int c = 0; c < NC; ++c) {
+                nw[c] = val(c, (c < NW ? p3 : p1) + own);
+                if (edge) hv[c] = val(c, p1 + hoff);
+            }
         }
-        plane(x, y, z, sl[i & 3], me, w);
-        // slot (i + 3) & 3 held plane x - 1, last read in iteration i - 1 (before the previous
-        // barrier); plane x + 3 goes there and is read after this barrier
-        if (more) store((i + 3) & 3);
         __syncthreads();
+        PairView v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = PairView{s[c], me, w[c]};
+        plane((x0 + i) * np + own, v);
+        if (more)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (c < NW) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) w[c][k] = w[c][k + 1];
+                    w[c][4] = nw[c];
+                } else {
+                    w[c][2] = nw[c];
+                }
+            }
     }
 }
 
-// LLA overdensity (as k_lla_rows)
-template <bool SUM>
-__global__ void __launch_bounds__(256) k_lla_tile(const double* __restrict__ a0, const double* __restrict__ a1,
-                                                  const double* __restrict__ a2, const double* __restrict__ b0,
-                                                  const double* __restrict__ b1, const double* __restrict__ b2,
-                                                  Dims d, double h, double* __restrict__ out) {
-    __shared__ double sl[4][3][kNS];
+// the block's sum of `acc` to part (or nowhere), waves in order
+__device__ __forceinline__ void store_partial(double acc, double* part) {
+    __shared__ double s_w[kLtThreads / 64];
+    if (!part) return;
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double r = 0.0;
+        for (int k = 0; k < kLtThreads / 64; ++k) r += s_w[k];
+        part[blockIdx.x] = r;
+    }
+}
+
+// LLA overdensity (as k_lla_rows); part: the sums of the blocks' results
+template <bool SUM, bool VEC>
+__global__ void __launch_bounds__(kLtThreads) k_lla_tile(const double* __restrict__ a0, const double* __restrict__ a1,
+                                                            const double* __restrict__ a2, const double* __restrict__ b0,
+                                                            const double* __restrict__ b1, const double* __restrict__ b2,
+                                                            Dims d, int cx, double h, double* __restrict__ out,
+                                                            double* __restrict__ part) {
+    __shared__ __align__(16) double sl[2][3][kNS];
     const double* A[3] = {a0, a1, a2};
     const double* Bv[3] = {b0, b1, b2};
     const double inv = 1.0 / (12.0 * h);
-    const unsigned ny = (unsigned)d.y, nz = (unsigned)d.z;
     auto val = [&](int c, unsigned q) {
-        if constexpr (SUM) return A[c][q] + Bv[c][q];
-        else return A[c][q];
+        double2 v = load_pair<VEC>(A[c], q);
+        if constexpr (SUM) {
+            const double2 e = load_pair<VEC>(Bv[c], q);
+            v.x = v.x + e.x;
+            v.y = v.y + e.y;
+        }
+        return v;
     };
-    march_tiles<3, 3>(d, sl, val, [&](unsigned x, unsigned y, unsigned z, double (*s)[kNS], int me, double (*w)[5]) {
-        double m[3][3];
+    double acc = 0.0;
+    march_tiles<3, 3>(d, cx, sl, val, [&](unsigned q, const PairView* v) {
+        double m[2][3][3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            m[c][0] = 1.0 * (c == 0) + g4m(w[c][0], w[c][1], w[c][3], w[c][4], inv);
-            m[c][1] = 1.0 * (c == 1) + g4m(s[c][me - 2 * kSZ], s[c][me - kSZ], s[c][me + kSZ], s[c][me + 2 * kSZ], inv);
-            m[c][2] = 1.0 * (c == 2) + g4m(s[c][me - 2], s[c][me - 1], s[c][me + 1], s[c][me + 2], inv);
+            const double2* w = v[c].w;
+            const double2 y0 = v[c].y(-2), y1 = v[c].y(-1), y3 = v[c].y(1), y4 = v[c].y(2);
+            double n[2][4];
+            v[c].z(n);
+            m[0][c][0] = 1.0 * (c == 0) + g4m(w[0].x, w[1].x, w[3].x, w[4].x, inv);
+            m[1][c][0] = 1.0 * (c == 0) + g4m(w[0].y, w[1].y, w[3].y, w[4].y, inv);
+            m[0][c][1] = 1.0 * (c == 1) + g4m(y0.x, y1.x, y3.x, y4.x, inv);
+            m[1][c][1] = 1.0 * (c == 1) + g4m(y0.y, y1.y, y3.y, y4.y, inv);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) m[k][c][2] = 1.0 * (c == 2) + g4m(n[k][0], n[k][1], n[k][2], n[k][3], inv);
         }
-        const double c0 = m[1][1] * m[2][2] - m[1][2] * m[2][1];
-        const double c1 = m[1][0] * m[2][2] - m[1][2] * m[2][0];
-        const double c2 = m[1][0] * m[2][1] - m[1][1] * m[2][0];
-        const double det = (m[0][0] * c0 - m[0][1] * c1) + m[0][2] * c2;
-        out[(x * ny + y) * nz + z] = 1.0 / det - 1.0;
+        double o[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const double c0 = m[k][1][1] * m[k][2][2] - m[k][1][2] * m[k][2][1];
+            const double c1 = m[k][1][0] * m[k][2][2] - m[k][1][2] * m[k][2][0];
+            const double c2 = m[k][1][0] * m[k][2][1] - m[k][1][1] * m[k][2][0];
+            const double det = (m[k][0][0] * c0 - m[k][0][1] * c1) + m[k][0][2] * c2;
+            o[k] = 1.0 / det - 1.0;
+        }
+        acc += o[0];
+        acc += o[1];
+        store_pair<VEC>(out, q, make_double2(o[0], o[1]));
     });
+    store_partial(acc, part);
 }
 
 // psi_c = scale * G4_c phi (as k_grad4_rows)
-__global__ void __launch_bounds__(256) k_grad4_tile(const double* __restrict__ p, Dims d, double h, double scale,
-                                                    double* __restrict__ ox, double* __restrict__ oy,
-                                                    double* __restrict__ oz) {
-    __shared__ double sl[4][1][kNS];
+template <bool VEC>
+__global__ void __launch_bounds__(kLtThreads) k_grad4_tile(const double* __restrict__ p, Dims d, int cx, double h,
+                                                           double scale, double* __restrict__ ox,
+                                                           double* __restrict__ oy, double* __restrict__ oz) {
+    __shared__ __align__(16) double sl[2][1][kNS];
     const double den = 12.0 * h;
-    const unsigned ny = (unsigned)d.y, nz = (unsigned)d.z;
-    march_tiles<1, 1>(d, sl, [&](int, unsigned q) { return p[q]; },
-                      [&](unsigned x, unsigned y, unsigned z, double (*s)[kNS], int me, double (*w)[5]) {
-                          const double gx = g4v(w[0][0], w[0][1], w[0][3], w[0][4], den);
-                          const double gy = g4v(s[0][me - 2 * kSZ], s[0][me - kSZ], s[0][me + kSZ], s[0][me + 2 * kSZ], den);
-                          const double gz = g4v(s[0][me - 2], s[0][me - 1], s[0][me + 1], s[0][me + 2], den);
-                          const unsigned q = (x * ny + y) * nz + z;
-                          ox[q] = scale * gx;
-                          oy[q] = scale * gy;
-                          oz[q] = scale * gz;
+    march_tiles<1, 1>(d, cx, sl, [&](int, unsigned q) { return load_pair<VEC>(p, q); },
+                      [&](unsigned q, const PairView* v) {
+                          const double2* w = v[0].w;
+                          const double2 y0 = v[0].y(-2), y1 = v[0].y(-1), y3 = v[0].y(1), y4 = v[0].y(2);
+                          double n[2][4];
+                          v[0].z(n);
+                          store_pair<VEC>(ox, q, make_double2(scale * g4v(w[0].x, w[1].x, w[3].x, w[4].x, den),
+                                                              scale * g4v(w[0].y, w[1].y, w[3].y, w[4].y, den)));
+                          store_pair<VEC>(oy, q, make_double2(scale * g4v(y0.x, y1.x, y3.x, y4.x, den),
+                                                              scale * g4v(y0.y, y1.y, y3.y, y4.y, den)));
+                          store_pair<VEC>(oz, q, make_double2(scale * g4v(n[0][0], n[0][1], n[0][2], n[0][3], den),
+                                                              scale * g4v(n[1][0], n[1][1], n[1][2], n[1][3], den)));
                       });
 }
 
-// tau from the three gradient components (as k_tau_rows)
-__global__ void __launch_bounds__(256) k_tau_tile(const double* __restrict__ q0, const double* __restrict__ q1,
-                                                  const double* __restrict__ q2, Dims d, double h, double post,
-                                                  double* __restrict__ tau) {
-    __shared__ double sl[4][3][kNS];
+// tau from the three gradient components (as k_tau_rows); part: the sums of the blocks' results
+template <bool VEC>
+__global__ void __launch_bounds__(kLtThreads) k_tau_tile(const double* __restrict__ q0, const double* __restrict__ q1,
+                                                         const double* __restrict__ q2, Dims d, int cx, double h,
+                                                         double post, double* __restrict__ tau,
+                                                         double* __restrict__ part) {
+    __shared__ __align__(16) double sl[2][3][kNS];
     const double* Q[3] = {q0, q1, q2};
     const double den = 12.0 * h;
-    const unsigned ny = (unsigned)d.y, nz = (unsigned)d.z;
-    march_tiles<3, 1>(d, sl, [&](int c, unsigned q) { return Q[c][q]; },
-                      [&](unsigned x, unsigned y, unsigned z, double (*s)[kNS], int me, double (*w)[5]) {
-                          const double Dxx = g4v(w[0][0], w[0][1], w[0][3], w[0][4], den);
-                          const double Dyy = g4v(s[1][me - 2 * kSZ], s[1][me - kSZ], s[1][me + kSZ], s[1][me + 2 * kSZ], den);
-                          const double Dzz = g4v(s[2][me - 2], s[2][me - 1], s[2][me + 1], s[2][me + 2], den);
-                          const double Dyx = g4v(s[0][me - 2 * kSZ], s[0][me - kSZ], s[0][me + kSZ], s[0][me + 2 * kSZ], den);
-                          const double Dzx = g4v(s[0][me - 2], s[0][me - 1], s[0][me + 1], s[0][me + 2], den);
-                          const double Dzy = g4v(s[1][me - 2], s[1][me - 1], s[1][me + 1], s[1][me + 2], den);
-                          double acc = 0.0;
-                          acc = acc + (Dyy * Dxx - Dyx * Dyx);
-                          acc = acc + (Dzz * Dxx - Dzx * Dzx);
-                          acc = acc + (Dzz * Dyy - Dzy * Dzy);
-                          tau[(x * ny + y) * nz + z] = post == 1.0 ? acc : acc * post;
+    double total = 0.0;
+    march_tiles<3, 1>(d, cx, sl, [&](int c, unsigned q) { return load_pair<VEC>(Q[c], q); },
+                      [&](unsigned q, const PairView* v) {
+                          const double2* w = v[0].w;
+                          double2 ya[4], yb[4];
+                          double n0[2][4], n1[2][4], n2[2][4], o[2];
+#pragma unroll
+                          for (int k = 0; k < 4; ++k) {
+                              ya[k] = v[0].y(k < 2 ? k - 2 : k - 1);
+                              yb[k] = v[1].y(k < 2 ? k - 2 : k - 1);
+                          }
+                          v[0].z(n0);
+                          v[1].z(n1);
+                          v[2].z(n2);
+#pragma unroll
+                          for (int k = 0; k < 2; ++k) {
+                              auto at = [&](const double2& e) { return k ? e.y : e.x; };
+                              const double Dxx = g4v(at(w[0]), at(w[1]), at(w[3]), at(w[4]), den);
+                              const double Dyy = g4v(at(yb[0]), at(yb[1]), at(yb[2]), at(yb[3]), den);
+                              const double Dzz = g4v(n2[k][0], n2[k][1], n2[k][2], n2[k][3], den);
+                              const double Dyx = g4v(at(ya[0]), at(ya[1]), at(ya[2]), at(ya[3]), den);
+                              const double Dzx = g4v(n0[k][0], n0[k][1], n0[k][2], n0[k][3], den);
+                              const double Dzy = g4v(n1[k][0], n1[k][1], n1[k][2], n1[k][3], den);
+                              double acc = 0.0;
+                              acc = acc + (Dyy * Dxx - Dyx * Dyx);
+                              acc = acc + (Dzz * Dxx - Dzx * Dzx);
+                              acc = acc + (Dzz * Dyy - Dzy * Dzy);
+                              o[k] = post == 1.0 ? acc : acc * post;
+                              total += o[k];
+                          }
+                          store_pair<VEC>(tau, q, make_double2(o[0], o[1]));
                       });
+    store_partial(total, part);
 }
 
+static void run_grad4_tile(const double* p, Dims d, double h, double scale, double* ox, double* oy, double* oz,
+                           hipStream_t st) {
+    const int cx = tiles_planes(d);
+    if (pairs_aligned({p, ox, oy, oz})) k_grad4_tile<true><<<tiles_grid(d), kLtThreads, 0, st>>>(p, d, cx, h, scale, ox, oy, oz);
+    else k_grad4_tile<false><<<tiles_grid(d), kLtThreads, 0, st>>>(p, d, cx, h, scale, ox, oy, oz);
+}
+
+// the partial sums of a tile kernel's results: wanted, and few enough for the partials buffer
+static double* tile_partials(Dims d, double* partials, int* nparts) {
+    if (nparts) *nparts = 0;
+    if (!partials || tiles_grid(d) > (unsigned)kMaxPartials) return nullptr;
+    *nparts = (int)tiles_grid(d);
+    return partials;
+}
+
+static void run_tau_tile(const double* g0, const double* g1, const double* g2, Dims d, double h, double post,
+                         double* tau, double* partials, int* nparts, hipStream_t st) {
+    const int cx = tiles_planes(d);
+    double* part = tile_partials(d, partials, nparts);
+    if (pairs_aligned({g0, g1, g2, tau})) k_tau_tile<true><<<tiles_grid(d), kLtThreads, 0, st>>>(g0, g1, g2, d, cx, h, post, tau, part);
+    else k_tau_tile<false><<<tiles_grid(d), kLtThreads, 0, st>>>(g0, g1, g2, d, cx, h, post, tau, part);
+}
+
+template <bool SUM>
+static void run_lla_tile(const double* const* a, const double* const* b, Dims d, double h, double* out,
+                         double* partials, int* nparts, hipStream_t st) {
+    const int cx = tiles_planes(d);
+    double* part = tile_partials(d, partials, nparts);
+    const unsigned g = tiles_grid(d);
+    if (pairs_aligned({a[0], a[1], a[2], b[0], b[1], b[2], out}))
+        k_lla_tile<SUM, true><<<g, kLtThreads, 0, st>>>(a[0], a[1], a[2], b[0], b[1], b[2], d, cx, h, out, part);
+    else
+        k_lla_tile<SUM, false><<<g, kLtThreads, 0, st>>>(a[0], a[1], a[2], b[0], b[1], b[2], d, cx, h, out, part);
+}
 
 static unsigned rows_grid(Dims d) { return (unsigned)d.x * (unsigned)((d.y + kRowsY - 1) / kRowsY); }
 static unsigned rows_block(Dims d) { return d.z >= 256 ? 256u : (unsigned)((d.z + 63) / 64 * 64); }
@@ -566,14 +706,16 @@ void launch_grad4(const double* src, int R, Dims d, double h, double scale, doub
         return;
     }
     if (R == 0 && lpt_tiled(d))
-        k_grad4_tile<<<tiles_grid(d), 256, 0, st>>>(src, d, h, scale, ox, oy, oz);
+        run_grad4_tile(src, d, h, scale, ox, oy, oz, st);
     else if (R == 0)
         k_grad4_rows<<<rows_grid(d), rows_block(d), 0, st>>>(src, d, h, scale, ox, oy, oz);
     else
         k_grad4<true><<<grid_for(d.cells()), kBlock, 0, st>>>(Src<true>{src, R, d}, B, h, scale, ox, oy, oz);
 }
 
-void launch_tau(const double* src, int R, Dims d, double h, double* tau, double* psi, hipStream_t st, int order) {
+void launch_tau(const double* src, int R, Dims d, double h, double* tau, double* psi, hipStream_t st, int order,
+                double* partials, int* nparts) {
+    if (nparts) *nparts = 0;
     const int rg = order / 2;   // the gradient's radius
     const int e = R >= rg ? R - rg : 0;
     const Lay E(Dims{d.x + 2 * e, d.y + 2 * e, d.z + 2 * e}, 0);
@@ -595,7 +737,7 @@ void launch_tau(const double* src, int R, Dims d, double h, double* tau, double*
     }
     if (R == 0) {
         k_psi<false><<<grid_for(E.d.cells()), kBlock, 0, st>>>(Src<false>{src, 0, d}, E, 0, h, p0, p1, p2);
-        if (lpt_tiled(d)) k_tau_tile<<<tiles_grid(d), 256, 0, st>>>(p0, p1, p2, d, h, 1.0, tau);
+        if (lpt_tiled(d)) run_tau_tile(p0, p1, p2, d, h, 1.0, tau, partials, nparts, st);
         else k_tau_rows<<<rows_grid(d), rows_block(d), 0, st>>>(p0, p1, p2, d, h, 1.0, tau);
     } else {
         k_psi<true><<<grid_for(E.d.cells()), kBlock, 0, st>>>(Src<true>{src, R, d}, E, e, h, p0, p1, p2);
@@ -605,18 +747,21 @@ void launch_tau(const double* src, int R, Dims d, double h, double* tau, double*
 }
 
 void launch_tau_from_grad(const double* g0, const double* g1, const double* g2, Dims d, double h, double post,
-                         double* tau, hipStream_t st, int order) {
+                         double* tau, hipStream_t st, int order, double* partials, int* nparts) {
+    if (nparts) *nparts = 0;
     if (order == 6) {
         k_tau_psi<false, 6><<<grid_for(d.cells()), kBlock, 0, st>>>(Src<false>{g0, 0, d}, Src<false>{g1, 0, d},
                                                                     Src<false>{g2, 0, d}, Lay(d, 0), h, post, tau);
         return;
     }
-    if (lpt_tiled(d)) k_tau_tile<<<tiles_grid(d), 256, 0, st>>>(g0, g1, g2, d, h, post, tau);
+    if (lpt_tiled(d)) run_tau_tile(g0, g1, g2, d, h, post, tau, partials, nparts, st);
     else k_tau_rows<<<rows_grid(d), rows_block(d), 0, st>>>(g0, g1, g2, d, h, post, tau);
 }
 
 
-void launch_lla(const double* const* a, const double* const* b, int R, Dims d, double h, double* out, hipStream_t st) {
+void launch_lla(const double* const* a, const double* const* b, int R, Dims d, double h, double* out, hipStream_t st,
+                double* partials, int* nparts) {
+    if (nparts) *nparts = 0;
     const Lay B(d, 0);
     const int sum = b != nullptr;
     const double* const* bb = sum ? b : a;
@@ -624,8 +769,8 @@ void launch_lla(const double* const* a, const double* const* b, int R, Dims d, d
     // offset of 2 holds) by x-marched tiles where they divide the level, else by groups of rows;
     // padded patches by the per-cell kernel
     if (R == 0 && lpt_tiled(d)) {
-        if (sum) k_lla_tile<true><<<tiles_grid(d), 256, 0, st>>>(a[0], a[1], a[2], bb[0], bb[1], bb[2], d, h, out);
-        else k_lla_tile<false><<<tiles_grid(d), 256, 0, st>>>(a[0], a[1], a[2], bb[0], bb[1], bb[2], d, h, out);
+        if (sum) run_lla_tile<true>(a, bb, d, h, out, partials, nparts, st);
+        else run_lla_tile<false>(a, bb, d, h, out, partials, nparts, st);
     } else if (R == 0 && sum)
         k_lla_rows<true><<<rows_grid(d), rows_block(d), 0, st>>>(a[0], a[1], a[2], bb[0], bb[1], bb[2], d, h, out);
     else if (R == 0)

@@ -283,15 +283,19 @@ void launch_grad4(const double* src, int R, Dims d, double h, double scale, doub
                   double* oz, hipStream_t st, int order = 4);
 // tau = sum_{i>j} D_ii D_jj - D_ij^2, D = G o G of `order`; src periodic (R = 0) or padded by
 // R >= order; psi is scratch for 3 arrays of (d + 2(R - order/2))^3 (d^3 when periodic)
+// (partials and nparts as for launch_lla)
 void launch_tau(const double* src, int R, Dims d, double h, double* tau, double* psi, hipStream_t st,
-                int order = 4);
+                int order = 4, double* partials = nullptr, int* nparts = nullptr);
 // tau on a periodic level from the three components g_c = s G_c phi of a scaled gradient
 // (post = 1 / s^2)
 void launch_tau_from_grad(const double* g0, const double* g1, const double* g2, Dims d, double h, double post,
-                          double* tau, hipStream_t st, int order = 4);
+                          double* tau, hipStream_t st, int order = 4, double* partials = nullptr,
+                          int* nparts = nullptr);
 // LLA overdensity 1 / det(I + G4 L) - 1 with L = a (+ b when b is given), three components each,
-// periodic (R = 0) or padded by R >= 2
-void launch_lla(const double* const* a, const double* const* b, int R, Dims d, double h, double* out, hipStream_t st);
+// periodic (R = 0) or padded by R >= 2.  partials (kMaxPartials): where the kernel can, it leaves
+// *nparts partial sums of out there; *nparts = 0 otherwise
+void launch_lla(const double* const* a, const double* const* b, int R, Dims d, double h, double* out, hipStream_t st,
+                double* partials = nullptr, int* nparts = nullptr);
 // dst = a + b elementwise
 void launch_add2(const double* a, const double* b, double* dst, size_t n, hipStream_t st);
 

@@ -2638,14 +2638,17 @@ namespace mgic {
 // 1 / s^2) when given, else from phi
 static int tau_levels(const mg_hier* hier, LptPlan& lp, double* const* tau, double* const* base_grad, double post,
                       hipStream_t st, int order) {
+    // without patches the base's sum is the one of tau as it is formed
+    int np = 0;
+    double* part = hier->nlev == 1 ? lp.partials : nullptr;
     for (int p = 0; p < hier->nlev; ++p) {
         if (!tau[p]) return fail(MG_EINVAL, "tau level pointer is NULL");
         const Dims d = dims_of(hier, p);
         const double h = h_of(hier, p);
         if (p == 0 && base_grad) {
-            launch_tau_from_grad(base_grad[0], base_grad[1], base_grad[2], d, h, post, tau[0], st, order);
+            launch_tau_from_grad(base_grad[0], base_grad[1], base_grad[2], d, h, post, tau[0], st, order, part, &np);
         } else if (p == 0) {
-            launch_tau(lp.phi[0], 0, d, h, tau[0], lp.psi, st, order);
+            launch_tau(lp.phi[0], 0, d, h, tau[0], lp.psi, st, order, part, &np);
         } else {   // ghosts of width `order`: D = G o G reaches order / 2 twice
             launch_wide_ghost(lp.phi[p - 1], lp.phi[p], lp.padded, d, parent_of(hier, p), order, st);
             launch_tau(lp.padded, order, d, h, tau[p], lp.psi, st, order);
@@ -2654,9 +2657,8 @@ static int tau_levels(const mg_hier* hier, LptPlan& lp, double* const* tau, doub
     // composite mean: covered cells := mean of children, then subtract the base mean everywhere
     for (int p = hier->nlev - 1; p >= 1; --p)
         launch_restrict_cov<double>(tau[p], mklay(dims_of(hier, p), 0), tau[p - 1], parent_of(hier, p), st);
-    int np = 0;
     CovBox none{};
-    launch_sum(tau[0], mklay(dims_of(hier, 0), 0), none, 0, lp.partials, &np, st);
+    if (np == 0) launch_sum(tau[0], mklay(dims_of(hier, 0), 0), none, 0, lp.partials, &np, st);
     SegList s{};
     s.n = 1; s.off[0] = 0; s.cnt[0] = np; s.w[0] = 1.0;
     launch_finalize(lp.partials, s, lp.scal, st);
@@ -2723,10 +2725,11 @@ int lpt_lla_density(const mg_hier* hier, const double* const* disp, const double
     Carver cv(workspace);
     lpt_carve(hier, 3, cv, lp);
     (void)hipGetLastError();
+    int np = 0;   // partial sums of the base's delta
     if (nl == 1) {
         const double* a[3] = {disp[0], disp[1], disp[2]};
         const double* b[3] = {disp2 ? disp2[0] : nullptr, disp2 ? disp2[1] : nullptr, disp2 ? disp2[2] : nullptr};
-        launch_lla(a, disp2 ? b : nullptr, 0, dims_of(hier, 0), h_of(hier, 0), delta[0], st);
+        launch_lla(a, disp2 ? b : nullptr, 0, dims_of(hier, 0), h_of(hier, 0), delta[0], st, lp.partials, &np);
     } else {
         // working copies of L (= disp + disp2), covered cells restricted from the finer level
         auto comp = [&](int c, int p) { return lp.phi[(size_t)c * nl + p]; };
@@ -2759,9 +2762,8 @@ int lpt_lla_density(const mg_hier* hier, const double* const* disp, const double
     // volume mean) is subtracted everywhere
     for (int p = nl - 1; p >= 1; --p)
         launch_restrict_cov<double>(delta[p], mklay(dims_of(hier, p), 0), delta[p - 1], parent_of(hier, p), st);
-    int np = 0;
     CovBox none{};
-    launch_sum(delta[0], mklay(dims_of(hier, 0), 0), none, 0, lp.partials, &np, st);
+    if (np == 0) launch_sum(delta[0], mklay(dims_of(hier, 0), 0), none, 0, lp.partials, &np, st);
     SegList s{};
     s.n = 1; s.off[0] = 0; s.cnt[0] = np; s.w[0] = 1.0;
     launch_finalize(lp.partials, s, lp.scal, st);
