@@ -1,5 +1,5 @@
-// Fused small-level kernels of the FAS V-cycle (Section 3.2) for the periodic coarsenings that
-// are power-of-two cubes of 16^3, 32^3 and 64^3 cells.
+// Fused small-level kernels of the FAS V-cycle (Section 3.2) for the periodic coarsenings of 16^3
+// to 64^3 cells.
 //
 // As one-step kernels each such level costs eleven launches per cycle (FAS right-hand side,
 // 2 nu1 half-sweeps, residual + restriction, prolongation, 2 nu2 half-sweeps), and at these sizes
@@ -14,8 +14,15 @@
 // by the neighbouring tiles.  Every value is formed by the same operations in the same order as
 // in the one-step kernels, so the results are bit-identical to them.  Workgroups read the level's
 // arrays and write a second copy (no workgroup reads what another writes).
+//
+// Edges that are no power of two (20, 24, 28, 40, 48, 56: bases of 3, 5 or 7 times one) take the
+// same kernels with multiplications and one conditional wrap in place of shifts and masks; where 8
+// does not divide the edge, the last tile of a row ends inside the level.  Measured for a 96^3 base
+// (FP32, levels 48^3 and 24^3 per cycle): @@96@@.
 
 #include <hip/hip_ext.h>
+
+#include <type_traits>
 
 #include "mg_internal.h"
 #include "p2_bodies.h"
@@ -75,40 +82,80 @@ __device__ __forceinline__ void lds_sweeps(T* su, const T* sf, T h2, int p0) {
     }
 }
 
+// Index arithmetic of a level of edge n (even) and its tiles: P2 for n = 2^lg.
+template <bool P2>
+struct LevelIdx {
+    int n, lg;
+    // origin of tile b
+    __device__ __forceinline__ void origin(unsigned b, int& ox, int& oy, int& oz) const {
+        if constexpr (P2) {
+            const int lt = lg - 3;
+            ox = (int)(b >> (2 * lt)) * kTile;
+            oy = (int)((b >> lt) & ((1u << lt) - 1)) * kTile;
+            oz = (int)(b & ((1u << lt) - 1)) * kTile;
+        } else {
+            const unsigned nt = (unsigned)(n + kTile - 1) / kTile, r = b / nt, q = r / nt;
+            ox = (int)q * kTile;
+            oy = (int)(r - q * nt) * kTile;
+            oz = (int)(b - r * nt) * kTile;
+        }
+    }
+    // periodic wrap of a coordinate in -n .. 2 n - 1
+    __device__ __forceinline__ unsigned wrap(int a) const {
+        if constexpr (P2) return (unsigned)a & ((1u << lg) - 1);
+        else return (unsigned)(a < 0 ? a + n : (a >= n ? a - n : a));
+    }
+    __device__ __forceinline__ bool inside(int x, int y, int z) const { return P2 || (x < n && y < n && z < n); }
+    // position in the colour-split level, in the colour-split coarse level, and in the coarse level's
+    // natural order
+    __device__ __forceinline__ unsigned at(unsigned x, unsigned y, unsigned z) const {
+        if constexpr (P2) return sidx(lg, x, y, z);
+        else return (x * n + y) * n + (((x + y + z) & 1u) ? (unsigned)n >> 1 : 0u) + (z >> 1);
+    }
+    __device__ __forceinline__ unsigned coarse(unsigned X, unsigned Y, unsigned Z) const {
+        if constexpr (P2) return sidx(lg - 1, X, Y, Z);
+        const unsigned c = (unsigned)n >> 1;
+        return (X * c + Y) * c + (((X + Y + Z) & 1u) ? c >> 1 : 0u) + (Z >> 1);
+    }
+    __device__ __forceinline__ unsigned natural(unsigned X, unsigned Y, unsigned Z) const {
+        if constexpr (P2) return (((X << (lg - 1)) | Y) << (lg - 1)) | Z;
+        const unsigned c = (unsigned)n >> 1;
+        return (X * c + Y) * c + Z;
+    }
+};
+
 // v[S^3 region with origin o - R] = a[cell] (periodic wrap), into LDS
-template <class T, int S>
-__device__ __forceinline__ void load_region(T* dst, const T* __restrict__ a, int lg, int ox, int oy, int oz, int R) {
+template <class T, int S, bool P2>
+__device__ __forceinline__ void load_region(T* dst, const T* __restrict__ a, LevelIdx<P2> ix, int ox, int oy, int oz,
+                                            int R) {
     using Pp = Passes<S * S * S>;
-    const unsigned msk = (1u << lg) - 1;
     T v[Pp::n];
 #pragma unroll
     for (int r = 0; r < Pp::n; ++r) {
         const int t = Pp::cell(r);
         const int i = t / (S * S), j = (t / S) % S, m = t % S;
-        v[r] = a[sidx(lg, (unsigned)(ox - R + i) & msk, (unsigned)(oy - R + j) & msk, (unsigned)(oz - R + m) & msk)];
+        v[r] = a[ix.at(ix.wrap(ox - R + i), ix.wrap(oy - R + j), ix.wrap(oz - R + m))];
     }
 #pragma unroll
     for (int r = 0; r < Pp::n; ++r)
         if (Pp::live(r)) dst[(int)threadIdx.x + r * kFusedThreads] = v[r];
 }
 
-// pre leg on level (edge 2^lg): u, f are the level's arrays as the parent's restriction left
+// pre leg on a level of edge ix.n: u, f are the level's arrays as the parent's restriction left
 // them; uo, fo receive the smoothed u and the FAS right-hand side of this tile; pu, pf, uold the
-// restricted u, the restricted residual and its copy for the coarse level (edge 2^(lg-1))
-template <class T, int NU>
-__global__ void __launch_bounds__(kFusedThreads)
-k_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo, T* __restrict__ fo,
-            T* __restrict__ pu, T* __restrict__ pf, T* __restrict__ uold, int lg, T h2) {
+// restricted u, the restricted residual and its copy for the coarse level
+template <class T, int NU, bool P2>
+__device__ __forceinline__ void body_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo,
+                                               T* __restrict__ fo, T* __restrict__ pu, T* __restrict__ pf,
+                                               T* __restrict__ uold, LevelIdx<P2> ix, T h2, unsigned b) {
     constexpr int R = 2 * NU + 1;      // u halo: 2 nu1 half-sweeps + the residual stencil
     constexpr int S = kTile + 2 * R, SF = S - 2;
     __shared__ T su[S * S * S];
     __shared__ T sf[SF * SF * SF];
-    const int lt = lg - 3;
-    const unsigned b = blockIdx.x;
-    const int ox = (int)(b >> (2 * lt)) * kTile, oy = (int)((b >> lt) & ((1u << lt) - 1)) * kTile,
-              oz = (int)(b & ((1u << lt) - 1)) * kTile;
-    load_region<T, S>(su, u, lg, ox, oy, oz, R);
-    load_region<T, SF>(sf, f, lg, ox, oy, oz, R - 1);
+    int ox, oy, oz;
+    ix.origin(b, ox, oy, oz);
+    load_region<T, S, P2>(su, u, ix, ox, oy, oz, R);
+    load_region<T, SF, P2>(sf, f, ix, ox, oy, oz, R - 1);
     __syncthreads();
     // FAS right-hand side on the f region: f += L u (u here is the restricted fine u)
     {
@@ -147,36 +194,41 @@ k_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo
             sr = sr + __shfl(r, lane0 + q, 64);
             sum_u = sum_u + __shfl(ui, lane0 + q, 64);
         }
+        if (!ix.inside(ox + x, oy + y, oz + z)) return;   // all 8 children or none: the edge is even
         if (ch == 0) {
             const unsigned Xg = (unsigned)(ox / 2 + X), Yg = (unsigned)(oy / 2 + Y), Zg = (unsigned)(oz / 2 + Z);
-            const int lc = lg - 1;
             const T uc = sum_u * T(0.125);
-            const unsigned P = sidx(lc, Xg, Yg, Zg);
+            const unsigned P = ix.coarse(Xg, Yg, Zg);
             pu[P] = uc;
             pf[P] = sr * T(0.125);
-            uold[(((Xg << lc) | Yg) << lc) | Zg] = uc;
+            uold[ix.natural(Xg, Yg, Zg)] = uc;
         }
         // the tile itself: smoothed u and the FAS right-hand side
-        const unsigned g = sidx(lg, (unsigned)(ox + x), (unsigned)(oy + y), (unsigned)(oz + z));
+        const unsigned g = ix.at((unsigned)(ox + x), (unsigned)(oy + y), (unsigned)(oz + z));
         uo[g] = ui;
         fo[g] = fi;
     }
 }
 
+template <class T, int NU, bool P2>
+__global__ void __launch_bounds__(kFusedThreads)
+k_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo, T* __restrict__ fo,
+            T* __restrict__ pu, T* __restrict__ pf, T* __restrict__ uold, LevelIdx<P2> ix, T h2) {
+    body_level_pre<T, NU, P2>(u, f, uo, fo, pu, pf, uold, ix, h2, blockIdx.x);
+}
+
 // post leg: u = ui + (uc[parent] - uold[parent]) over the tile and a halo of 2 nu2 cells, then
 // nu2 red-black sweeps; the tile is written to uout.  fi is the FAS right-hand side of the level.
-template <class T, int NU>
-__global__ void __launch_bounds__(kFusedThreads)
-k_level_post(const T* __restrict__ ui, const T* __restrict__ fi, const T* __restrict__ uc,
-             const T* __restrict__ uold, T* __restrict__ uout, int lg, T h2) {
+template <class T, int NU, bool P2>
+__device__ __forceinline__ void body_level_post(const T* __restrict__ ui, const T* __restrict__ fi,
+                                                const T* __restrict__ uc, const T* __restrict__ uold,
+                                                T* __restrict__ uout, LevelIdx<P2> ix, T h2, unsigned b) {
     constexpr int R = 2 * NU;
     constexpr int S = kTile + 2 * R, SF = S - 2;
     __shared__ T su[S * S * S];
     __shared__ T sf[SF * SF * SF];
-    const int lt = lg - 3, lc = lg - 1;
-    const unsigned b = blockIdx.x, msk = (1u << lg) - 1;
-    const int ox = (int)(b >> (2 * lt)) * kTile, oy = (int)((b >> lt) & ((1u << lt) - 1)) * kTile,
-              oz = (int)(b & ((1u << lt) - 1)) * kTile;
+    int ox, oy, oz;
+    ix.origin(b, ox, oy, oz);
     {
         using Pp = Passes<S * S * S>;
         T v[Pp::n];
@@ -184,23 +236,31 @@ k_level_post(const T* __restrict__ ui, const T* __restrict__ fi, const T* __rest
         for (int r = 0; r < Pp::n; ++r) {
             const int t = Pp::cell(r);
             const int i = t / (S * S), j = (t / S) % S, m = t % S;
-            const unsigned x = (unsigned)(ox - R + i) & msk, y = (unsigned)(oy - R + j) & msk,
-                           z = (unsigned)(oz - R + m) & msk;
+            const unsigned x = ix.wrap(ox - R + i), y = ix.wrap(oy - R + j), z = ix.wrap(oz - R + m);
             const unsigned X = x >> 1, Y = y >> 1, Z = z >> 1;
-            v[r] = ui[sidx(lg, x, y, z)] + (uc[sidx(lc, X, Y, Z)] - uold[(((X << lc) | Y) << lc) | Z]);
+            v[r] = ui[ix.at(x, y, z)] + (uc[ix.coarse(X, Y, Z)] - uold[ix.natural(X, Y, Z)]);
         }
 #pragma unroll
         for (int r = 0; r < Pp::n; ++r)
             if (Pp::live(r)) su[(int)threadIdx.x + r * kFusedThreads] = v[r];
     }
-    load_region<T, SF>(sf, fi, lg, ox, oy, oz, R - 1);
+    load_region<T, SF, P2>(sf, fi, ix, ox, oy, oz, R - 1);
     __syncthreads();
     lds_sweeps<T, S, 1, 2 * NU>(su, sf, h2, R & 1);
     {
         const int t = threadIdx.x;
         const int x = t >> 6, y = (t >> 3) & 7, z = t & 7;
-        uout[sidx(lg, (unsigned)(ox + x), (unsigned)(oy + y), (unsigned)(oz + z))] = su[((x + R) * S + (y + R)) * S + (z + R)];
+        if (ix.inside(ox + x, oy + y, oz + z))
+            uout[ix.at((unsigned)(ox + x), (unsigned)(oy + y), (unsigned)(oz + z))] =
+                su[((x + R) * S + (y + R)) * S + (z + R)];
     }
+}
+
+template <class T, int NU, bool P2>
+__global__ void __launch_bounds__(kFusedThreads)
+k_level_post(const T* __restrict__ ui, const T* __restrict__ fi, const T* __restrict__ uc,
+             const T* __restrict__ uold, T* __restrict__ uout, LevelIdx<P2> ix, T h2) {
+    body_level_post<T, NU, P2>(ui, fi, uc, uold, uout, ix, h2, blockIdx.x);
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -469,27 +529,43 @@ void launch_rbgs_vec(T* u, const T* f, const Lay& L, double h, int colour, hipSt
 }
 
 bool level_fusable(int n, int nu1, int nu2) {
-    return (n == 16 || n == 32 || n == 64) && nu1 >= 1 && nu1 <= 2 && nu2 >= 1 && nu2 <= 2;
+    // colour-split with a colour-split coarse level; the wrap of LevelIdx needs n > kTile + 5
+    return n >= 16 && n <= 64 && n % 4 == 0 && nu1 >= 1 && nu1 <= 2 && nu2 >= 1 && nu2 <= 2;
+}
+
+static unsigned level_tiles(int n) {
+    const unsigned t = (unsigned)(n + kTile - 1) / kTile;
+    return t * t * t;
 }
 
 template <class T>
 void launch_level_pre(const T* u, const T* f, T* uo, T* fo, T* pu, T* pf, T* uold, int n, double h, int nu1,
                       hipStream_t st) {
-    const int lg = __builtin_ctz((unsigned)n);
-    const unsigned tiles = 1u << (3 * (lg - 3));
+    const int lg = log2_exact(n);
+    const unsigned tiles = level_tiles(n);
     const T h2 = (T)(h * h);
-    if (nu1 == 1) k_level_pre<T, 1><<<tiles, kFusedThreads, 0, st>>>(u, f, uo, fo, pu, pf, uold, lg, h2);
-    else k_level_pre<T, 2><<<tiles, kFusedThreads, 0, st>>>(u, f, uo, fo, pu, pf, uold, lg, h2);
+    auto run = [&](auto ix) {
+        constexpr bool P2 = std::is_same_v<decltype(ix), LevelIdx<true>>;
+        if (nu1 == 1) k_level_pre<T, 1, P2><<<tiles, kFusedThreads, 0, st>>>(u, f, uo, fo, pu, pf, uold, ix, h2);
+        else k_level_pre<T, 2, P2><<<tiles, kFusedThreads, 0, st>>>(u, f, uo, fo, pu, pf, uold, ix, h2);
+    };
+    if (lg >= 0) run(LevelIdx<true>{n, lg});
+    else run(LevelIdx<false>{n, lg});
 }
 
 template <class T>
 void launch_level_post(const T* ui, const T* fi, const T* uc, const T* uold, T* uout, int n, double h, int nu2,
                        hipStream_t st) {
-    const int lg = __builtin_ctz((unsigned)n);
-    const unsigned tiles = 1u << (3 * (lg - 3));
+    const int lg = log2_exact(n);
+    const unsigned tiles = level_tiles(n);
     const T h2 = (T)(h * h);
-    if (nu2 == 1) k_level_post<T, 1><<<tiles, kFusedThreads, 0, st>>>(ui, fi, uc, uold, uout, lg, h2);
-    else k_level_post<T, 2><<<tiles, kFusedThreads, 0, st>>>(ui, fi, uc, uold, uout, lg, h2);
+    auto run = [&](auto ix) {
+        constexpr bool P2 = std::is_same_v<decltype(ix), LevelIdx<true>>;
+        if (nu2 == 1) k_level_post<T, 1, P2><<<tiles, kFusedThreads, 0, st>>>(ui, fi, uc, uold, uout, ix, h2);
+        else k_level_post<T, 2, P2><<<tiles, kFusedThreads, 0, st>>>(ui, fi, uc, uold, uout, ix, h2);
+    };
+    if (lg >= 0) run(LevelIdx<true>{n, lg});
+    else run(LevelIdx<false>{n, lg});
 }
 
 #define MG_INST(T)                                                                                      \

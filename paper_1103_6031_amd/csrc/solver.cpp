@@ -126,9 +126,13 @@ static int validate_hier(const mg_hier* H) {
     return MG_OK;
 }
 
+// which small coarsenings get the second arrays of the fused tile kernels: none, the power-of-two
+// cubes, or every one that fits those kernels
+enum Fuse { kFuseNone, kFuseP2, kFuseAll };
+
 // Build the level list and carve buffers.  u_user / f_user may be null (size query).
 static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* const* u_user, Plan& P,
-                      bool fuse = true) {
+                      Fuse fuse = kFuseAll) {
     int rc = validate_hier(H);
     if (rc) return rc;
     P.nu1 = o ? o->nu1 : 2;
@@ -193,15 +197,16 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
             }
         }
     }
-    // coarsenings (below the base: their whole box is the restriction of the finer level) that
-    // are power-of-two cubes of 16^3, 32^3 or 64^3 run as two fused tile launches per cycle; their
+    // coarsenings (below the base: their whole box is the restriction of the finer level) of 16^3
+    // to 64^3 run as two fused tile launches per cycle; their
     // second arrays are reserved whatever nu1 / nu2 are, so that the workspace size depends on
     // the shapes and the precision only
-    if (fuse)
+    if (fuse != kFuseNone)
         for (int l = 1; l < P.last; ++l) {
             Level& L = P.L[l];
             const int n = L.d.x;
             if (L.p >= 0 || !L.periodic || L.d.y != n || L.d.z != n || !level_fusable(n, 1, 1)) continue;
+            if (fuse == kFuseP2 && !L.lay.pow2) continue;
             L.fusable = true;
             const size_t c = L.d.cells();
             if (P.mixed) {
@@ -661,10 +666,19 @@ static int solve(const mg_hier* H, const double* const* f, double* const* u, con
     Carver size_cv(nullptr);
     int rc = build_plan(H, o, size_cv, u, P);
     if (rc) return rc;
-    if (!ws || ws_bytes < size_cv.off) return fail(MG_EINVAL, "workspace too small: need " + std::to_string(size_cv.off));
+    const size_t need = size_cv.off;
+    // a workspace (or the static scratch array) without room for the fused levels that are no power
+    // of two runs them as one-step launches (same bits)
+    Fuse fuse = kFuseAll;
+    if (ws_bytes < need) {
+        fuse = kFuseP2;
+        size_cv = Carver(nullptr);
+        build_plan(H, o, size_cv, u, P, fuse);
+    }
+    if (!ws || ws_bytes < size_cv.off) return fail(MG_EINVAL, "workspace too small: need " + std::to_string(need));
     if (((uintptr_t)ws) & 255) return fail(MG_EINVAL, "workspace must be 256-byte aligned");
     Carver cv(ws);
-    build_plan(H, o, cv, u, P);
+    build_plan(H, o, cv, u, P, fuse);
     (void)hipGetLastError();
 
     const bool fixed = (o->flags & MG_FIXED_CYCLES) != 0;
@@ -921,7 +935,7 @@ static int solve_noalloc(const mg_hier* H, const double* const* f, double* const
     if (int v = validate_hier(H)) return v;
     Plan P;
     Carver size_cv(nullptr);
-    if (int rc = build_plan(H, o, size_cv, nullptr, P)) return rc;
+    if (int rc = build_plan(H, o, size_cv, nullptr, P, kFuseP2)) return rc;
     if (size_cv.off > (size_t)MG_SCRATCH_BYTES)
         return fail(MG_EINVAL, "problem needs " + std::to_string(size_cv.off) + " workspace bytes, above the " +
                                    std::to_string((size_t)MG_SCRATCH_BYTES) + " of the static scratch array");
@@ -1211,14 +1225,14 @@ static size_t batch_layout(int ninst, const int* n, const double* h, const mg_op
         Plan P;
         Carver cv(nullptr);
         // batched instances run the one-step kernels (no fused levels); the others are solo solves
-        if (build_plan(&H, o, cv, nullptr, P, !batchable(n[i]))) return 0;
+        if (build_plan(&H, o, cv, nullptr, P, batchable(n[i]) ? kFuseNone : kFuseAll)) return 0;
         slice[i] = off;
         slice_bytes[i] = (cv.off + 255) & ~(size_t)255;
         off += slice_bytes[i];
         if (batchable(n[i])) {
             Plan Q;
             Carver c2(ws ? ws + slice[i] : nullptr);
-            build_plan(&H, o, c2, nullptr, Q, false);
+            build_plan(&H, o, c2, nullptr, Q, kFuseNone);
             B.ids.push_back(i);
             B.P.push_back(Q);
         }
@@ -2574,11 +2588,11 @@ int mg_residual_hierarchy(const mg_hier* hier, const double* const* f, double* c
     o.nu1 = o.nu2 = 2;
     Plan P;
     Carver sz(nullptr);
-    int rc = build_plan(hier, &o, sz, u, P);
+    int rc = build_plan(hier, &o, sz, u, P, kFuseP2);   // runs no V-cycle
     if (rc) return rc;
     if (!workspace || workspace_bytes < sz.off) return fail(MG_EINVAL, "workspace too small");
     Carver cv(workspace);
-    build_plan(hier, &o, cv, u, P);
+    build_plan(hier, &o, cv, u, P, kFuseP2);
     (void)hipGetLastError();
     if ((rc = prepare_f(P, f, st))) return rc;
     for (int l = 0; l < P.nh; ++l) {
@@ -2794,11 +2808,11 @@ int mg_smooth_level(int n, double h, const double* f, double* u, int half_sweeps
     Plan P;
     Carver sz(nullptr);
     double* up[1] = {u};
-    int rc = build_plan(&H, &o, sz, up, P);
+    int rc = build_plan(&H, &o, sz, up, P, kFuseP2);   // runs no V-cycle
     if (rc) return rc;
     if (!workspace || workspace_bytes < sz.off) return fail(MG_EINVAL, "workspace too small");
     Carver cv(workspace);
-    build_plan(&H, &o, cv, up, P);
+    build_plan(&H, &o, cv, up, P, kFuseP2);
     (void)hipGetLastError();
     Level& L = P.L[0];
     const Lay nat(L.d, 0);
