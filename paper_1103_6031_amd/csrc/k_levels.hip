@@ -32,6 +32,11 @@ namespace mgic {
 constexpr int kTile = 8;            // tile edge (cells)
 constexpr int kFusedThreads = 512;  // one thread per tile cell
 
+// LDS cells of the legs' u regions (f = 0) and f regions (f = 1)
+constexpr int cube(int s) { return s * s * s; }
+constexpr int pre_cells(int nu, int f) { return cube(kTile + 2 * (2 * nu + 1) - 2 * f); }
+constexpr int post_cells(int nu, int f) { return cube(kTile + 2 * (2 * nu) - 2 * f); }
+
 // Loops over the cells of a region: each thread takes the cells t = threadIdx.x + r * 512; every
 // pass first forms all its values (an index past the end is clamped to the last cell, so every
 // load stays inside the arrays) and only then stores them, so that the loads of all passes are in
@@ -147,11 +152,10 @@ __device__ __forceinline__ void load_region(T* dst, const T* __restrict__ a, Lev
 template <class T, int NU, bool P2>
 __device__ __forceinline__ void body_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo,
                                                T* __restrict__ fo, T* __restrict__ pu, T* __restrict__ pf,
-                                               T* __restrict__ uold, LevelIdx<P2> ix, T h2, unsigned b) {
+                                               T* __restrict__ uold, LevelIdx<P2> ix, T h2, unsigned b, T* su,
+                                               T* sf) {
     constexpr int R = 2 * NU + 1;      // u halo: 2 nu1 half-sweeps + the residual stencil
     constexpr int S = kTile + 2 * R, SF = S - 2;
-    __shared__ T su[S * S * S];
-    __shared__ T sf[SF * SF * SF];
     int ox, oy, oz;
     ix.origin(b, ox, oy, oz);
     load_region<T, S, P2>(su, u, ix, ox, oy, oz, R);
@@ -214,7 +218,8 @@ template <class T, int NU, bool P2>
 __global__ void __launch_bounds__(kFusedThreads)
 k_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo, T* __restrict__ fo,
             T* __restrict__ pu, T* __restrict__ pf, T* __restrict__ uold, LevelIdx<P2> ix, T h2) {
-    body_level_pre<T, NU, P2>(u, f, uo, fo, pu, pf, uold, ix, h2, blockIdx.x);
+    __shared__ T su[pre_cells(NU, 0)], sf[pre_cells(NU, 1)];
+    body_level_pre<T, NU, P2>(u, f, uo, fo, pu, pf, uold, ix, h2, blockIdx.x, su, sf);
 }
 
 // post leg: u = ui + (uc[parent] - uold[parent]) over the tile and a halo of 2 nu2 cells, then
@@ -222,11 +227,10 @@ k_level_pre(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ uo
 template <class T, int NU, bool P2>
 __device__ __forceinline__ void body_level_post(const T* __restrict__ ui, const T* __restrict__ fi,
                                                 const T* __restrict__ uc, const T* __restrict__ uold,
-                                                T* __restrict__ uout, LevelIdx<P2> ix, T h2, unsigned b) {
+                                                T* __restrict__ uout, LevelIdx<P2> ix, T h2, unsigned b, T* su,
+                                                T* sf) {
     constexpr int R = 2 * NU;
     constexpr int S = kTile + 2 * R, SF = S - 2;
-    __shared__ T su[S * S * S];
-    __shared__ T sf[SF * SF * SF];
     int ox, oy, oz;
     ix.origin(b, ox, oy, oz);
     {
@@ -260,7 +264,40 @@ template <class T, int NU, bool P2>
 __global__ void __launch_bounds__(kFusedThreads)
 k_level_post(const T* __restrict__ ui, const T* __restrict__ fi, const T* __restrict__ uc,
              const T* __restrict__ uold, T* __restrict__ uout, LevelIdx<P2> ix, T h2) {
-    body_level_post<T, NU, P2>(ui, fi, uc, uold, uout, ix, h2, blockIdx.x);
+    __shared__ T su[post_cells(NU, 0)], sf[post_cells(NU, 1)];
+    body_level_post<T, NU, P2>(ui, fi, uc, uold, uout, ix, h2, blockIdx.x, su, sf);
+}
+
+// The same legs of the levels of many batched instances: a block finds its instance's level and
+// tile.  pre: a = {u, f, uo, pu, pf, uold}, part = fo; post: a = {ui, fi, uc, uold, uout}.
+template <class T, int NU>
+__global__ void __launch_bounds__(kFusedThreads) kb_level_pre(const BSeg* __restrict__ segs, int nseg,
+                                                              const int* __restrict__ active) {
+    __shared__ T su[pre_cells(NU, 0)], sf[pre_cells(NU, 1)];
+    unsigned lb;
+    const BSeg& s = seg_of(segs, nseg, lb);
+    if (!active[s.inst]) return;
+    const int n = s.L.d.x, lg = s.L.lgx;
+    const T h2 = (T)(s.h * s.h);
+    const T *u = (const T*)s.a[0], *f = (const T*)s.a[1];
+    T *uo = (T*)s.a[2], *pu = (T*)s.a[3], *pf = (T*)s.a[4], *uold = (T*)s.a[5], *fo = (T*)s.part;
+    if (lg >= 0) body_level_pre<T, NU, true>(u, f, uo, fo, pu, pf, uold, LevelIdx<true>{n, lg}, h2, lb, su, sf);
+    else body_level_pre<T, NU, false>(u, f, uo, fo, pu, pf, uold, LevelIdx<false>{n, lg}, h2, lb, su, sf);
+}
+
+template <class T, int NU>
+__global__ void __launch_bounds__(kFusedThreads) kb_level_post(const BSeg* __restrict__ segs, int nseg,
+                                                               const int* __restrict__ active) {
+    __shared__ T su[post_cells(NU, 0)], sf[post_cells(NU, 1)];
+    unsigned lb;
+    const BSeg& s = seg_of(segs, nseg, lb);
+    if (!active[s.inst]) return;
+    const int n = s.L.d.x, lg = s.L.lgx;
+    const T h2 = (T)(s.h * s.h);
+    const T *ui = (const T*)s.a[0], *fi = (const T*)s.a[1], *uc = (const T*)s.a[2], *uold = (const T*)s.a[3];
+    T* uout = (T*)s.a[4];
+    if (lg >= 0) body_level_post<T, NU, true>(ui, fi, uc, uold, uout, LevelIdx<true>{n, lg}, h2, lb, su, sf);
+    else body_level_post<T, NU, false>(ui, fi, uc, uold, uout, LevelIdx<false>{n, lg}, h2, lb, su, sf);
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -533,7 +570,7 @@ bool level_fusable(int n, int nu1, int nu2) {
     return n >= 16 && n <= 64 && n % 4 == 0 && nu1 >= 1 && nu1 <= 2 && nu2 >= 1 && nu2 <= 2;
 }
 
-static unsigned level_tiles(int n) {
+unsigned level_tiles(int n) {
     const unsigned t = (unsigned)(n + kTile - 1) / kTile;
     return t * t * t;
 }
@@ -568,6 +605,18 @@ void launch_level_post(const T* ui, const T* fi, const T* uc, const T* uold, T* 
     else run(LevelIdx<false>{n, lg});
 }
 
+template <class T>
+void launch_b_level_pre(const BSeg* segs, int nseg, unsigned grid, const int* active, int nu1, hipStream_t st) {
+    if (nu1 == 1) kb_level_pre<T, 1><<<grid, kFusedThreads, 0, st>>>(segs, nseg, active);
+    else kb_level_pre<T, 2><<<grid, kFusedThreads, 0, st>>>(segs, nseg, active);
+}
+
+template <class T>
+void launch_b_level_post(const BSeg* segs, int nseg, unsigned grid, const int* active, int nu2, hipStream_t st) {
+    if (nu2 == 1) kb_level_post<T, 1><<<grid, kFusedThreads, 0, st>>>(segs, nseg, active);
+    else kb_level_post<T, 2><<<grid, kFusedThreads, 0, st>>>(segs, nseg, active);
+}
+
 #define MG_INST(T)                                                                                      \
     template void launch_resid_restrict_p2<T>(const T*, const T*, int, double, T*, T*, T*, hipStream_t);      \
     template void launch_prolong_black_p2<T>(T*, int, const T*, const T*, hipStream_t);                       \
@@ -576,7 +625,9 @@ void launch_level_post(const T* ui, const T* fi, const T* uc, const T* uold, T* 
     template void launch_rbgs_vec_corr<T>(T*, const T*, const Lay&, double, const T*, const T*, hipStream_t);     \
     template void launch_fas_vec<T>(const T*, T*, int, double, hipStream_t);                                  \
     template void launch_level_pre<T>(const T*, const T*, T*, T*, T*, T*, T*, int, double, int, hipStream_t); \
-    template void launch_level_post<T>(const T*, const T*, const T*, const T*, T*, int, double, int, hipStream_t);
+    template void launch_level_post<T>(const T*, const T*, const T*, const T*, T*, int, double, int, hipStream_t); \
+    template void launch_b_level_pre<T>(const BSeg*, int, unsigned, const int*, int, hipStream_t);            \
+    template void launch_b_level_post<T>(const BSeg*, int, unsigned, const int*, int, hipStream_t);
 MG_INST(float)
 MG_INST(double)
 #undef MG_INST

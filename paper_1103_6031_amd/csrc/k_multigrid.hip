@@ -1717,18 +1717,6 @@ unsigned prolong_black_blocks(const Lay& L, const ParentMap& pm, int elem) {
     return (unsigned)((n + kBlock - 1) / kBlock);
 }
 
-__device__ __forceinline__ const BSeg& seg_of(const BSeg* __restrict__ segs, int nseg, unsigned& lb) {
-    const unsigned b = blockIdx.x;
-    int lo = 0, hi = nseg - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (segs[mid].blk0 <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    lb = b - segs[lo].blk0;
-    return segs[lo];
-}
-
 template <class T, int V>
 __global__ void kb_rbgs(const BSeg* __restrict__ segs, int nseg, const int* __restrict__ active, int colour) {
     unsigned lb;

@@ -314,8 +314,22 @@ struct BSeg {
     ParentMap pm;       // transfers: the coarse representation inside the parent
     double h;           // level spacing (FAS right-hand side: the parent's; mean removal: 1/cells)
     void* a[6];         // arrays, listed per batched kernel
-    double* part;       // reductions: nblk partial sums of this instance
+    double* part;       // reductions: nblk partial sums of this instance; fused pre leg: fo
 };
+#ifdef __HIPCC__
+// the segment of this block and the block's index in it (binary search over the table; block-uniform)
+__device__ __forceinline__ const BSeg& seg_of(const BSeg* __restrict__ segs, int nseg, unsigned& lb) {
+    const unsigned b = blockIdx.x;
+    int lo = 0, hi = nseg - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (segs[mid].blk0 <= b) lo = mid;
+        else hi = mid - 1;
+    }
+    lb = b - segs[lo].blk0;
+    return segs[lo];
+}
+#endif
 // per-instance finalize of a batched reduction: *out = w * sum(part[0..cnt)), one block each
 struct BFin {
     const double* part;
@@ -339,6 +353,13 @@ template <class T> void launch_b_rbgs(const BSeg* segs, int nseg, unsigned grid,
 template <class T> void launch_b_resid_restrict(const BSeg* segs, int nseg, unsigned grid, const int* active,
                                                 hipStream_t st);
 // a = {pu, pf}: FAS right-hand side (step 6), h = the parent's spacing
+// fused legs of levels of level_fusable edges (nblk = level_tiles(edge)); pre: a = {u, f, uo, pu, pf,
+// uold}, part = fo; post: a = {ui, fi, uc, uold, uout}
+unsigned level_tiles(int n);
+template <class T>
+void launch_b_level_pre(const BSeg* segs, int nseg, unsigned grid, const int* active, int nu1, hipStream_t st);
+template <class T>
+void launch_b_level_post(const BSeg* segs, int nseg, unsigned grid, const int* active, int nu2, hipStream_t st);
 template <class T> void launch_b_fas(const BSeg* segs, int nseg, unsigned grid, const int* active, hipStream_t st);
 // a = {u, pu, uold}: step 8 (black cells only if black_only)
 template <class T> void launch_b_prolong(const BSeg* segs, int nseg, unsigned grid, const int* active,

@@ -1068,10 +1068,12 @@ struct BatchPlan {
     std::vector<int> ids;        // caller's index of each batched instance
     std::vector<Plan> P;
     int D = 0;                   // depths of grid levels (above every instance's tail)
+    int D1 = 0;                  // depths with levels run by one-step launches
     bool mixed = false;
     // static tables: [0] float, [1] double; float tables by parity of the finest correction buffer
     std::vector<BSeg> segs;
-    std::vector<BLaunch> sm[2][2], rr[2][2], fas[2][2], pr[2][2];
+    std::vector<BLaunch> sm[2][2], rr[2][2], fas[2][2], pr[2][2];   // one-step launches per depth
+    std::vector<BLaunch> pre[2][2], post[2][2];                     // fused legs per depth
     BLaunch outer[2], resid;
     std::vector<TailPlan<float>> tpf;
     std::vector<TailPlan<double>> tpd;
@@ -1140,9 +1142,11 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
     B.rr[ti][par].assign(B.D, BLaunch{});
     B.fas[ti][par].assign(B.D, BLaunch{});
     B.pr[ti][par].assign(B.D, BLaunch{});
+    B.pre[ti][par].assign(B.D, BLaunch{});
+    B.post[ti][par].assign(B.D, BLaunch{});
     for (int d = 0; d < B.D; ++d) {
-        std::vector<BSeg> sm, rr, fa, pr;
-        const SmoothShape sh = shape[d];
+        std::vector<BSeg> sm, rr, fa, pr, pre, post;
+        const SmoothShape sh = d < B.D1 ? shape[d] : SmoothShape{};
         for (int i = 0; i < n; ++i) {
             Plan& P = B.P[i];
             if (d >= P.tail) continue;
@@ -1152,7 +1156,19 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
             T* u = d == 0 ? fine_u[i] : b.u;
             const size_t cells = L.d.cells();
             const Lay C(Dims{L.d.x / 2, L.d.y / 2, L.d.z / 2}, 0);
-            BSeg s = seg0(i, rbgs_split_blocks(L.lay, sh.block, sh.V));
+            BSeg s;
+            if (fused<T>(P, d)) {
+                s = seg0(i, level_tiles(L.d.x));
+                s.L = L.lay;
+                s.h = L.h;
+                s.a[0] = b.u; s.a[1] = b.f; s.a[2] = b.ua; s.a[3] = q.u; s.a[4] = q.f; s.a[5] = b.uold;
+                s.part = (double*)b.fa;
+                pre.push_back(s);
+                s.a[0] = b.ua; s.a[1] = b.fa; s.a[2] = q.u; s.a[3] = b.uold; s.a[4] = b.u;
+                post.push_back(s);
+                continue;
+            }
+            s = seg0(i, rbgs_split_blocks(L.lay, sh.block, sh.V));
             s.L = L.lay;
             s.h = L.h;
             s.a[0] = u;
@@ -1165,12 +1181,14 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
             s.h = L.h;
             s.a[0] = u; s.a[1] = b.f; s.a[2] = q.u; s.a[3] = q.f; s.a[4] = b.uold;
             rr.push_back(s);
-            s = seg0(i, fas_blocks(C, L.pm, (int)sizeof(T)));
-            s.C = C;
-            s.pm = L.pm;
-            s.h = Q.h;
-            s.a[0] = q.u; s.a[1] = q.f;
-            fa.push_back(s);
+            if (!fused<T>(P, d + 1)) {   // a fused level does its own step 6
+                s = seg0(i, fas_blocks(C, L.pm, (int)sizeof(T)));
+                s.C = C;
+                s.pm = L.pm;
+                s.h = Q.h;
+                s.a[0] = q.u; s.a[1] = q.f;
+                fa.push_back(s);
+            }
             s = seg0(i, B.P[i].nu2 > 0 ? prolong_black_blocks(L.lay, L.pm, (int)sizeof(T)) : cdiv(cells, kBlock));
             s.L = L.lay;
             s.pm = L.pm;
@@ -1181,6 +1199,8 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
         B.rr[ti][par][d] = add_launch(tab, rr);
         B.fas[ti][par][d] = add_launch(tab, fa);
         B.pr[ti][par][d] = add_launch(tab, pr);
+        B.pre[ti][par][d] = add_launch(tab, pre);
+        B.post[ti][par][d] = add_launch(tab, post);
     }
 }
 
@@ -1195,6 +1215,7 @@ static std::vector<TailPlan<T>> tail_plans(BatchPlan& B, unsigned& lds) {
         tp.nu1 = P.nu1;
         tp.nu2 = P.nu2;
         tp.inst = i;
+        tp.fas0 = P.tail > 0 && fused<T>(P, P.tail - 1);   // a fused parent leaves step 6 to this level
         for (int k = 0; k < tp.n; ++k) {
             ::mgic::B<T> c = bufs<T>(P.L[P.tail + k]);
             tp.lev[k] = TailLevel<T>{c.u, c.f, P.L[P.tail + k].lay, P.L[P.tail + k].h, 0, 0, 0};
@@ -1213,7 +1234,7 @@ static size_t batch_segs_cap(const BatchPlan& B) {
 
 // build plans (cv == null: sizes only); returns bytes of the whole workspace or 0 on error
 static size_t batch_layout(int ninst, const int* n, const double* h, const mg_opts* o, char* ws, BatchPlan& B,
-                           std::vector<size_t>& slice, std::vector<size_t>& slice_bytes) {
+                           std::vector<size_t>& slice, std::vector<size_t>& slice_bytes, Fuse fuse = kFuseAll) {
     size_t off = 0;
     slice.assign(ninst, 0);
     slice_bytes.assign(ninst, 0);
@@ -1224,21 +1245,37 @@ static size_t batch_layout(int ninst, const int* n, const double* h, const mg_op
         mg_hier H = single_level(n[i], h ? h[i] : 1.0);
         Plan P;
         Carver cv(nullptr);
-        // batched instances run the one-step kernels (no fused levels); the others are solo solves
-        if (build_plan(&H, o, cv, nullptr, P, batchable(n[i]) ? kFuseNone : kFuseAll)) return 0;
+        // (instances outside the batched schedule are solo solves without fusable levels)
+        if (build_plan(&H, o, cv, nullptr, P, fuse)) return 0;
         slice[i] = off;
         slice_bytes[i] = (cv.off + 255) & ~(size_t)255;
         off += slice_bytes[i];
         if (batchable(n[i])) {
             Plan Q;
             Carver c2(ws ? ws + slice[i] : nullptr);
-            build_plan(&H, o, c2, nullptr, Q, kFuseNone);
+            build_plan(&H, o, c2, nullptr, Q, fuse);
             B.ids.push_back(i);
             B.P.push_back(Q);
         }
     }
-    B.D = 0;
+    B.D = B.D1 = 0;
     for (auto& P : B.P) B.D = std::max(B.D, P.tail);
+    // The fused legs recompute their tiles' halos (4.7 times the updates in the pre leg), which pays
+    // while a depth's levels are bound by launches.  Measured for 64 instances of 32^3 - 128^3, FP32,
+    // per cycle: 1353 tiles at depth 2 take 47 us fused and 69 us by one-step launches, 11279 tiles
+    // at depth 1 243 us and 160 us; the line lies between, at 8 tiles per CU.
+    for (int d = 1; d < B.D; ++d) {
+        unsigned tiles = 0;
+        for (auto& P : B.P)
+            if (d < P.tail && P.L[d].fusable) tiles += level_tiles(P.L[d].d.x);
+        if (tiles > 2048)
+            for (auto& P : B.P)
+                if (d < P.tail) P.L[d].fusable = false;
+    }
+    for (auto& P : B.P) {
+        for (int d = 0; d < P.tail; ++d)
+            if (!(B.mixed ? fused<float>(P, d) : fused<double>(P, d))) B.D1 = std::max(B.D1, d + 1);
+    }
     B.segs_cap = batch_segs_cap(B);
     const size_t ni = B.P.size();
     Carver cv(ws ? ws + off : nullptr);
@@ -1374,29 +1411,29 @@ static int tune_smoother(BatchPlan& B, int ti, hipStream_t st, std::vector<Smoot
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         if (g_force_shape >= 0) {
-            out.assign(B.D, kShapes[g_force_shape]);
+            out.assign(B.D1, kShapes[g_force_shape]);
             return MG_OK;
         }
         auto it = g_tune.find(key);
-        if (it != g_tune.end() && (int)it->second.size() == B.D) {
-            out = it->second;
+        if (it != g_tune.end() && (int)it->second.size() >= B.D1) {   // one entry per depth
+            out.assign(it->second.begin(), it->second.begin() + B.D1);
             return MG_OK;
         }
     }
-    out.assign(B.D, SmoothShape{});
+    out.assign(B.D1, SmoothShape{});
     const int n = (int)B.P.size();
     std::vector<int> ones(n + 1, 1);
     MG_HIP(hipMemcpyAsync(B.active_dev, ones.data(), ones.size() * sizeof(int), hipMemcpyHostToDevice, st));
     hipEvent_t e0, e1;
     MG_HIP(hipEventCreate(&e0));
     MG_HIP(hipEventCreate(&e1));
-    for (int d = 0; d < B.D; ++d) {
+    for (int d = 0; d < B.D1; ++d) {
         float best = 1e30f;
         for (const SmoothShape& sh : kShapes) {
             std::vector<BSeg> tab, segs;
             for (int i = 0; i < n; ++i) {
                 Plan& P = B.P[i];
-                if (d >= P.tail) continue;
+                if (d >= P.tail || fused<T>(P, d)) continue;
                 Level& L = P.L[d];
                 BSeg s = seg0(i, rbgs_split_blocks(L.lay, sh.block, sh.V));
                 s.L = L.lay;
@@ -1456,6 +1493,8 @@ static void b_vcycle(BatchPlan& B, int ti, int par, bool skip_first_red, hipStre
     const int* act = B.active_dev;
     BSeg* sd = B.segs_dev;
     for (int d = 0; d < B.D; ++d) {
+        const BLaunch& pre = B.pre[ti][par][d];
+        if (pre.n) launch_b_level_pre<T>(sd + pre.off, pre.n, pre.grid, act, B.P[0].nu1, st);
         const BLaunch& sm = B.sm[ti][par][d];
         for (int s = 0; s < B.P[0].nu1; ++s)
             for (int c = 0; c < 2; ++c) {
@@ -1470,6 +1509,8 @@ static void b_vcycle(BatchPlan& B, int ti, int par, bool skip_first_red, hipStre
     if (ti == 0) launch_b_tail<float>(B.tpf_dev, (int)B.P.size(), B.lds_f, act, st);
     else launch_b_tail<double>(B.tpd_dev, (int)B.P.size(), B.lds_d, act, st);
     for (int d = B.D - 1; d >= 0; --d) {
+        const BLaunch& post = B.post[ti][par][d];
+        if (post.n) launch_b_level_post<T>(sd + post.off, post.n, post.grid, act, B.P[0].nu2, st);
         const BLaunch& pr = B.pr[ti][par][d];
         if (pr.n) launch_b_prolong<T>(sd + pr.off, pr.n, pr.grid, act, B.P[0].nu2 > 0, st);
         const BLaunch& sm = B.sm[ti][par][d];
@@ -1504,10 +1545,13 @@ static int solve_batch(int ninst, const int* n, const double* h, const double* c
     std::vector<size_t> slice, sbytes;
     const size_t need = batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes);
     if (!need) return MG_EINVAL;   // build_plan reported the reason
-    if (!ws || ws_bytes < need) return fail(MG_EINVAL, "workspace too small: need " + std::to_string(need));
+    // a workspace without room for the fused levels' second arrays runs one-step launches (same bits)
+    const Fuse fuse = ws_bytes < need ? kFuseNone : kFuseAll;
+    const size_t least = fuse == kFuseAll ? need : batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes, fuse);
+    if (!ws || ws_bytes < least) return fail(MG_EINVAL, "workspace too small: need " + std::to_string(need));
     if (((uintptr_t)ws) & 255) return fail(MG_EINVAL, "workspace must be 256-byte aligned");
     if (int rc = refuse_capture(st, "the batched solve (it uploads tables and reads flags back)")) return rc;
-    batch_layout(ninst, n, h, o, (char*)ws, B, slice, sbytes);
+    batch_layout(ninst, n, h, o, (char*)ws, B, slice, sbytes, fuse);
     (void)hipGetLastError();
     int worst = MG_OK;
     // instances outside the batched schedule (tiny or odd grids) are solved on their own
@@ -1728,7 +1772,7 @@ static int solve_batch(int ninst, const int* n, const double* h, const double* c
     for (const SmoothShape& sh : B.mixed ? shf : shd) shape_tag += std::to_string(sh.block) + "x" + std::to_string(sh.V) + ",";
     const std::string wkey = std::to_string((uintptr_t)ws) + "|" + batch_key(B, B.mixed ? 0 : 1) + "|" + shape_tag + "|" +
                              std::to_string(o->nu2) + "|" +
-                             std::to_string(B.segs.size()) + "|" + (fixed ? "f" : "c");
+                             std::to_string(B.segs.size()) + "|" + std::to_string((int)fuse) + "|" + (fixed ? "f" : "c");
     if (B.mixed) {
         bool first = true;
         int par = 0;

@@ -108,7 +108,14 @@ int spec_plan(const int* n, int isolated, void* ws, SpecPlan& S) {
     spec_grid_carve(S.G, (char*)ws, off);
     off = align256(off);
     S.G.W = ws ? (double2*)((char*)ws + off) : nullptr;
-    off += kFftMaxFields * sizeof(double2) * S.G.field();   // the hybrid correction's components
+    const SpecGrid& G = S.G;
+    const size_t used = kFftMaxFields * sizeof(double2) * G.field();   // the hybrid correction's components
+    // the size that callers reserve stays that of one n0 x n1 x P2 and two n0 x P1 x P2 complex arrays
+    // where these are more
+    const size_t w1 = sizeof(double2) * (size_t)G.n[0] * G.n[1] * G.P[2];
+    const size_t w2 = sizeof(double2) * (size_t)G.n[0] * G.P[1] * G.P[2];
+    const size_t full = align256(w1) + align256(w2) + w2;
+    off += std::max(used, full);
     S.bytes = align256(off);
     return MG_OK;
 }

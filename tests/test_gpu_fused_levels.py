@@ -67,3 +67,28 @@ def test_workspace_without_the_second_arrays():
     rc = mgic._lib.mg_solve_level(n, h, f.data_ptr(), u.data_ptr(), ctypes.byref(o), ctypes.byref(st),
                                   ctypes.c_void_p(ws.ptr), need // 2, mgic._stream())
     assert rc == mgic.MG_EINVAL
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+def test_batched_fused_levels_match_their_one_step_launches(prec):
+    """A batch workspace without room for the second arrays runs every level by one-step launches."""
+    import torch
+    from paper_1103_6031_amd import mgic
+    sizes = [32, 24, 64, 40, 112, 256, 96]
+    fs = [to_dev(_f(n, 5)) for n in sizes]
+    o = mgic.make_opts(prec=prec, fixed_cycles=True, max_cycles=2)
+    need = mgic.mg_batch_workspace_bytes(sizes, o)
+    ws = mgic.Workspace(need)
+    note("batched fused levels %s" % prec)
+    want, _ = mgic.mg_solve_batch(fs, [100.0 / n for n in sizes], opts=o, workspace=ws)
+    n = (ctypes.c_int * len(sizes))(*sizes)
+    h = (ctypes.c_double * len(sizes))(*[100.0 / v for v in sizes])
+    got = [torch.empty_like(f) for f in fs]
+    fp, keep_f = mgic._ptr_array([f.data_ptr() for f in fs])
+    up, keep_u = mgic._ptr_array([u.data_ptr() for u in got])
+    st = (mgic.mg_stats * len(sizes))()
+    rc = mgic._lib.mg_solve_batch(len(sizes), n, h, fp, up, ctypes.byref(o), st, ctypes.c_void_p(ws.ptr),
+                                  need - 4096, mgic._stream())
+    assert rc == mgic.MG_OK
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
