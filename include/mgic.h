@@ -442,7 +442,9 @@ int mg_ghost_fill_ho(const mg_hier* hier, int order, int p, const double* const*
 int mg_kprof_enable(int period);
 
 /* Wait for the recorded events, return the summed launch durations (ms), the number of timed
- * launches and their algorithmic bytes (3 words per cell-update: u in, f in, u out), and reset. */
+ * launches and their algorithmic bytes, and reset.  A half-sweep launch counts 3 words per
+ * cell-update (u in, f in, u out); a launch that runs two whole sweeps counts what it cannot do
+ * without, 2.5 words per cell (one colour and f in, both colours out). */
 int mg_kprof_read(double* ms_total, long long* launches, double* bytes_total);
 
 const char* mg_last_error(void);

@@ -70,7 +70,7 @@ __device__ __forceinline__ void lds_half_sweep(T* su, const T* sf, T h2, int col
         const int z = k + 2 * m + q;
         const int c = (i * S + j) * S + z;
         const T s = ((su[c - S * S] + su[c + S * S]) + (su[c - S] + su[c + S])) + (su[c - 1] + su[c + 1]);
-        v[r] = (s - h2 * sf[((i - 1) * SF + (j - 1)) * SF + (z - 1)]) / T(6);
+        v[r] = div6(s - h2 * sf[((i - 1) * SF + (j - 1)) * SF + (z - 1)]);
         at[r] = c;
     }
 #pragma unroll
@@ -430,27 +430,6 @@ k_rbgs_vec(T* __restrict__ u, const T* __restrict__ f, int lgx, int lgy, int lgz
 // W consecutive Z of one coarse row: a vector of uold (natural order) and two half-vectors of pu
 // (colour-split order, even and odd Z in the two halves).  Same arithmetic as k_prolong_black_p2
 // followed by k_rbgs_vec, so the same bits.
-// d[k] = pu - uold for the parents (X, Y, j0 + k) of a run of W black cells
-template <class T>
-__device__ __forceinline__ void corr_delta(const T* __restrict__ pu, const T* __restrict__ uold, int lc, unsigned X,
-                                           unsigned Y, unsigned j0, T* d) {
-    constexpr int W = Vec16<T>::W;
-    const unsigned nch = (1u << lc) >> 1;
-    const unsigned rb = ((X << lc) | Y) << lc;
-    const unsigned he = ((X + Y) & 1u) * nch, ho = nch - he;   // halves holding even / odd Z
-    const typename Vec16<T>::type o = *(const typename Vec16<T>::type*)(uold + rb + j0);
-    if constexpr (W == 4) {
-        const float2 pe = *(const float2*)(pu + rb + he + (j0 >> 1)), po = *(const float2*)(pu + rb + ho + (j0 >> 1));
-        d[0] = pe.x - o.x;
-        d[1] = po.x - o.y;
-        d[2] = pe.y - o.z;
-        d[3] = po.y - o.w;
-    } else {
-        d[0] = pu[rb + he + (j0 >> 1)] - o.x;
-        d[1] = pu[rb + ho + (j0 >> 1)] - o.y;
-    }
-}
-
 template <class T>
 __global__ void __launch_bounds__(256)
 k_rbgs_vec_corr(T* __restrict__ u, const T* __restrict__ f, int lgx, int lgy, int lgz, T h2,
@@ -501,7 +480,7 @@ k_rbgs_vec_corr(T* __restrict__ u, const T* __restrict__ f, int lgx, int lgy, in
         const T zm = q ? C[k] : (k == 0 ? edge : C[k - 1]);
         const T zp = q ? (k == W - 1 ? edge : C[k + 1]) : C[k];
         const T s = ((XM[k] + XP[k]) + (YM[k] + YP[k])) + (zm + zp);
-        out[k] = (s - h2 * lane<T>(F, k)) / T(6);
+        out[k] = div6(s - h2 * lane<T>(F, k));
     }
     V o;
     if constexpr (W == 4) o = V{out[0], out[1], out[2], out[3]};

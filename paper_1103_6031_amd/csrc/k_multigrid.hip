@@ -209,7 +209,7 @@ __device__ __forceinline__ void cell_rbgs_split(T* __restrict__ u, const T* __re
     const T ym = u[rym + oth + j], yp = u[ryp + oth + j];
     const T zm = u[r0 + oth + jm], zp = u[r0 + oth + jp];
     const T s = ((xm + xp) + (ym + yp)) + (zm + zp);
-    u[r0 + own + j] = (s - h2 * f[r0 + own + j]) / T(6);
+    u[r0 + own + j] = div6(s - h2 * f[r0 + own + j]);
 }
 
 // residual + restriction of the covered coarse cell t (steps 3-5)
@@ -412,7 +412,7 @@ __global__ void k_rbgs_ghost(T* __restrict__ u, const T* __restrict__ f, const T
     const T zm = z > 0 ? u[r0 + oth + (unsigned)((z - 1) >> 1)] : g[ghost_face_offset(d, 4) + (size_t)x * d.y + y];
     const T zp = z < d.z - 1 ? u[r0 + oth + (unsigned)((z + 1) >> 1)] : g[ghost_face_offset(d, 5) + (size_t)x * d.y + y];
     const T s = ((xm + xp) + (ym + yp)) + (zm + zp);
-    u[r0 + own + j] = (s - h2 * f[r0 + own + j]) / T(6);
+    u[r0 + own + j] = div6(s - h2 * f[r0 + own + j]);
 }
 
 // k_rbgs_ghost on runs of W cells of the colour in one half-row (W = 4 in FP32, 2 in FP64), as
@@ -462,7 +462,7 @@ __global__ void k_rbgs_ghost_vec(T* __restrict__ u, const T* __restrict__ f, con
             const T zm = q ? lane<T>(C, k) : (k == 0 ? edge : lane<T>(C, k - 1));
             const T zp = q ? (k == W - 1 ? edge : lane<T>(C, k + 1)) : lane<T>(C, k);
             const T s = ((lane<T>(XM, k) + lane<T>(XP, k)) + (lane<T>(YM, k) + lane<T>(YP, k))) + (zm + zp);
-            out[k] = (s - h2 * lane<T>(F, k)) / T(6);
+            out[k] = div6(s - h2 * lane<T>(F, k));
         }
         V o;
         if constexpr (W == 4) o = V{out[0], out[1], out[2], out[3]};
@@ -1257,7 +1257,7 @@ __device__ __forceinline__ double body_outer_split(const double* __restrict__ u_
         rhs[t] = rf;
         // black entries of e_out are left as they are: the black half-sweep that follows writes
         // every one of them before anything reads them
-        if (!col) e_out[t] = (0.0f - h2f * rf) / 6.0f;
+        if (!col) e_out[t] = div6(0.0f - h2f * rf);
     }
     return acc;
 }
@@ -1338,7 +1338,7 @@ __device__ __forceinline__ double body_outer_pairs(const double* __restrict__ u_
         if constexpr (WU) *(double2*)(u_out + t) = double2{c0[0], c0[1]};
         *(float2*)(rhs + t) = float2{rf0, rf1};
         // black entries of e_out are left as they are (see body_outer_split)
-        if (!c.col) *(float2*)(e_out + t) = float2{(0.0f - h2f * rf0) / 6.0f, (0.0f - h2f * rf1) / 6.0f};
+        if (!c.col) *(float2*)(e_out + t) = float2{div6(0.0f - h2f * rf0), div6(0.0f - h2f * rf1)};
     }
     return acc;
 }

@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "div6.h"
 #include "fastdiv.h"
 
 namespace mgic {
@@ -231,6 +232,14 @@ void launch_rbgs_vec_corr(T* u, const T* f, const Lay& L, double h, const T* pu,
 template <class T>
 void launch_rbgs_vec(T* u, const T* f, const Lay& L, double h, int colour, hipStream_t st, hipEvent_t ev0,
                      hipEvent_t ev1);
+// two red-black sweeps of a periodic colour-split power-of-two cube (two_sweeps_ok) in one launch, u -> out
+// (another array); mode kSweepCorr adds the correction pu - uold to u's black cells first, kSweepRed
+// starts from u's red cells, the first red half-sweep done; same bits as the one-step launches
+enum { kSweepPlain = 0, kSweepCorr = 1, kSweepRed = 2 };
+bool two_sweeps_ok(const Lay& L);
+template <class T>
+void launch_two_sweeps(const T* u, const T* f, T* out, const Lay& L, double h, int mode, const T* pu, const T* uold,
+                       hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 template <class T>
 void launch_level_pre(const T* u, const T* f, T* uo, T* fo, T* pu, T* pf, T* uold, int n, double h, int nu1,
                       hipStream_t st);

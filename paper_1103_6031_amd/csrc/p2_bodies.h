@@ -51,7 +51,7 @@ __device__ __forceinline__ void run_rbgs_vec(T* __restrict__ u, const T* __restr
         const T zm = q ? lane<T>(C, k) : (k == 0 ? edge : lane<T>(C, k - 1));
         const T zp = q ? (k == W - 1 ? edge : lane<T>(C, k + 1)) : lane<T>(C, k);
         const T s = ((lane<T>(XM, k) + lane<T>(XP, k)) + (lane<T>(YM, k) + lane<T>(YP, k))) + (zm + zp);
-        out[k] = (s - h2 * lane<T>(F, k)) / T(6);
+        out[k] = div6(s - h2 * lane<T>(F, k));
     }
     V o;
     if constexpr (W == 4) o = V{out[0], out[1], out[2], out[3]};
@@ -218,6 +218,27 @@ __device__ __forceinline__ void run_prolong_black_vec(T* __restrict__ u, int lg,
     if constexpr (W == 4) o = V{out[0], out[1], out[2], out[3]};
     else o = V{out[0], out[1]};
     *(V*)ur = o;
+}
+
+// d[k] = pu - uold for the parents (X, Y, j0 + k) of a run of W black cells
+template <class T>
+__device__ __forceinline__ void corr_delta(const T* __restrict__ pu, const T* __restrict__ uold, int lc, unsigned X,
+                                           unsigned Y, unsigned j0, T* d) {
+    constexpr int W = Vec16<T>::W;
+    const unsigned nch = (1u << lc) >> 1;
+    const unsigned rb = ((X << lc) | Y) << lc;
+    const unsigned he = ((X + Y) & 1u) * nch, ho = nch - he;   // halves holding even / odd Z
+    const typename Vec16<T>::type o = *(const typename Vec16<T>::type*)(uold + rb + j0);
+    if constexpr (W == 4) {
+        const float2 pe = *(const float2*)(pu + rb + he + (j0 >> 1)), po = *(const float2*)(pu + rb + ho + (j0 >> 1));
+        d[0] = pe.x - o.x;
+        d[1] = po.x - o.y;
+        d[2] = pe.y - o.z;
+        d[3] = po.y - o.w;
+    } else {
+        d[0] = pu[rb + he + (j0 >> 1)] - o.x;
+        d[1] = pu[rb + ho + (j0 >> 1)] - o.y;
+    }
 }
 
 }  // namespace mgic

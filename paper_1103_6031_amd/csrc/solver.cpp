@@ -76,6 +76,10 @@ struct Level {
     bool fusable = false;
     double *ua = nullptr, *fa = nullptr;
     float *ua32 = nullptr, *fa32 = nullptr;
+    // second u of a level smoothed by k_two_sweeps (between its pre and post smoothing); where the fused
+    // outer step's second e is free, that
+    double* us = nullptr;
+    float* us32 = nullptr;
 };
 
 struct Plan {
@@ -91,10 +95,12 @@ struct Plan {
 
 enum { S_FSUM = 0, S_FNORM = 1, S_RNORM = 2, S_USUM = 3, S_TMP = 4, S_COUNT = 8 };
 
-template <class T> struct B { T *u, *f, *g, *uold, *ua, *fa; };
+template <class T> struct B { T *u, *f, *g, *uold, *ua, *fa, *us; };
 template <class T> static B<T> bufs(Level& l);
-template <> B<double> bufs<double>(Level& l) { return {l.u, l.f, l.g, l.uold, l.ua, l.fa}; }
-template <> B<float> bufs<float>(Level& l) { return {l.u32, l.f32, l.g32, l.uold32, l.ua32, l.fa32}; }
+template <> B<double> bufs<double>(Level& l) { return {l.u, l.f, l.g, l.uold, l.ua, l.fa, l.us}; }
+template <> B<float> bufs<float>(Level& l) {
+    return {l.u32, l.f32, l.g32, l.uold32, l.ua32, l.fa32, l.ealt ? l.ealt : l.us32};
+}
 
 static bool odd_ok(int m) { return m == 1 || m == 3 || m == 5 || m == 7; }
 
@@ -216,6 +222,14 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
                 L.ua = cv.take<double>(c);
                 L.fa = cv.take<double>(c);
             }
+        }
+    // the second u of the larger power-of-two periodic levels, for smoothing in one launch
+    if (fuse == kFuseAll)
+        for (int l = 0; l < P.last; ++l) {
+            Level& L = P.L[l];
+            if (!L.periodic || !two_sweeps_ok(L.lay)) continue;
+            if (!P.mixed) L.us = cv.take<double>(L.d.cells());
+            else if (!L.ealt) L.us32 = cv.take<float>(L.d.cells());
         }
     // the small periodic levels at the bottom, below any fused one, run as one single-workgroup
     // launch (measured: a fused 16^3 level and an 8^3 tail take 28 us per FP32 cycle, a 16^3
@@ -413,6 +427,21 @@ static bool p2lev(const Level& L) {
            L.pm.off[0] == 0 && L.pm.off[1] == 0 && L.pm.off[2] == 0;
 }
 
+// level l is smoothed by k_two_sweeps before and after the coarse-grid correction
+template <class T>
+static bool two_sweeps(Plan& P, int l) {
+    Level& L = P.L[l];
+    return P.nu1 == 2 && P.nu2 == 2 && L.periodic && two_sweeps_ok(L.lay) && p2lev(L) && bufs<T>(L).us;
+}
+template <class T>
+static void sweep_twice(Plan& P, int l, const T* in, T* out, int mode, const T* pu, hipStream_t st) {
+    Level& L = P.L[l];
+    B<T> b = bufs<T>(L);
+    KEvents ev(l == 0);
+    launch_two_sweeps<T>(in, b.f, out, L.lay, L.h, mode, pu, b.uold, st, ev.a, ev.b);
+    ev.done(2.5 * (double)L.d.cells() * sizeof(T));   // one colour and f in, both colours out
+}
+
 template <class T>
 static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) {
     Level& L = P.L[l];
@@ -444,11 +473,15 @@ static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) 
         launch_level_post<T>(b.ua, b.fa, q.u, b.uold, b.u, L.d.x, L.h, P.nu2, st);
         return;
     }
-    const bool filled = smooth<T>(P, l, P.nu1, st, skip_first_red);  // step 2
+    const bool twice = two_sweeps<T>(P, l);
+    T* u1 = twice ? b.us : b.u;   // where the pre-smoothed u is
+    bool filled = false;
+    if (twice) sweep_twice<T>(P, l, b.u, b.us, skip_first_red ? kSweepRed : kSweepPlain, nullptr, st);   // step 2
+    else filled = smooth<T>(P, l, P.nu1, st, skip_first_red);
     if (!L.periodic) ghosts<T>(P, l, st, filled ? 2 : 0);
     // steps 3-5, then step 6 on the covered region of the parent (a fused parent does its own)
     const bool p2 = p2lev(L);
-    if (p2) launch_resid_restrict_p2<T>(b.u, b.f, L.d.x, L.h, q.u, q.f, b.uold, st);
+    if (p2) launch_resid_restrict_p2<T>(u1, b.f, L.d.x, L.h, q.u, q.f, b.uold, st);
     else launch_resid_restrict<T>(b.u, b.f, L.periodic ? nullptr : b.g, L.lay, L.h, q.u, q.f, b.uold, L.pm, st);
     if (!fused<T>(P, l + 1)) {
         if (p2 && Q.lay.pow2 && Q.lay.split && rbgs_vec_ok(Q.lay, sizeof(T))) launch_fas_vec<T>(q.u, q.f, Q.d.x, Q.h, st);
@@ -456,6 +489,10 @@ static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) 
         else launch_fas_rhs<T>(q.u, q.f, L.pm, Dims{L.d.x / 2, L.d.y / 2, L.d.z / 2}, Q.h, st);
     }
     vcycle<T>(P, l + 1, st);                         // step 7
+    if (twice) {
+        sweep_twice<T>(P, l, b.us, b.u, kSweepCorr, q.u, st);   // steps 8-9
+        return;
+    }
     // black cells only where nothing reads the red ones before the red half-sweep rewrites them:
     // a patch's ghost fill reads both colours of its first two layers
     // step 8: on power-of-two levels the black correction is applied by the first red half-sweep
@@ -628,7 +665,7 @@ static std::string plan_key(const Plan& P, const void* ws) {
         std::memcpy(&hb, &L.h, sizeof(hb));
         k += "|" + std::to_string(L.d.x) + "," + std::to_string(L.d.y) + "," + std::to_string(L.d.z) + "," +
              std::to_string(L.pm.off[0]) + "," + std::to_string(L.pm.off[1]) + "," + std::to_string(L.pm.off[2]) +
-             "," + std::to_string(hb) + "," + std::to_string((int)L.fusable);
+             "," + std::to_string(hb) + "," + std::to_string((int)L.fusable) + (L.us || L.us32 ? "s" : "");
         if (L.u && L.u == L.u_user) k += "," + std::to_string((uintptr_t)L.u_user);
     }
     return k;
