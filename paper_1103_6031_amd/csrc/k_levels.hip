@@ -452,9 +452,9 @@ k_rbgs_vec_corr(T* __restrict__ u, const T* __restrict__ f, int lgx, int lgy, in
     // one along y, so three correction runs cover all five
     const unsigned X = x >> 1, Y = y >> 1;
     T dO[W], dX[W], dY[W];
-    corr_delta<T>(pu, uold, lc, X, Y, j0, dO);
-    corr_delta<T>(pu, uold, lc, ((x & 1u) ? xp : xm) >> 1, Y, j0, dX);
-    corr_delta<T>(pu, uold, lc, X, ((y & 1u) ? yp : ym) >> 1, j0, dY);
+    corr_delta<T>(pu, uold, 1 << lc, X, Y, j0, dO);
+    corr_delta<T>(pu, uold, 1 << lc, ((x & 1u) ? xp : xm) >> 1, Y, j0, dX);
+    corr_delta<T>(pu, uold, 1 << lc, X, ((y & 1u) ? yp : ym) >> 1, j0, dY);
     auto run = [&](unsigned xr, unsigned yr, const T* d, T* c) {
         const V v = *(const V*)(u + (((xr << lgy) | yr) << lgz) + nzh + j0);
 #pragma unroll

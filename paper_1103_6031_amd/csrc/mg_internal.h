@@ -232,14 +232,22 @@ void launch_rbgs_vec_corr(T* u, const T* f, const Lay& L, double h, const T* pu,
 template <class T>
 void launch_rbgs_vec(T* u, const T* f, const Lay& L, double h, int colour, hipStream_t st, hipEvent_t ev0,
                      hipEvent_t ev1);
-// two red-black sweeps of a periodic colour-split power-of-two cube (two_sweeps_ok) in one launch, u -> out
-// (another array); mode kSweepCorr adds the correction pu - uold to u's black cells first, kSweepRed
-// starts from u's red cells, the first red half-sweep done; same bits as the one-step launches
+// two red-black sweeps of a periodic colour-split cube (two_sweeps_ok) in one launch, u -> out (another
+// array); mode kSweepCorr adds the correction pu - uold to u's black cells first, kSweepRed starts from
+// u's red cells, the first red half-sweep done; same bits as the one-step launches.  sh: a block's tile,
+// rows x runs of 16 bytes per colour x planes
 enum { kSweepPlain = 0, kSweepCorr = 1, kSweepRed = 2 };
-bool two_sweeps_ok(const Lay& L);
+struct SweepShape {
+    int yr = 0, zr = 0, cx = 0;
+};
+bool two_sweeps_ok(const Lay& L, size_t elem);
+SweepShape sweep_shape(int n, int W, bool many);
+unsigned sweep_blocks(int n, int W, const SweepShape& sh);
+int sweep_cells(const SweepShape& sh);       // runs of a block, halo included
 template <class T>
-void launch_two_sweeps(const T* u, const T* f, T* out, const Lay& L, double h, int mode, const T* pu, const T* uold,
-                       hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+void launch_two_sweeps(const T* u, const T* f, T* out, const Lay& L, double h, int mode, const T* pu,
+                       const T* uold, const SweepShape& sh, hipStream_t st, hipEvent_t ev0 = nullptr,
+                       hipEvent_t ev1 = nullptr);
 template <class T>
 void launch_level_pre(const T* u, const T* f, T* uo, T* fo, T* pu, T* pf, T* uold, int n, double h, int nu1,
                       hipStream_t st);
@@ -339,6 +347,10 @@ __device__ __forceinline__ const BSeg& seg_of(const BSeg* __restrict__ segs, int
     return segs[lo];
 }
 #endif
+// two sweeps of the segments' levels; cells: the largest tile's runs
+template <class T>
+void launch_b_two_sweeps(const BSeg* segs, int nseg, unsigned grid, int cells, const int* active, int mode,
+                         hipStream_t st);
 // per-instance finalize of a batched reduction: *out = w * sum(part[0..cnt)), one block each
 struct BFin {
     const double* part;

@@ -222,11 +222,11 @@ __device__ __forceinline__ void run_prolong_black_vec(T* __restrict__ u, int lg,
 
 // d[k] = pu - uold for the parents (X, Y, j0 + k) of a run of W black cells
 template <class T>
-__device__ __forceinline__ void corr_delta(const T* __restrict__ pu, const T* __restrict__ uold, int lc, unsigned X,
+__device__ __forceinline__ void corr_delta(const T* __restrict__ pu, const T* __restrict__ uold, int nc, unsigned X,
                                            unsigned Y, unsigned j0, T* d) {
     constexpr int W = Vec16<T>::W;
-    const unsigned nch = (1u << lc) >> 1;
-    const unsigned rb = ((X << lc) | Y) << lc;
+    const unsigned nch = (unsigned)nc >> 1;
+    const unsigned rb = (X * (unsigned)nc + Y) * (unsigned)nc;   // nc: the coarse level's edge
     const unsigned he = ((X + Y) & 1u) * nch, ho = nch - he;   // halves holding even / odd Z
     const typename Vec16<T>::type o = *(const typename Vec16<T>::type*)(uold + rb + j0);
     if constexpr (W == 4) {

@@ -80,6 +80,7 @@ struct Level {
     // outer step's second e is free, that
     double* us = nullptr;
     float* us32 = nullptr;
+    SweepShape sweep;   // its tile, chosen at the first use
 };
 
 struct Plan {
@@ -99,7 +100,8 @@ template <class T> struct B { T *u, *f, *g, *uold, *ua, *fa, *us; };
 template <class T> static B<T> bufs(Level& l);
 template <> B<double> bufs<double>(Level& l) { return {l.u, l.f, l.g, l.uold, l.ua, l.fa, l.us}; }
 template <> B<float> bufs<float>(Level& l) {
-    return {l.u32, l.f32, l.g32, l.uold32, l.ua32, l.fa32, l.ealt ? l.ealt : l.us32};
+    // (the finest correction and its second buffer change places at every outer step)
+    return {l.u32, l.f32, l.g32, l.uold32, l.ua32, l.fa32, l.us32 && l.ealt ? l.ealt : l.us32};
 }
 
 static bool odd_ok(int m) { return m == 1 || m == 3 || m == 5 || m == 7; }
@@ -223,14 +225,6 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
                 L.fa = cv.take<double>(c);
             }
         }
-    // the second u of the larger power-of-two periodic levels, for smoothing in one launch
-    if (fuse == kFuseAll)
-        for (int l = 0; l < P.last; ++l) {
-            Level& L = P.L[l];
-            if (!L.periodic || !two_sweeps_ok(L.lay)) continue;
-            if (!P.mixed) L.us = cv.take<double>(L.d.cells());
-            else if (!L.ealt) L.us32 = cv.take<float>(L.d.cells());
-        }
     // the small periodic levels at the bottom, below any fused one, run as one single-workgroup
     // launch (measured: a fused 16^3 level and an 8^3 tail take 28 us per FP32 cycle, a 16^3
     // tail 32 us)
@@ -242,6 +236,20 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
         }
     P.partials = cv.take<double>((size_t)kMaxPartials * (P.nh + 1));
     P.scal = cv.take<double>(S_COUNT);
+    // the second u of the other periodic levels, for smoothing in one launch; a plan that fits the static
+    // scratch array keeps fitting it, without the arrays that do not
+    if (fuse == kFuseAll)
+        for (int l = 0; l < P.last; ++l) {
+            Level& L = P.L[l];
+            const size_t c = L.d.cells(), bytes = c * (P.mixed ? sizeof(float) : sizeof(double)) + 256;
+            if (!L.periodic || L.fusable || c <= kTailMaxCells ||
+                !two_sweeps_ok(L.lay, P.mixed ? sizeof(float) : sizeof(double)))
+                continue;
+            if (P.mixed && L.ealt) L.us32 = L.ealt;
+            else if (cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) continue;
+            else if (P.mixed) L.us32 = cv.take<float>(c);
+            else L.us = cv.take<double>(c);
+        }
     return MG_OK;
 }
 
@@ -427,18 +435,21 @@ static bool p2lev(const Level& L) {
            L.pm.off[0] == 0 && L.pm.off[1] == 0 && L.pm.off[2] == 0;
 }
 
-// level l is smoothed by k_two_sweeps before and after the coarse-grid correction
+// level l is smoothed by k_two_sweeps before and after the coarse-grid correction: faster than half-sweeps on
+// every level above the single-workgroup tail's (figures in k_sweeps.hip)
 template <class T>
 static bool two_sweeps(Plan& P, int l) {
     Level& L = P.L[l];
-    return P.nu1 == 2 && P.nu2 == 2 && L.periodic && two_sweeps_ok(L.lay) && p2lev(L) && bufs<T>(L).us;
+    return P.nu1 == 2 && P.nu2 == 2 && L.periodic && two_sweeps_ok(L.lay, sizeof(T)) && L.pm.off[0] == 0 &&
+           L.pm.off[1] == 0 && L.pm.off[2] == 0 && bufs<T>(L).us;
 }
 template <class T>
 static void sweep_twice(Plan& P, int l, const T* in, T* out, int mode, const T* pu, hipStream_t st) {
     Level& L = P.L[l];
     B<T> b = bufs<T>(L);
+    if (!L.sweep.yr) L.sweep = sweep_shape(L.d.x, (int)(16 / sizeof(T)), false);
     KEvents ev(l == 0);
-    launch_two_sweeps<T>(in, b.f, out, L.lay, L.h, mode, pu, b.uold, st, ev.a, ev.b);
+    launch_two_sweeps<T>(in, b.f, out, L.lay, L.h, mode, pu, b.uold, L.sweep, st, ev.a, ev.b);
     ev.done(2.5 * (double)L.d.cells() * sizeof(T));   // one colour and f in, both colours out
 }
 
@@ -482,7 +493,7 @@ static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) 
     // steps 3-5, then step 6 on the covered region of the parent (a fused parent does its own)
     const bool p2 = p2lev(L);
     if (p2) launch_resid_restrict_p2<T>(u1, b.f, L.d.x, L.h, q.u, q.f, b.uold, st);
-    else launch_resid_restrict<T>(b.u, b.f, L.periodic ? nullptr : b.g, L.lay, L.h, q.u, q.f, b.uold, L.pm, st);
+    else launch_resid_restrict<T>(u1, b.f, L.periodic ? nullptr : b.g, L.lay, L.h, q.u, q.f, b.uold, L.pm, st);
     if (!fused<T>(P, l + 1)) {
         if (p2 && Q.lay.pow2 && Q.lay.split && rbgs_vec_ok(Q.lay, sizeof(T))) launch_fas_vec<T>(q.u, q.f, Q.d.x, Q.h, st);
         else if (p2 && Q.lay.pow2 && Q.lay.split) launch_fas_rhs_p2<T>(q.u, q.f, Q.d.x, Q.h, st);
@@ -1092,7 +1103,7 @@ static int lpt_common(const mg_hier* H, int what, const double* const* phi, void
 struct BLaunch {
     int off = 0, n = 0;      // segments [off, off + n) of the table
     unsigned grid = 0;       // blocks (sum of the segments' nblk)
-    int block = kBlock, V = 1;
+    int block = kBlock, V = 1;   // (two sweeps: block = the largest tile's runs)
 };
 
 struct SmoothShape {
@@ -1111,6 +1122,7 @@ struct BatchPlan {
     std::vector<BSeg> segs;
     std::vector<BLaunch> sm[2][2], rr[2][2], fas[2][2], pr[2][2];   // one-step launches per depth
     std::vector<BLaunch> pre[2][2], post[2][2];                     // fused legs per depth
+    std::vector<BLaunch> sw1[2][2], sw2[2][2];                      // two sweeps in one launch per depth
     BLaunch outer[2], resid;
     std::vector<TailPlan<float>> tpf;
     std::vector<TailPlan<double>> tpd;
@@ -1169,6 +1181,21 @@ template <class T> static T* ubuf(Level& L);
 template <> double* ubuf<double>(Level& L) { return L.u; }
 template <> float* ubuf<float>(Level& L) { return L.u32; }
 
+// the second u of depth d: the finest correction's other buffer, the array reserved for it, or the unused
+// one of the fused legs
+template <class T>
+static T* second_u(Plan& P, int d, const T* u) {
+    Level& L = P.L[d];
+    ::mgic::B<T> b = bufs<T>(L);
+    if constexpr (std::is_same_v<T, float>)
+        if (d == 0) return b.us && u == b.us ? b.u : b.us;
+    return b.us ? b.us : b.ua;
+}
+template <class T>
+static bool b_two_sweeps(Plan& P, int d) {
+    return P.nu1 == 2 && P.nu2 == 2 && two_sweeps_ok(P.L[d].lay, sizeof(T)) && second_u<T>(P, d, bufs<T>(P.L[d]).u);
+}
+
 // the V-cycle tables of precision T (ti = 0 float, 1 double); fine_u replaces level 0's u
 template <class T>
 static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& fine_u,
@@ -1181,8 +1208,11 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
     B.pr[ti][par].assign(B.D, BLaunch{});
     B.pre[ti][par].assign(B.D, BLaunch{});
     B.post[ti][par].assign(B.D, BLaunch{});
+    B.sw1[ti][par].assign(B.D, BLaunch{});
+    B.sw2[ti][par].assign(B.D, BLaunch{});
     for (int d = 0; d < B.D; ++d) {
-        std::vector<BSeg> sm, rr, fa, pr, pre, post;
+        std::vector<BSeg> sm, rr, fa, pr, pre, post, sw1, sw2;
+        int sweep_runs = 0;
         const SmoothShape sh = d < B.D1 ? shape[d] : SmoothShape{};
         for (int i = 0; i < n; ++i) {
             Plan& P = B.P[i];
@@ -1205,18 +1235,34 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
                 post.push_back(s);
                 continue;
             }
-            s = seg0(i, rbgs_split_blocks(L.lay, sh.block, sh.V));
-            s.L = L.lay;
-            s.h = L.h;
-            s.a[0] = u;
-            s.a[1] = b.f;
-            sm.push_back(s);
+            T* u1 = u;   // where the pre-smoothed u is
+            if (b_two_sweeps<T>(P, d)) {
+                u1 = second_u<T>(P, d, u);
+                const int W = (int)(16 / sizeof(T));
+                const SweepShape tile = sweep_shape(L.d.x, W, true);
+                sweep_runs = std::max(sweep_runs, sweep_cells(tile));
+                s = seg0(i, sweep_blocks(L.d.x, W, tile));
+                s.L = L.lay;
+                s.C.d = Dims{tile.yr, tile.zr, tile.cx};
+                s.h = L.h;
+                s.a[0] = u; s.a[1] = b.f; s.a[2] = u1; s.a[3] = q.u; s.a[4] = b.uold;
+                sw1.push_back(s);
+                s.a[0] = u1; s.a[2] = u;
+                sw2.push_back(s);
+            } else {
+                s = seg0(i, rbgs_split_blocks(L.lay, sh.block, sh.V));
+                s.L = L.lay;
+                s.h = L.h;
+                s.a[0] = u;
+                s.a[1] = b.f;
+                sm.push_back(s);
+            }
             s = seg0(i, cdiv(C.d.cells(), kBlock));
             s.L = L.lay;
             s.C = C;
             s.pm = L.pm;
             s.h = L.h;
-            s.a[0] = u; s.a[1] = b.f; s.a[2] = q.u; s.a[3] = q.f; s.a[4] = b.uold;
+            s.a[0] = u1; s.a[1] = b.f; s.a[2] = q.u; s.a[3] = q.f; s.a[4] = b.uold;
             rr.push_back(s);
             if (!fused<T>(P, d + 1)) {   // a fused level does its own step 6
                 s = seg0(i, fas_blocks(C, L.pm, (int)sizeof(T)));
@@ -1226,6 +1272,7 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
                 s.a[0] = q.u; s.a[1] = q.f;
                 fa.push_back(s);
             }
+            if (u1 != u) continue;       // the sweeps add the correction
             s = seg0(i, B.P[i].nu2 > 0 ? prolong_black_blocks(L.lay, L.pm, (int)sizeof(T)) : cdiv(cells, kBlock));
             s.L = L.lay;
             s.pm = L.pm;
@@ -1238,6 +1285,8 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
         B.pr[ti][par][d] = add_launch(tab, pr);
         B.pre[ti][par][d] = add_launch(tab, pre);
         B.post[ti][par][d] = add_launch(tab, post);
+        B.sw1[ti][par][d] = add_launch(tab, sw1, sweep_runs);
+        B.sw2[ti][par][d] = add_launch(tab, sw2, sweep_runs);
     }
 }
 
@@ -1329,8 +1378,12 @@ static size_t batch_layout(int ninst, const int* n, const double* h, const mg_op
 static std::mutex g_tune_mu;
 static std::map<std::string, std::vector<SmoothShape>> g_tune;
 
-static std::string batch_key(const BatchPlan& B, int ti) {
-    std::string k = std::to_string(ti) + ":" + std::to_string(B.P.empty() ? 0 : B.P[0].nu1) + ":";
+// (an "s" marks plans with depths smoothed by two sweeps in one launch, which have nothing to tune)
+static std::string batch_key(BatchPlan& B, int ti) {
+    bool swept = false;
+    for (auto& P : B.P)
+        for (int d = 0; d < P.tail; ++d) swept = swept || (ti ? b_two_sweeps<double>(P, d) : b_two_sweeps<float>(P, d));
+    std::string k = (swept ? "s" : "") + std::to_string(ti) + ":" + std::to_string(B.P.empty() ? 0 : B.P[0].nu1) + ":";
     for (auto& P : B.P) k += std::to_string(P.L[0].d.x) + ",";
     return k;
 }
@@ -1470,7 +1523,7 @@ static int tune_smoother(BatchPlan& B, int ti, hipStream_t st, std::vector<Smoot
             std::vector<BSeg> tab, segs;
             for (int i = 0; i < n; ++i) {
                 Plan& P = B.P[i];
-                if (d >= P.tail || fused<T>(P, d)) continue;
+                if (d >= P.tail || fused<T>(P, d) || b_two_sweeps<T>(P, d)) continue;
                 Level& L = P.L[d];
                 BSeg s = seg0(i, rbgs_split_blocks(L.lay, sh.block, sh.V));
                 s.L = L.lay;
@@ -1479,6 +1532,7 @@ static int tune_smoother(BatchPlan& B, int ti, hipStream_t st, std::vector<Smoot
                 s.a[1] = bufs<T>(L).f;
                 segs.push_back(s);
             }
+            if (segs.empty()) break;   // nothing at this depth is smoothed by half-sweeps
             BLaunch la = add_launch(tab, segs, sh.block, sh.V);
             MG_HIP(hipMemcpyAsync(B.segs_dev, tab.data(), tab.size() * sizeof(BSeg), hipMemcpyHostToDevice, st));
             for (int r = 0; r < 2; ++r)
@@ -1533,6 +1587,10 @@ static void b_vcycle(BatchPlan& B, int ti, int par, bool skip_first_red, hipStre
         const BLaunch& pre = B.pre[ti][par][d];
         if (pre.n) launch_b_level_pre<T>(sd + pre.off, pre.n, pre.grid, act, B.P[0].nu1, st);
         const BLaunch& sm = B.sm[ti][par][d];
+        const BLaunch& sw = B.sw1[ti][par][d];
+        if (sw.n)
+            launch_b_two_sweeps<T>(sd + sw.off, sw.n, sw.grid, sw.block, act,
+                                   skip_first_red && d == 0 ? kSweepRed : kSweepPlain, st);
         for (int s = 0; s < B.P[0].nu1; ++s)
             for (int c = 0; c < 2; ++c) {
                 if (skip_first_red && d == 0 && s == 0 && c == 0) continue;
@@ -1548,6 +1606,8 @@ static void b_vcycle(BatchPlan& B, int ti, int par, bool skip_first_red, hipStre
     for (int d = B.D - 1; d >= 0; --d) {
         const BLaunch& post = B.post[ti][par][d];
         if (post.n) launch_b_level_post<T>(sd + post.off, post.n, post.grid, act, B.P[0].nu2, st);
+        const BLaunch& sw = B.sw2[ti][par][d];
+        if (sw.n) launch_b_two_sweeps<T>(sd + sw.off, sw.n, sw.grid, sw.block, act, kSweepCorr, st);
         const BLaunch& pr = B.pr[ti][par][d];
         if (pr.n) launch_b_prolong<T>(sd + pr.off, pr.n, pr.grid, act, B.P[0].nu2 > 0, st);
         const BLaunch& sm = B.sm[ti][par][d];
