@@ -21,7 +21,7 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function",
 ]
-SOURCES = ["k_multigrid.hip", "k_levels.hip", "k_sweeps.hip", "k_lpt.hip", "k_highorder.hip", "k_fft.hip", "k_density.hip",
+SOURCES = ["k_multigrid.hip", "k_levels.hip", "k_sweeps.hip", "k_patch.hip", "k_lpt.hip", "k_highorder.hip", "k_fft.hip", "k_density.hip",
            "solver.cpp", "spectral.cpp", "density.cpp", "batch_hier.cpp"]
 
 

@@ -20,12 +20,12 @@
 
 #include <algorithm>
 
+#include "ghost_bodies.h"
 #include "mg_internal.h"
 #include "p2_bodies.h"
 
 namespace mgic {
 
-__device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 
 // ((x- + x+) + (y- + y+)) + (z- + z+) on a periodic level in any layout
@@ -58,18 +58,6 @@ __device__ __forceinline__ T nsum(const T* __restrict__ u, const T* __restrict__
     if constexpr (GH) return nsum_ghost<T>(u, g, L, x, y, z);
     else return nsum_periodic<T>(u, L.d, L.split, x, y, z);
 }
-
-// index of covered cell (X,Y,Z) (relative to the covered box) in the parent array
-__device__ __forceinline__ size_t pidx(const ParentMap& pm, int X, int Y, int Z) {
-    int a = pm.off[0] + X, b = pm.off[1] + Y, c = pm.off[2] + Z;
-    if (pm.periodic) {
-        a = wrap(a, pm.pl.d.x);
-        b = wrap(b, pm.pl.d.y);
-        c = wrap(c, pm.pl.d.z);
-    }
-    return lidx(pm.pl.d, pm.pl.split, a, b, c);
-}
-
 
 // Reduction kernels stride over the whole array, kRedV independent cells per thread per pass;
 // blk / nblk are the block's index and the block count of its array (the grid of a plain launch,
@@ -914,22 +902,6 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_p2(TailPlan<T> tp) {
     body_tail_p2<T>(tp);
 }
 
-// ----------------------------------------------------------------------------------------------
-// coarse-fine ghost zones with flux matching (Section 3.3, Table 2 order-1 flux), computed per 2x2
-// group of fine face cells sharing a parent C.  For the low-x face and fine cell (0, j, k):
-//   a  = quadratic interpolation in the outside parent layer at the child's transverse position
-//   g0 = 8/15 a + 2/3 u0 - 1/5 u1            (quadratic normal to the face)
-//   g  = g0 + (mean u0 - mean g0) - 1/2 (mean8(children of C) - U[O])
-// so the mean fine flux (u0 - g)/h through the coarse face equals the coarse flux (C - O)/(2h),
-// with C taken as the live mean of its children.  Other faces mirror this.
-// ----------------------------------------------------------------------------------------------
-
-__device__ __forceinline__ void w2(double t, double w[3]) {
-    w[0] = 0.5 * t * (t - 1.0);
-    w[1] = 1.0 - t * t;
-    w[2] = 0.5 * t * (t + 1.0);
-}
-
 // The ghost value of lane q = 2 jb + kc (jb, kc in {0, 1}) of group (J, K) on face `face` of a
 // patch: the group is the 2 x 2 fine ghost cells in front of parent cell (J, K) of the face (J
 // along axis b, K along axis c; a is the normal).  Each lane forms its own g0; the group means
@@ -963,31 +935,13 @@ __device__ __forceinline__ double ghost_lane(const T* __restrict__ pu, const T* 
         aq = pa.x;
         O = pa.y;
     } else {
-        const int on = side ? pm.off[a] + n[a] / 2 : pm.off[a] - 1;
-        const int pdim[3] = {pm.pl.d.x, pm.pl.d.y, pm.pl.d.z};
-        // 3x3 outside coarse layer around O
         double L[3][3];
-        for (int db = 0; db < 3; ++db)
-            for (int dc = 0; dc < 3; ++dc) {
-                int qq[3];
-                qq[a] = on;
-                qq[b] = pm.off[b] + J + db - 1;
-                qq[c] = pm.off[c] + K + dc - 1;
-                if (pm.periodic)
-                    for (int k = 0; k < 3; ++k) qq[k] = wrap(qq[k], pdim[k]);
-                L[db][dc] = (double)pu[lidx(pm.pl.d, pm.pl.split, qq[0], qq[1], qq[2])];
-            }
-        double wb[3], wc[3];
-        w2(jb ? 0.25 : -0.25, wb);
-        w2(kc ? 0.25 : -0.25, wc);
-        // parallel to the face: first along b (for each of the 3 c-columns), then along c
-        double Ab[3];
-        for (int dc = 0; dc < 3; ++dc) Ab[dc] = (wb[0] * L[0][dc] + wb[1] * L[1][dc]) + wb[2] * L[2][dc];
-        aq = (wc[0] * Ab[0] + wc[1] * Ab[1]) + wc[2] * Ab[2];
+        ghost_parent(pu, pm, d, face, J, K, L);
+        aq = ghost_interp(L, jb, kc);
         O = L[1][1];
         if constexpr (MODE == 1) pa = make_double2(aq, O);
     }
-    const double g0 = ((8.0 / 15.0) * aq + (2.0 / 3.0) * u0) - 0.2 * u1;
+    const double g0 = ghost_g0(aq, u0, u1);
     double shift = 0.0;
     if (flux_match) {
         const int base = (int)(threadIdx.x & 63) & ~3;
@@ -997,8 +951,7 @@ __device__ __forceinline__ double ghost_lane(const T* __restrict__ pu, const T* 
             return ((v0 + v1) + (v2 + v3)) * 0.25;
         };
         const double m_u0 = mean4(u0), m_u1 = mean4(u1), m_g0 = mean4(g0);
-        const double uC = 0.5 * (m_u0 + m_u1);
-        shift = (m_u0 - m_g0) - 0.5 * (uC - O);
+        shift = ghost_shift(m_u0, m_u1, m_g0, O);
     }
     return g0 + shift;
 }

@@ -248,6 +248,14 @@ template <class T>
 void launch_two_sweeps(const T* u, const T* f, T* out, const Lay& L, double h, int mode, const T* pu,
                        const T* uold, const SweepShape& sh, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
+// two red-black sweeps of a patch (patch_sweeps_ok) with its ghost zones, u -> out (another array); corr
+// adds the correction pu - uold to u first, otherwise the ghosts of the result are written; same bits as
+// ghost fills and half-sweeps one by one
+bool patch_sweeps_ok(const Lay& L, size_t elem);
+template <class T>
+void launch_patch_sweeps(const T* u, const T* f, T* out, T* ghosts, const Lay& L, double h, bool corr, const T* pu,
+                         const T* uold, const ParentMap& pm, hipStream_t st, hipEvent_t ev0 = nullptr,
+                         hipEvent_t ev1 = nullptr);
 template <class T>
 void launch_level_pre(const T* u, const T* f, T* uo, T* fo, T* pu, T* pf, T* uold, int n, double h, int nu1,
                       hipStream_t st);

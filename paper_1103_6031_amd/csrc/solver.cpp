@@ -236,14 +236,14 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
         }
     P.partials = cv.take<double>((size_t)kMaxPartials * (P.nh + 1));
     P.scal = cv.take<double>(S_COUNT);
-    // the second u of the other periodic levels, for smoothing in one launch; a plan that fits the static
+    // the second u of patches and the other periodic levels, for smoothing in one launch; a plan that fits the static
     // scratch array keeps fitting it, without the arrays that do not
     if (fuse == kFuseAll)
         for (int l = 0; l < P.last; ++l) {
             Level& L = P.L[l];
-            const size_t c = L.d.cells(), bytes = c * (P.mixed ? sizeof(float) : sizeof(double)) + 256;
-            if (!L.periodic || L.fusable || c <= kTailMaxCells ||
-                !two_sweeps_ok(L.lay, P.mixed ? sizeof(float) : sizeof(double)))
+            const size_t elem = P.mixed ? sizeof(float) : sizeof(double);
+            const size_t c = L.d.cells(), bytes = c * elem + 256;
+            if (L.periodic ? L.fusable || c <= kTailMaxCells || !two_sweeps_ok(L.lay, elem) : !patch_sweeps_ok(L.lay, elem))
                 continue;
             if (P.mixed && L.ealt) L.us32 = L.ealt;
             else if (cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) continue;
@@ -453,6 +453,21 @@ static void sweep_twice(Plan& P, int l, const T* in, T* out, int mode, const T* 
     ev.done(2.5 * (double)L.d.cells() * sizeof(T));   // one colour and f in, both colours out
 }
 
+// patch l is smoothed by k_patch_sweeps
+template <class T>
+static bool patch_sweeps(Plan& P, int l) {
+    Level& L = P.L[l];
+    return P.nu1 == 2 && P.nu2 == 2 && !L.periodic && patch_sweeps_ok(L.lay, sizeof(T)) && bufs<T>(L).us;
+}
+template <class T>
+static void sweep_patch(Plan& P, int l, const T* in, T* out, bool corr, hipStream_t st) {
+    Level& L = P.L[l];
+    B<T> b = bufs<T>(L);
+    KEvents ev(l == 0);
+    launch_patch_sweeps<T>(in, b.f, out, b.g, L.lay, L.h, corr, bufs<T>(P.L[l + 1]).u, b.uold, L.pm, st, ev.a, ev.b);
+    ev.done(3.0 * (double)L.d.cells() * sizeof(T));   // u and f in, u out
+}
+
 template <class T>
 static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) {
     Level& L = P.L[l];
@@ -484,12 +499,13 @@ static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) 
         launch_level_post<T>(b.ua, b.fa, q.u, b.uold, b.u, L.d.x, L.h, P.nu2, st);
         return;
     }
-    const bool twice = two_sweeps<T>(P, l);
-    T* u1 = twice ? b.us : b.u;   // where the pre-smoothed u is
+    const bool twice = two_sweeps<T>(P, l), patch = patch_sweeps<T>(P, l);
+    T* u1 = twice || patch ? b.us : b.u;   // where the pre-smoothed u is
     bool filled = false;
     if (twice) sweep_twice<T>(P, l, b.u, b.us, skip_first_red ? kSweepRed : kSweepPlain, nullptr, st);   // step 2
+    else if (patch) sweep_patch<T>(P, l, b.u, b.us, false, st);
     else filled = smooth<T>(P, l, P.nu1, st, skip_first_red);
-    if (!L.periodic) ghosts<T>(P, l, st, filled ? 2 : 0);
+    if (!L.periodic && !patch) ghosts<T>(P, l, st, filled ? 2 : 0);
     // steps 3-5, then step 6 on the covered region of the parent (a fused parent does its own)
     const bool p2 = p2lev(L);
     if (p2) launch_resid_restrict_p2<T>(u1, b.f, L.d.x, L.h, q.u, q.f, b.uold, st);
@@ -502,6 +518,10 @@ static void vcycle(Plan& P, int l, hipStream_t st, bool skip_first_red = false) 
     vcycle<T>(P, l + 1, st);                         // step 7
     if (twice) {
         sweep_twice<T>(P, l, b.us, b.u, kSweepCorr, q.u, st);   // steps 8-9
+        return;
+    }
+    if (patch) {
+        sweep_patch<T>(P, l, b.us, b.u, true, st);              // steps 8-9
         return;
     }
     // black cells only where nothing reads the red ones before the red half-sweep rewrites them:
