@@ -16,7 +16,9 @@
 // separate kernels.  The FP64 arithmetic is the oracle's up to summation order.
 
 #include <algorithm>
+#include <type_traits>
 
+#include "div6.h"
 #include "mg_internal.h"
 
 namespace mgic {
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void k_ho_half(const T* __restrict__ in, T*
     const unsigned t0 = 2 * p, m = (1u << lg) - 1, z0 = t0 & m, y = (t0 >> lg) & m, x = t0 >> (2 * lg);
     const unsigned q = (x + y + (unsigned)colour) & 1u;   // (x + y + z0 + q) & 1 == colour
     const v2_t<T> cur = *(const v2_t<T>*)(in + t0);
-    const T v = (h2 * f[t0 + q] - ho_off<R>(in, x, y, z0 + q, lg, m)) / ((T)3 * (T)HoW<R>::w0);
+    const T v = div_const(h2 * f[t0 + q] - ho_off<R>(in, x, y, z0 + q, lg, m), (T)3 * (T)HoW<R>::w0);
     *(v2_t<T>*)(out + t0) = q ? mk2<T>(cur.x, v) : mk2<T>(v, cur.y);
 }
 
@@ -163,8 +165,133 @@ __global__ __launch_bounds__(kBlock) void k_ho_half_lds(const T* __restrict__ in
             acc += (T)ho_w<R>(s) * ((px + py) + pz_);
         }
         const v2_t<T> cur = *(const v2_t<T>*)(row + z0);
-        const T v = (h2 * f[ho_idx(x, y, z, lg)] - acc) / ((T)3 * (T)HoW<R>::w0);
+        const T v = div_const(h2 * f[ho_idx(x, y, z, lg)] - acc, (T)3 * (T)HoW<R>::w0);
         *(v2_t<T>*)(out + ho_idx(x, y, z0, lg)) = q ? mk2<T>(cur.x, v) : mk2<T>(v, cur.y);
+    }
+}
+
+// A red-black sweep (both half-sweeps) in one launch.  As two launches it moves 6 words per cell (each
+// half-sweep reads u and f and writes u); here u and f are read and u is written once.  A block takes
+// tl.yr rows x tl.zp pairs of z-neighbours and marches over tl.cx planes, with a halo of 2R rows and
+// cells on each side: the red half-sweep works on plane p, the black one R planes behind.  A thread
+// owns a pair, one cell of each colour, in one row and keeps the planes around both half-sweeps in
+// registers, by colour (rings, the slots constant in the unrolled steps): a neighbour s away along an
+// axis has the other colour for odd s, the own one for even s, so no value is selected by parity.
+// The x-neighbours are the thread's own; y and z come from LDS, by colour too, where every thread
+// leaves its values for the next step (two buffers, one barrier per step).  Halo values that depend
+// on cells outside the tile are wrong and never stored.  The operations are those of k_ho_half in
+// their order, so the bits are the same.
+//
+// Bound: HBM at 512^3 (3 words per cell at 3.8 TB/s), the recomputed halos and the latency of a step below.
+// Measured (MI355X) against two half-sweeps, FP64 / FP32: order 4 512^3 1747 -> 891 us, 256^3 180 -> 104 / 73 -> 41,
+// 128^3 22 -> 14 / 15 -> 10, 64^3 7.0 -> 6.5 / 6.1 -> 5.5; order 6 256^3 208 -> 108 / 89 -> 50, 128^3 25 -> 18 /
+// 18 -> 14, 64^3 7.4 -> 8.3; order 2 256^3 158 -> 77 / 66 -> 39, 64^3 6.8 -> 4.7.  Hence order 6 from 128^3, the
+// others from 32^3.  (With the pairs kept as read, a select by parity for each neighbour: order 6 256^3 135 us.)
+struct HoTile { int yr, zp, cx; };   // rows, pairs, planes: powers of two
+
+constexpr int ho_sweep_threads(int R, size_t elem) { return R >= 2 && elem == 8 ? 768 : 1024; }
+
+template <int R, class T>
+__global__ void __launch_bounds__((ho_sweep_threads(R, sizeof(T))))
+k_ho_sweep(const T* __restrict__ in, T* __restrict__ out, const T* __restrict__ f, int lg, T h2, HoTile tl) {
+    using V = v2_t<T>;
+    constexpr int L = R == 1 ? 4 : (R == 2 ? 8 : 10);   // ring: planes p - R - 2 .. p + R
+    extern __shared__ __align__(16) unsigned char ho_smem[];
+    const int n = 1 << lg, m = n - 1;
+    const int NP = tl.zp + 2 * R, ny = tl.yr + 4 * R, cells = ny * NP;
+    if ((int)(threadIdx.x & ~63u) >= cells) return;     // waves without a pair
+    // each XCD takes a contiguous run of tiles, so that the halos of neighbours are in its own L2
+    const unsigned b = (blockIdx.x % 8) * (gridDim.x / 8) + min(blockIdx.x % 8, gridDim.x % 8) + blockIdx.x / 8;
+    const int ntz = (n >> 1) / tl.zp, nty = n / tl.yr;
+    const int zt = (int)(b % (unsigned)ntz), bt = (int)(b / (unsigned)ntz);
+    const int y0 = (bt % nty) * tl.yr, x0 = (bt / nty) * tl.cx;
+    const int t = min((int)threadIdx.x, cells - 1), r = t / NP, k = t - r * NP;
+    const bool live = (int)threadIdx.x < cells;
+    const bool mine = live && r >= 2 * R && r < 2 * R + tl.yr && k >= R && k < R + tl.zp;
+    const int y = (y0 + r - 2 * R) & m, z0 = 2 * (zt * tl.zp + k - R) & m;
+    const unsigned at = ((unsigned)(y << lg) | (unsigned)z0) * (unsigned)sizeof(T);
+    // per buffer the red and black values of the red half-sweep's plane, then of the black one's; R more
+    // rows of padding on each side
+    const int size = (ny + 2 * R) * NP;
+    T* own = (T*)ho_smem + (r + R) * NP + k;
+    auto plane = [&](auto* p, int x) { return (char*)(p + ((size_t)(unsigned)(x & m) << (2 * lg))); };
+    auto load = [&](const T* p, int x) { return *(const V*)(plane(const_cast<T*>(p), x) + at); };
+    auto split = [&](const V& v, int x, T& red, T& black) {
+        const bool q = (x + y) & 1;                     // the red cell is the pair's second one
+        red = q ? v.y : v.x;
+        black = q ? v.x : v.y;
+    };
+    const int first = x0 - R, steps = tl.cx + 2 * R;    // step s: red of plane first + s
+    T red[L], blk[L], upd[L], fb[L];                // before the sweep; updated red; f.  Plane first + d: d mod L
+#pragma unroll
+    for (int i = 0; i < L; ++i) red[i] = blk[i] = upd[i] = fb[i] = (T)0;
+#pragma unroll
+    for (int d = -R; d < R; ++d) split(load(in, first + d), first + d, red[(d + L) % L], blk[(d + L) % L]);
+    V nu = load(in, first + R), nf = load(f, first);    // loaded a step ahead of their use
+    own[0] = red[0];
+    own[size] = blk[0];
+    own[2 * size] = own[3 * size] = (T)0;
+    __syncthreads();
+    // the new value of a cell from rings and LDS of the other colour (O, lo) and its own (S, ls); ctr: the
+    // plane's slot, q: the cell is the pair's second one
+    auto update = [&](const T* O, const T* S, const T* lo, const T* ls, int ctr, T fv, bool q) {
+        T acc = 0;
+#pragma unroll
+        for (int s = 1; s <= R; ++s) {
+            const T *D = s & 1 ? O : S, *l = s & 1 ? lo : ls;
+            const T px = D[(ctr - s + L) % L] + D[(ctr + s) % L];
+            const T py = l[-s * NP] + l[s * NP];
+            T pz;
+            if (s == 1) pz = O[ctr] + (q ? lo + 1 : lo - 1)[0];
+            else if (s == 2) pz = ls[-1] + ls[1];
+            else pz = (q ? lo + 1 : lo)[-2] + (q ? lo + 1 : lo)[1];
+            acc += (T)ho_w<R>(s) * ((px + py) + pz);
+        }
+        return div_const(h2 * fv - acc, (T)3 * (T)HoW<R>::w0);
+    };
+    auto step = [&](int s, auto phase) __attribute__((always_inline)) {
+        constexpr int P = decltype(phase)::value;       // s mod L
+        constexpr int C = (P + L - R) % L, N = (P + R) % L;   // the black half-sweep's plane; the newest one
+        T* rd = own + (P & 1 ? 4 * size : 0);
+        T* wr = own + (P & 1 ? 0 : 4 * size);
+        const int p = first + s;
+        const bool more = s + 1 < steps, q = (p + y) & 1;
+        T fr;
+        split(nu, p + R, red[N], blk[N]);
+        split(nf, p, fr, fb[P]);
+        if (more) {
+            nu = load(in, p + R + 1);
+            nf = load(f, p + 1);
+        }
+        upd[P] = update(blk, red, rd + size, rd, P, fr, q);
+        if (p - R >= x0) {
+            const bool qb = (p - R + y + 1) & 1;
+            const T w = update(upd, blk, rd + 2 * size, rd + 3 * size, C, fb[C], qb);
+            if (mine) *(V*)(plane(out, p - R) + at) = qb ? mk2<T>(upd[C], w) : mk2<T>(w, upd[C]);
+        }
+        if (live) {
+            if constexpr (R > 1) wr[0] = red[(P + 1) % L];
+            wr[size] = blk[(P + 1) % L];
+            wr[2 * size] = upd[(C + 1) % L];
+            if constexpr (R > 1) wr[3 * size] = blk[(C + 1) % L];
+        }
+        __syncthreads();
+    };
+    for (int s = 0; s < steps; s += L) {
+        step(s, std::integral_constant<int, 0>{});
+        if (s + 1 < steps) step(s + 1, std::integral_constant<int, 1>{});
+        if (s + 2 < steps) step(s + 2, std::integral_constant<int, 2>{});
+        if (s + 3 < steps) step(s + 3, std::integral_constant<int, 3>{});
+        if constexpr (L > 4) {
+            if (s + 4 < steps) step(s + 4, std::integral_constant<int, 4>{});
+            if (s + 5 < steps) step(s + 5, std::integral_constant<int, 5>{});
+            if (s + 6 < steps) step(s + 6, std::integral_constant<int, 6>{});
+            if (s + 7 < steps) step(s + 7, std::integral_constant<int, 7>{});
+        }
+        if constexpr (L > 8) {
+            if (s + 8 < steps) step(s + 8, std::integral_constant<int, 8>{});
+            if (s + 9 < steps) step(s + 9, std::integral_constant<int, 9>{});
+        }
     }
 }
 
@@ -400,7 +527,7 @@ __global__ __launch_bounds__(kHoTailThreads) void k_ho_tail(T* __restrict__ u, c
                 if (t0 < 2 * pairs) {
                     const unsigned z0 = t0 & m, y = (t0 >> lg) & m, x = t0 >> (2 * lg);
                     const unsigned q = (x + y + (unsigned)(c & 1)) & 1u;
-                    v[k] = (h2 * F[t0 + q] - ho_off<R>(U, x, y, z0 + q, lg, m)) / ((T)3 * (T)HoW<R>::w0);
+                    v[k] = div_const(h2 * F[t0 + q] - ho_off<R>(U, x, y, z0 + q, lg, m), (T)3 * (T)HoW<R>::w0);
                 }
             }
             __syncthreads();
@@ -645,6 +772,58 @@ void launch_ho_half(const T* in, T* out, const T* f, int lg, double h, int order
 }
 
 template <class T>
+static unsigned ho_sweep_lds(const HoTile& tl, int R) {
+    return 8u * (unsigned)((tl.yr + 6 * R) * (tl.zp + 2 * R)) * (unsigned)sizeof(T);
+}
+
+template <class T>
+static void launch_ho_sweep_tile(const T* in, T* out, const T* f, int lg, double h, int order, const HoTile& tl,
+                                 hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
+    const int R = order / 2, n = 1 << lg;
+    const unsigned grid = (unsigned)((n / tl.yr) * (n / (2 * tl.zp)) * (n / tl.cx)), lds = ho_sweep_lds<T>(tl, R);
+    const unsigned block = (unsigned)((tl.yr + 4 * R) * (tl.zp + 2 * R) + 63) / 64 * 64;
+    if (ea) (void)hipEventRecord(ea, st);
+    auto run = [&](auto kernel) { kernel<<<grid, block, lds, st>>>(in, out, f, lg, (T)(h * h), tl); };
+    if (R == 1) run(k_ho_sweep<1, T>);
+    else if (R == 2) run(k_ho_sweep<2, T>);
+    else run(k_ho_sweep<3, T>);
+    if (eb) (void)hipEventRecord(eb, st);
+}
+
+// The tile: the least of rounds x steps x time of a step (2.2 + the waves per SIMD), blocks sharing 256 CUs
+// of `most` threads each; within 6 % of the fastest shape measured from 32^3 to 512^3, orders 2 to 6.
+template <class T>
+static HoTile ho_sweep_tile(int lg, int order) {
+    HoTile best{};
+    const int R = order / 2, n = 1 << lg, most = ho_sweep_threads(R, sizeof(T));
+    double least = 1e30;
+    for (int zp = 4; zp <= 32 && 2 * zp <= n; zp *= 2)
+        for (int yr = 8; yr <= 32 && yr <= n; yr *= 2) {
+            const int cells = (yr + 4 * R) * (zp + 2 * R);
+            if (cells > most || ho_sweep_lds<T>(HoTile{yr, zp, 0}, R) > 65536) continue;
+            const int waves = (cells + 63) / 64, fit = most / 64 / waves;
+            for (int cx = 4; cx <= n; cx *= 2) {
+                const int blocks = (n / yr) * (n / (2 * zp)) * (n / cx), q = (blocks + 255) / 256;
+                const int m = std::min(q, fit);
+                const double cost = (double)((q + fit - 1) / fit) * (cx + 2 * R) * (2.2 + (m * waves + 3) / 4);
+                if (cost <= least) {   // of equals the one with the longer rows
+                    least = cost;
+                    best = HoTile{yr, zp, cx};
+                }
+            }
+        }
+    return best;
+}
+
+bool ho_sweep_ok(int lg, int order) { return lg >= (order == 6 ? 7 : 5); }
+
+template <class T>
+void launch_ho_sweep(const T* in, T* out, const T* f, int lg, double h, int order, hipStream_t st, hipEvent_t ea,
+                     hipEvent_t eb) {
+    launch_ho_sweep_tile<T>(in, out, f, lg, h, order, ho_sweep_tile<T>(lg, order), st, ea, eb);
+}
+
+template <class T>
 void launch_ho_resid_restrict(const T* u, const T* f, T* uc, T* uold, T* rc, int lgc, double h, int order,
                               hipStream_t st) {
     if (lgc >= 3 && lgc <= 7) {   // fine 16^3 .. 256^3: rows staged in LDS
@@ -696,6 +875,7 @@ hipError_t launch_ho_tail(T* u, const T* f, int lg, double h, int order, int nu1
 }
 
 #define HO_INST(T)                                                                                          \
+    template void launch_ho_sweep<T>(const T*, T*, const T*, int, double, int, hipStream_t, hipEvent_t, hipEvent_t); \
     template void launch_ho_half<T>(const T*, T*, const T*, int, double, int, int, hipStream_t, hipEvent_t,    \
                                     hipEvent_t);                                                            \
     template void launch_ho_resid_restrict<T>(const T*, const T*, T*, T*, T*, int, double, int, hipStream_t); \
@@ -1040,7 +1220,7 @@ __global__ __launch_bounds__(kBlock) void k_hoz_half(const double* __restrict__ 
     } else {
         acc = hoz_off<R>(in, g, P.n, (int)x, (int)y, (int)z);
     }
-    const double v = (h2 * f[t] - acc) / (3.0 * HoW<R>::w0);
+    const double v = div_const(h2 * f[t] - acc, 3.0 * HoW<R>::w0);
     *(double2*)(out + t0) = q ? make_double2(cur.x, v) : make_double2(v, cur.y);
 }
 
@@ -1135,7 +1315,7 @@ __global__ __launch_bounds__(kBlock) void k_hoz_half_lds(const double* __restric
             const double pz = row[z - s] + row[z + s];
             acc += ho_w<R>(s) * ((px + py) + pz);
         }
-        const double v = (h2 * f[i] - acc) / (3.0 * HoW<R>::w0);
+        const double v = div_const(h2 * f[i] - acc, 3.0 * HoW<R>::w0);
         *(double2*)(out + i0) = q ? make_double2(row[z0], v) : make_double2(v, row[z0 + 1]);
     }
 }

@@ -426,6 +426,11 @@ constexpr int kHoParts = 8192;   // partial sums of the reductions, at most
 template <class T>
 void launch_ho_half(const T* in, T* out, const T* f, int lg, double h, int order, int colour, hipStream_t st,
                     hipEvent_t ea = nullptr, hipEvent_t eb = nullptr);
+// both half-sweeps of a sweep in one launch, in -> out (another array)
+bool ho_sweep_ok(int lg, int order);
+template <class T>
+void launch_ho_sweep(const T* in, T* out, const T* f, int lg, double h, int order, hipStream_t st,
+                     hipEvent_t ea = nullptr, hipEvent_t eb = nullptr);
 template <class T>   // h: the fine spacing
 void launch_ho_resid_restrict(const T* u, const T* f, T* uc, T* uold, T* rc, int lgc, double h, int order,
                               hipStream_t st);

@@ -2115,7 +2115,15 @@ static void ho_smooth(HoPlan& P, const HoArr<T>& A, int l, int sweeps, hipStream
     const int lg = P.lg - l;
     const double h = std::ldexp(P.h, l);
     const double half_bytes = 3.0 * sizeof(T) * (double)((size_t)1 << (3 * lg));   // in, f read; out written
-    for (int s = 0; s < sweeps; ++s)
+    int s = 0;
+    if (ho_sweep_ok(lg, P.order))
+        for (; s + 2 <= sweeps; s += 2)   // two sweeps of one launch each end where they started
+            for (int c = 0; c < 2; ++c) {
+                KEvents ev(l == 0);
+                launch_ho_sweep<T>(c ? A.tmp[l] : A.u[l], c ? A.u[l] : A.tmp[l], A.f[l], lg, h, P.order, st, ev.a, ev.b);
+                ev.done(half_bytes);
+            }
+    for (; s < sweeps; ++s)
         for (int c = 0; c < 2; ++c) {
             KEvents ev(l == 0);
             const T* in = c == 0 ? A.u[l] : A.tmp[l];
