@@ -19,6 +19,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ghost_bodies.h"
 #include "mg_internal.h"
@@ -303,34 +304,40 @@ __device__ const double kCoarsest7[64] = {
 // table takes the place of summing the modes at each call (up to 342 of them, four cosines and a
 // division each, per distance): 1LPT of one 28^3 box 4817 -> 1027 us, of one 20^3 box (FP64) 1580 ->
 // 797 us (MI355X).  G and F are workgroup arrays of at least M^3 doubles.
-template <class T>
-__device__ void block_coarsest(T* __restrict__ u, const T* __restrict__ f, int M, double h, double* G, double* F) {
-    const int n3 = M * M * M;
-    if (M == 1) {
+template <int M, class T>
+__device__ __forceinline__ void block_coarsest(T* __restrict__ u, const T* __restrict__ f, double h, double* G,
+                                               double* F, unsigned nt) {
+    if constexpr (M == 1) {
         if (threadIdx.x == 0) u[0] = T(0);
         return;
-    }
-    const int H = M / 2 + 1;
-    const double* g = M == 3 ? kCoarsest3 : (M == 5 ? kCoarsest5 : kCoarsest7);
-    for (int t = threadIdx.x; t < H * H * H; t += blockDim.x) G[t] = g[t] * (h * h);
-    for (int t = threadIdx.x; t < n3; t += blockDim.x) F[t] = (double)f[t];
-    __syncthreads();
-    auto dist = [M](int p, int q) {
-        const int d = p < q ? q - p : p - q;
-        return min(d, M - d);
-    };
-    for (int t = threadIdx.x; t < n3; t += blockDim.x) {
-        const int z = t % M, y = (t / M) % M, x = t / (M * M);
-        double acc = 0.0;
-        const double* Fs = F;
-        for (int sx = 0; sx < M; ++sx) {
-            const double* Gx = G + dist(x, sx) * H * H;
-            for (int sy = 0; sy < M; ++sy) {
-                const double* Gy = Gx + dist(y, sy) * H;
-                for (int sz = 0; sz < M; ++sz) acc += Gy[dist(z, sz)] * *Fs++;
+    } else {
+        constexpr int n3 = M * M * M, H = M / 2 + 1;
+        const double* g = M == 3 ? kCoarsest3 : (M == 5 ? kCoarsest5 : kCoarsest7);
+        for (int t = threadIdx.x; t < H * H * H; t += nt) G[t] = g[t] * (h * h);
+        for (int t = threadIdx.x; t < n3; t += nt) F[t] = (double)f[t];
+        __syncthreads();
+        auto dist = [](int p, int q) {
+            const int d = p < q ? q - p : p - q;
+            return min(d, M - d);
+        };
+        for (int t = threadIdx.x; t < n3; t += nt) {
+            const int z = t % M, y = (t / M) % M, x = t / (M * M);
+            int dy[M], dz[M];
+#pragma unroll
+            for (int s = 0; s < M; ++s) {
+                dy[s] = dist(y, s) * H;
+                dz[s] = dist(z, s);
             }
+            double acc = 0.0;
+            for (int sx = 0; sx < M; ++sx) {
+                const double *Gx = G + dist(x, sx) * H * H, *Fs = F + sx * M * M;
+#pragma unroll
+                for (int sy = 0; sy < M; ++sy)
+#pragma unroll
+                    for (int sz = 0; sz < M; ++sz) acc += Gx[dy[sy] + dz[sz]] * Fs[sy * M + sz];
+            }
+            u[t] = (T)acc;
         }
-        u[t] = (T)acc;
     }
 }
 
@@ -605,7 +612,12 @@ template <class T>
 __global__ void k_coarsest(T* __restrict__ u, const T* __restrict__ f, int M, double h) {
     __shared__ double G[343];
     __shared__ double F[343];
-    block_coarsest<T>(u, f, M, h, G, F);
+    switch (M) {
+        case 1: block_coarsest<1>(u, f, h, G, F, blockDim.x); break;
+        case 3: block_coarsest<3>(u, f, h, G, F, blockDim.x); break;
+        case 5: block_coarsest<5>(u, f, h, G, F, blockDim.x); break;
+        case 7: block_coarsest<7>(u, f, h, G, F, blockDim.x); break;
+    }
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -613,6 +625,12 @@ __global__ void k_coarsest(T* __restrict__ u, const T* __restrict__ f, int M, do
 // level of it held in LDS.  As separate kernels these levels are launch-bound; here each step is
 // a loop of the workgroup's threads over a level's cells with a barrier between steps.  The
 // first level's u and f are read from global memory and its u is written back at the end.
+// A chain of some 50 dependent steps: bound by the latency of each (LDS, divisions, the barrier).  So
+// the size is a template argument, one kernel for every size a tail can start at (index arithmetic by
+// constants), a thread keeps its cells' right-hand sides and neighbours' places over a pass's half-sweeps,
+// and no more waves take part than the first level needs.  Measured (MI355X) against one kernel for all sizes
+// with 16 waves, FP64 / FP32: from 8^3 15.9 -> 11.0 / 14.6 -> 10.3 us, 10^3 20.4 -> 14.7 / 18.5 -> 13.1, 12^3 25.6 ->
+// 18.3 / 23.3 -> 15.5, 14^3 45.8 -> 33.0 / 41.7 -> 28.5 (of it 18 the 7^3 solve, by LDS conflicts).
 // ----------------------------------------------------------------------------------------------
 
 // Copy of a block-uniform value whose 32-bit words are marked wave-uniform, so that the compiler
@@ -629,210 +647,95 @@ __device__ __forceinline__ S uniform(const S& v) {
     return out;
 }
 
-template <class T>
-__device__ void body_tail(const TailPlan<T>& tp) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    auto U = [&](int k) { return (T*)(smem + uniform(tp.lev[k].lds_u)); };
-    auto F = [&](int k) { return (T*)(smem + uniform(tp.lev[k].lds_f)); };
-    auto O = [&](int k) { return (T*)(smem + uniform(tp.lev[k].lds_o)); };
-    double* G = (double*)(smem + uniform(tp.lds_bytes) - 2 * 343 * sizeof(double));
-    double* Gf = G + 343;
-    const unsigned nt = blockDim.x;
-    {
-        const unsigned n0 = (unsigned)uniform(tp.lev[0].lay.d).cells();
-        T* U0 = U(0);
-        T* F0 = F(0);
-        const T* u0g = uniform(tp.lev[0].u);
-        const T* f0g = uniform(tp.lev[0].f);
-        for (unsigned t = threadIdx.x; t < n0; t += nt) {
-            U0[t] = u0g[t];
-            F0[t] = f0g[t];
-        }
-        __syncthreads();
-        if (uniform(tp.fas0)) {   // the parent's step 6 on this level: f += L u
-            const Lay A = uniform(tp.lev[0].lay);
-            const double h0 = uniform(tp.lev[0].h);
-            const T H2 = (T)(h0 * h0);
-            for (unsigned t = threadIdx.x; t < n0; t += nt) {
-                int x, y, z;
-                ldecode(A, t, x, y, z);
-                const T s = nsum_periodic<T>(U0, A.d, A.split, x, y, z);
-                F0[t] = F0[t] + (s - T(6) * U0[t]) / H2;
-            }
-            __syncthreads();
-        }
-    }
-    // descent: smooth, restrict, FAS right-hand side
-    const int nlev = uniform(tp.n), nu1 = uniform(tp.nu1), nu2 = uniform(tp.nu2);
-    for (int l = 0; l + 1 < nlev; ++l) {
-        const Lay A = uniform(tp.lev[l].lay), Bl = uniform(tp.lev[l + 1].lay);
-        const double hl = uniform(tp.lev[l].h);
-        const T h2 = (T)(hl * hl);
-        const unsigned half = (unsigned)A.d.cells() >> 1;
-        for (int s = 0; s < nu1; ++s)
-            for (int c = 0; c < 2; ++c) {
-                for (unsigned t = threadIdx.x; t < half; t += nt) cell_rbgs_split<T>(U(l), F(l), A, h2, c, t);
-                __syncthreads();
-            }
-        const ParentMap pm(Bl, 0, 0, 0, 1);
-        Lay C = Bl;   // the coarse level is the whole covered box, decoded in natural order
-        C.split = 0;
-        const unsigned nc = (unsigned)A.d.cells() >> 3;
-        {   // one thread per fine cell: the 8 children of a coarse cell in 8 neighbouring lanes, summed by
-            // shuffles in the order of cell_resid_restrict (every lane of a wave takes part)
-            const T* u = U(l);
-            const T* f = F(l);
-            for (unsigned base = 0; base < 8 * nc; base += nt) {
-                const unsigned t = base + threadIdx.x, ch = t & 7;
-                const bool act = t < 8 * nc;
-                int X = 0, Y = 0, Z = 0;
-                T r = T(0), ui = T(0);
-                if (act) {
-                    ldecode(C, t >> 3, X, Y, Z);
-                    const int x = 2 * X + (int)(ch >> 2), y = 2 * Y + (int)((ch >> 1) & 1), z = 2 * Z + (int)(ch & 1);
-                    const size_t i = lidx(A, x, y, z);
-                    ui = u[i];
-                    const T lap = (nsum_periodic<T>(u, A.d, A.split, x, y, z) - T(6) * ui) / h2;
-                    r = f[i] - lap;
-                }
-                const int lane0 = (int)(threadIdx.x & 63) & ~7;
-                T sr = T(0), su = T(0);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    sr = sr + __shfl(r, lane0 + q, 64);
-                    su = su + __shfl(ui, lane0 + q, 64);
-                }
-                if (act && ch == 0) {
-                    const T uc = su * T(0.125);
-                    const size_t P = pidx(pm, X, Y, Z);
-                    U(l + 1)[P] = uc;
-                    F(l + 1)[P] = sr * T(0.125);
-                    O(l)[t >> 3] = uc;
-                }
-            }
-        }
-        __syncthreads();
-        const double hc = uniform(tp.lev[l + 1].h);
-        const T H2 = (T)(hc * hc);
-        for (unsigned t = threadIdx.x; t < nc; t += nt) cell_fas<T>(U(l + 1), F(l + 1), pm, C, H2, t);
-        __syncthreads();
-    }
-    {
-        const int c = nlev - 1;
-        block_coarsest<T>(U(c), F(c), uniform(tp.lev[c].lay.d).x, uniform(tp.lev[c].h), G, Gf);
-        __syncthreads();
-    }
-    // ascent: correct, smooth
-    for (int l = nlev - 2; l >= 0; --l) {
-        const Lay A = uniform(tp.lev[l].lay), Bl = uniform(tp.lev[l + 1].lay);
-        const ParentMap pm(Bl, 0, 0, 0, 1);
-        const unsigned n = (unsigned)A.d.cells();
-        if (nu2 > 0 && A.split)   // red cells are rewritten unread by the first red half-sweep
-            for (unsigned t = threadIdx.x; t < n >> 1; t += nt) cell_prolong_black<T>(U(l), A, U(l + 1), O(l), pm, t);
-        else
-            for (unsigned t = threadIdx.x; t < n; t += nt) cell_prolong<T>(U(l), A, U(l + 1), O(l), pm, t);
-        __syncthreads();
-        const double hl = uniform(tp.lev[l].h);
-        const T h2 = (T)(hl * hl);
-        for (int s = 0; s < nu2; ++s)
-            for (int c = 0; c < 2; ++c) {
-                for (unsigned t = threadIdx.x; t < n >> 1; t += nt) cell_rbgs_split<T>(U(l), F(l), A, h2, c, t);
-                __syncthreads();
-            }
-    }
-    const unsigned n0 = (unsigned)uniform(tp.lev[0].lay.d).cells();
-    T* u0out = uniform(tp.lev[0].u);
-    for (unsigned t = threadIdx.x; t < n0; t += nt) u0out[t] = U(0)[t];
+// Position of cell (x, y, z) of an N^3 level: colour-split for even N, natural for odd.
+template <int N>
+__device__ __forceinline__ unsigned tail_pos(unsigned x, unsigned y, unsigned z) {
+    if constexpr (N % 2) return (x * N + y) * N + z;
+    else return (x * N + y) * N + ((x + y + z) & 1u) * (N / 2) + (z >> 1);
 }
-
-template <class T>
-__global__ void __launch_bounds__(kTailThreads) k_tail(TailPlan<T> tp) {
-    body_tail<T>(tp);
-}
-
-// The same tail when every level but the single-cell coarsest is a colour-split power-of-two cube
-// (the coarsenings of a power-of-two base).  Positions and periodic neighbour sums are formed by
-// shifts and masks of the edge's log2, and the residual + restriction takes one thread per fine
-// cell: the 8 children of a coarse cell sit in 8 neighbouring lanes and are summed by lane
-// shuffles in the same (a, b, e) order.  The operations on every value are those of body_tail,
-// so the bits are the same; only the index arithmetic and the work split differ.
-__device__ __forceinline__ unsigned p2pos(int lg, unsigned x, unsigned y, unsigned z) {
-    if (lg == 0) return 0u;   // the single-cell coarsest level
-    return ((((x << lg) | y) << lg) + (((x + y + z) & 1u) << (lg - 1))) + (z >> 1);
-}
-
-template <class T>
-__device__ __forceinline__ T p2nsum(const T* u, int lg, unsigned x, unsigned y, unsigned z) {
-    const unsigned m = (1u << lg) - 1;
-    const T xm = u[p2pos(lg, (x - 1) & m, y, z)], xp = u[p2pos(lg, (x + 1) & m, y, z)];
-    const T ym = u[p2pos(lg, x, (y - 1) & m, z)], yp = u[p2pos(lg, x, (y + 1) & m, z)];
-    const T zm = u[p2pos(lg, x, y, (z - 1) & m)], zp = u[p2pos(lg, x, y, (z + 1) & m)];
+template <int N, class T>
+__device__ __forceinline__ T tail_nsum(const T* u, unsigned x, unsigned y, unsigned z) {
+    auto up = [](unsigned a) { return a + 1 == N ? 0u : a + 1; };
+    auto dn = [](unsigned a) { return a == 0 ? N - 1u : a - 1; };
+    const T xm = u[tail_pos<N>(dn(x), y, z)], xp = u[tail_pos<N>(up(x), y, z)];
+    const T ym = u[tail_pos<N>(x, dn(y), z)], yp = u[tail_pos<N>(x, up(y), z)];
+    const T zm = u[tail_pos<N>(x, y, dn(z))], zp = u[tail_pos<N>(x, y, up(z))];
     return ((xm + xp) + (ym + yp)) + (zm + zp);
 }
+// threads of a tail that starts at N^3: one or two cells of a colour each, no more waves than that
+// takes (every barrier waits for all of them)
+constexpr int tail_threads(int N) { return N <= 4 ? 64 : (N <= 6 ? 128 : (N <= 10 ? 256 : (N <= 14 ? 512 : 1024))); }
 
-template <class T>
-__device__ void body_tail_p2(const TailPlan<T>& tp) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    auto U = [&](int k) { return (T*)(smem + uniform(tp.lev[k].lds_u)); };
-    auto F = [&](int k) { return (T*)(smem + uniform(tp.lev[k].lds_f)); };
-    auto O = [&](int k) { return (T*)(smem + uniform(tp.lev[k].lds_o)); };
-    const unsigned nt = blockDim.x, tid = threadIdx.x;
-    const int nlev = uniform(tp.n), nu1 = uniform(tp.nu1), nu2 = uniform(tp.nu2);
-    const int lg0 = uniform(tp.lev[0].lay.lgx);
-    {
-        const unsigned n0 = 1u << (3 * lg0);
-        T* U0 = U(0);
-        T* F0 = F(0);
-        const T* u0g = uniform(tp.lev[0].u);
-        const T* f0g = uniform(tp.lev[0].f);
-        for (unsigned t = tid; t < n0; t += nt) {
-            U0[t] = u0g[t];
-            F0[t] = f0g[t];
+// `sweeps` red-black sweeps: a thread keeps its cells' right-hand sides and neighbours' places
+template <int N, int NT, class T>
+__device__ __forceinline__ void tail_smooth(T* u, const T* f, T h2, int sweeps) {
+    if (sweeps == 0) return;
+    constexpr int H = N * N * N / 2, I = (H + NT - 1) / NT;
+    unsigned own[2][I], nb[2][I][6];
+    T fv[2][I];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            const unsigned t = min(threadIdx.x + (unsigned)(i * NT), (unsigned)H - 1);
+            const unsigned row = t / (N / 2), j = t - row * (N / 2), x = row / N, y = row - x * N;
+            const unsigned z = 2 * j + ((x + y + (unsigned)c) & 1u);
+            auto up = [](unsigned a) { return a + 1 == N ? 0u : a + 1; };
+            auto dn = [](unsigned a) { return a == 0 ? N - 1u : a - 1; };
+            own[c][i] = tail_pos<N>(x, y, z);
+            nb[c][i][0] = tail_pos<N>(dn(x), y, z);
+            nb[c][i][1] = tail_pos<N>(up(x), y, z);
+            nb[c][i][2] = tail_pos<N>(x, dn(y), z);
+            nb[c][i][3] = tail_pos<N>(x, up(y), z);
+            nb[c][i][4] = tail_pos<N>(x, y, dn(z));
+            nb[c][i][5] = tail_pos<N>(x, y, up(z));
+            fv[c][i] = f[own[c][i]];
         }
-        __syncthreads();
-        if (uniform(tp.fas0)) {   // the parent's step 6 on this level: f += L u
-            const Lay A = uniform(tp.lev[0].lay);
-            const double h0 = uniform(tp.lev[0].h);
-            const T H2 = (T)(h0 * h0);
-            for (unsigned t = tid; t < n0; t += nt) {
-                int x, y, z;
-                ldecode(A, t, x, y, z);
-                const T s = p2nsum<T>(U0, lg0, (unsigned)x, (unsigned)y, (unsigned)z);
-                F0[t] = F0[t] + (s - T(6) * U0[t]) / H2;
+    for (int s = 0; s < sweeps; ++s)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                const unsigned* n = nb[c][i];
+                const T sum = ((u[n[0]] + u[n[1]]) + (u[n[2]] + u[n[3]])) + (u[n[4]] + u[n[5]]);
+                if (threadIdx.x + i * NT < H) u[own[c][i]] = div6(sum - h2 * fv[c][i]);
             }
             __syncthreads();
         }
-    }
-    for (int l = 0; l + 1 < nlev; ++l) {
-        const Lay A = uniform(tp.lev[l].lay);
-        const int lg = lg0 - l, lc = lg - 1;
-        const double hl = uniform(tp.lev[l].h);
-        const T h2 = (T)(hl * hl);
-        const unsigned n = 1u << (3 * lg), half = n >> 1, mc = (1u << lc) - 1;
-        T* u = U(l);
-        T* f = F(l);
-        T* pu = U(l + 1);
-        T* pf = F(l + 1);
-        T* uo = O(l);
-        for (int s = 0; s < nu1; ++s)
-            for (int c = 0; c < 2; ++c) {
-                for (unsigned t = tid; t < half; t += nt) cell_rbgs_split<T>(u, f, A, h2, c, t);
-                __syncthreads();
-            }
-        for (unsigned base = 0; base < n; base += nt) {   // every lane of a wave takes part in the shuffles
-            const unsigned t = base + tid, ch = t & 7, cc = t >> 3;
-            const bool act = t < n;
-            const unsigned X = cc >> (2 * lc), Y = (cc >> lc) & mc, Z = cc & mc;
-            const unsigned x = 2 * X + (ch >> 2), y = 2 * Y + ((ch >> 1) & 1), z = 2 * Z + (ch & 1);
+}
+
+// one V-cycle from level l, N^3, down
+template <int N, int NT, class T>
+__device__ __forceinline__ void tail_level(const TailPlan<T>& tp, int l, unsigned char* smem, int nu1, int nu2) {
+    T* u = (T*)(smem + uniform(tp.lev[l].lds_u));
+    T* f = (T*)(smem + uniform(tp.lev[l].lds_f));
+    const double h = uniform(tp.lev[l].h);
+    if constexpr (N % 2) {
+        double* G = (double*)(smem + uniform(tp.lds_bytes) - 2 * 343 * sizeof(double));
+        block_coarsest<N>(u, f, h, G, G + 343, NT);
+        __syncthreads();
+    } else {
+        constexpr int C = N / 2, n = N * N * N, nc = C * C * C;
+        const T h2 = (T)(h * h);
+        T* pu = (T*)(smem + uniform(tp.lev[l + 1].lds_u));
+        T* pf = (T*)(smem + uniform(tp.lev[l + 1].lds_f));
+        T* uo = (T*)(smem + uniform(tp.lev[l].lds_o));
+        tail_smooth<N, NT>(u, f, h2, nu1);
+        // one thread per fine cell: the 8 children of a coarse cell in 8 neighbouring lanes, summed by shuffles
+        // in the order of cell_resid_restrict (every lane of a wave takes part)
+        for (unsigned base = 0; base < (unsigned)n; base += NT) {
+            const unsigned t = base + threadIdx.x, ch = t & 7, cc = t >> 3;
+            const bool act = t < (unsigned)n;
+            const unsigned row = cc / C, Z = cc - row * C, X = row / C, Y = row - X * C;
             T r = T(0), ui = T(0);
             if (act) {
-                const unsigned i = p2pos(lg, x, y, z);
+                const unsigned x = 2 * X + (ch >> 2), y = 2 * Y + ((ch >> 1) & 1), z = 2 * Z + (ch & 1);
+                const unsigned i = tail_pos<N>(x, y, z);
                 ui = u[i];
-                const T sn = p2nsum<T>(u, lg, x, y, z);
-                const T lap = (sn - T(6) * ui) / h2;
+                const T lap = (tail_nsum<N>(u, x, y, z) - T(6) * ui) / h2;
                 r = f[i] - lap;
             }
-            const int lane0 = (int)(tid & 63) & ~7;
+            const int lane0 = (int)(threadIdx.x & 63) & ~7;
             T sr = T(0), su = T(0);
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
@@ -841,7 +744,7 @@ __device__ void body_tail_p2(const TailPlan<T>& tp) {
             }
             if (act && ch == 0) {
                 const T uc = su * T(0.125);
-                const unsigned P = p2pos(lc, X, Y, Z);
+                const unsigned P = tail_pos<C>(X, Y, Z);
                 pu[P] = uc;
                 pf[P] = sr * T(0.125);
                 uo[cc] = uc;
@@ -850,56 +753,56 @@ __device__ void body_tail_p2(const TailPlan<T>& tp) {
         __syncthreads();
         const double hc = uniform(tp.lev[l + 1].h);
         const T H2 = (T)(hc * hc);
-        for (unsigned t = tid; t < (n >> 3); t += nt) {
-            const unsigned X = t >> (2 * lc), Y = (t >> lc) & mc, Z = t & mc;
-            const unsigned i = p2pos(lc, X, Y, Z);
-            const T sn = p2nsum<T>(pu, lc, X, Y, Z);
-            pf[i] = pf[i] + (sn - T(6) * pu[i]) / H2;
+        for (unsigned t = threadIdx.x; t < (unsigned)nc; t += NT) {
+            const unsigned row = t / C, Z = t - row * C, X = row / C, Y = row - X * C;
+            const unsigned i = tail_pos<C>(X, Y, Z);
+            pf[i] = pf[i] + (tail_nsum<C>(pu, X, Y, Z) - T(6) * pu[i]) / H2;
         }
         __syncthreads();
-    }
-    if (tid == 0) U(nlev - 1)[0] = T(0);   // step 1 on the single-cell coarsest level
-    __syncthreads();
-    for (int l = nlev - 2; l >= 0; --l) {
-        const Lay A = uniform(tp.lev[l].lay);
-        const int lg = lg0 - l, lc = lg - 1;
-        const unsigned n = 1u << (3 * lg), m = (1u << lg) - 1, nzh = 1u << (lg - 1);
-        T* u = U(l);
-        const T* pu = U(l + 1);
-        const T* uo = O(l);
-        if (nu2 > 0) {   // red cells are rewritten unread by the first red half-sweep
-            for (unsigned t = tid; t < (n >> 1); t += nt) {
-                const unsigned row = t >> (lg - 1), j = t & (nzh - 1);
-                const unsigned x = row >> lg, y = row & m, z = 2 * j + ((x + y + 1) & 1);
-                const unsigned i = (row << lg) + nzh + j;
-                const unsigned X = x >> 1, Y = y >> 1, Z = z >> 1;
-                u[i] = u[i] + (pu[p2pos(lc, X, Y, Z)] - uo[(((X << lc) | Y) << lc) | Z]);
-            }
-        } else {
-            for (unsigned t = tid; t < n; t += nt) {
-                int x, y, z;
-                ldecode(A, t, x, y, z);
-                const unsigned X = (unsigned)x >> 1, Y = (unsigned)y >> 1, Z = (unsigned)z >> 1;
-                u[t] = u[t] + (pu[p2pos(lc, X, Y, Z)] - uo[(((X << lc) | Y) << lc) | Z]);
-            }
+        tail_level<C, NT>(tp, l + 1, smem, nu1, nu2);
+        // with a sweep to come the red cells are rewritten unread by its first half
+        const unsigned first = nu2 > 0 ? (unsigned)(n / 2) : 0u;
+        for (unsigned t = first + threadIdx.x; t < (unsigned)n; t += NT) {
+            const unsigned black = t >= (unsigned)(n / 2), k = black ? t - n / 2 : t;   // cell k of its colour
+            const unsigned row = k / (N / 2), Z = k - row * (N / 2), x = row / N, y = row - x * N;
+            const unsigned i = row * N + black * (N / 2) + Z, X = x >> 1, Y = y >> 1;
+            u[i] = u[i] + (pu[tail_pos<C>(X, Y, Z)] - uo[(X * C + Y) * C + Z]);
         }
         __syncthreads();
-        const double hl = uniform(tp.lev[l].h);
-        const T h2 = (T)(hl * hl);
-        for (int s = 0; s < nu2; ++s)
-            for (int c = 0; c < 2; ++c) {
-                for (unsigned t = tid; t < (n >> 1); t += nt) cell_rbgs_split<T>(u, F(l), A, h2, c, t);
-                __syncthreads();
-            }
+        tail_smooth<N, NT>(u, f, h2, nu2);
     }
-    const unsigned n0 = 1u << (3 * lg0);
-    T* u0out = uniform(tp.lev[0].u);
-    for (unsigned t = tid; t < n0; t += nt) u0out[t] = U(0)[t];
 }
 
-template <class T>
-__global__ void __launch_bounds__(kTailThreads) k_tail_p2(TailPlan<T> tp) {
-    body_tail_p2<T>(tp);
+template <int N, class T>
+__device__ __forceinline__ void body_tail(const TailPlan<T>& tp) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int n = N * N * N, NT = tail_threads(N);
+    T* u = (T*)(smem + uniform(tp.lev[0].lds_u));
+    T* f = (T*)(smem + uniform(tp.lev[0].lds_f));
+    T* ug = uniform(tp.lev[0].u);
+    const T* fg = uniform(tp.lev[0].f);
+    for (unsigned t = threadIdx.x; t < (unsigned)n; t += NT) {
+        u[t] = ug[t];
+        f[t] = fg[t];
+    }
+    __syncthreads();
+    if (uniform(tp.fas0)) {   // the parent's step 6 on this level: f += L u
+        const double h0 = uniform(tp.lev[0].h);
+        const T H2 = (T)(h0 * h0);
+        for (unsigned t = threadIdx.x; t < (unsigned)n; t += NT) {
+            const unsigned row = t / N, z = t - row * N, x = row / N, y = row - x * N;
+            const unsigned i = tail_pos<N>(x, y, z);
+            f[i] = f[i] + (tail_nsum<N>(u, x, y, z) - T(6) * u[i]) / H2;
+        }
+        __syncthreads();
+    }
+    tail_level<N, NT>(tp, 0, smem, uniform(tp.nu1), uniform(tp.nu2));
+    for (unsigned t = threadIdx.x; t < (unsigned)n; t += NT) ug[t] = u[t];
+}
+
+template <int N, class T>
+__global__ void __launch_bounds__(tail_threads(N)) k_tail(TailPlan<T> tp) {
+    body_tail<N, T>(tp);
 }
 
 // The ghost value of lane q = 2 jb + kc (jb, kc in {0, 1}) of group (J, K) on face `face` of a
@@ -1518,16 +1421,39 @@ void launch_rbgs_half(T* u, const T* f, const T* ghosts, Lay L, double h, int co
     }
 }
 
+// every size a tail can start at (its levels are cubes of at most 16^3, 1, 3, 5 or 7 times a power of two)
+template <class Fn>
+__host__ __device__ inline bool tail_case(int n, Fn&& fn) {
+    switch (n) {
+        case 1: fn(std::integral_constant<int, 1>{}); return true;
+        case 2: fn(std::integral_constant<int, 2>{}); return true;
+        case 3: fn(std::integral_constant<int, 3>{}); return true;
+        case 4: fn(std::integral_constant<int, 4>{}); return true;
+        case 5: fn(std::integral_constant<int, 5>{}); return true;
+        case 6: fn(std::integral_constant<int, 6>{}); return true;
+        case 7: fn(std::integral_constant<int, 7>{}); return true;
+        case 8: fn(std::integral_constant<int, 8>{}); return true;
+        case 10: fn(std::integral_constant<int, 10>{}); return true;
+        case 12: fn(std::integral_constant<int, 12>{}); return true;
+        case 14: fn(std::integral_constant<int, 14>{}); return true;
+        case 16: fn(std::integral_constant<int, 16>{}); return true;
+    }
+    return false;
+}
+
 // dynamic LDS above the default for the tail kernels; set once, before any graph capture
 hipError_t tail_kernel_setup() {
     static bool done = false;
     if (done) return hipSuccess;
-    const void* fns[4] = {(const void*)k_tail<float>, (const void*)k_tail<double>, (const void*)k_tail_p2<float>,
-                          (const void*)k_tail_p2<double>};
-    for (const void* fn : fns) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailMaxLds);
-        if (e != hipSuccess) return e;
-    }
+    for (int n = 1; n <= 16; ++n)
+        for (int fp64 = 0; fp64 < 2; ++fp64) {
+            hipError_t e = hipSuccess;
+            auto raise = [&](auto N) {
+                const void* fn = fp64 ? (const void*)k_tail<N.value, double> : (const void*)k_tail<N.value, float>;
+                e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTailMaxLds);
+            };
+            if (tail_case(n, raise) && e != hipSuccess) return e;
+        }
     done = true;
     return hipSuccess;
 }
@@ -1535,13 +1461,9 @@ hipError_t tail_kernel_setup() {
 template <class T>
 void launch_tail(const TailPlan<T>& tp, hipStream_t st) {
     (void)tail_kernel_setup();
-    bool p2 = tp.n >= 2 && tp.lev[tp.n - 1].lay.d.cells() == 1;
-    for (int k = 0; p2 && k + 1 < tp.n; ++k) {
-        const Lay& A = tp.lev[k].lay;
-        p2 = A.pow2 && A.split && A.d.x == A.d.y && A.d.y == A.d.z && A.lgx == tp.lev[0].lay.lgx - k;
-    }
-    if (p2) k_tail_p2<T><<<1, kTailThreads, tp.lds_bytes, st>>>(tp);
-    else k_tail<T><<<1, kTailThreads, tp.lds_bytes, st>>>(tp);
+    tail_case(tp.lev[0].lay.d.x, [&](auto N) {
+        k_tail<N.value, T><<<1, tail_threads(N.value), tp.lds_bytes, st>>>(tp);
+    });
 }
 
 template <class T>
@@ -1759,7 +1681,10 @@ __global__ void __launch_bounds__(kTailThreads) kb_tail(const TailPlan<T>* __res
     __syncthreads();
     const TailPlan<T>& sp = *reinterpret_cast<const TailPlan<T>*>(raw);
     if (!active[uniform(sp.inst)]) return;
-    body_tail<T>(sp);
+    tail_case(uniform(sp.lev[0].lay.d.x), [&](auto N) {
+        // the waves that this size does not take leave (a barrier waits for the others only)
+        if (threadIdx.x < (unsigned)tail_threads(N.value)) body_tail<N.value, T>(sp);
+    });
 }
 
 __global__ void kb_outer(const BSeg* __restrict__ segs, int nseg, const int* __restrict__ active, int has_e,
