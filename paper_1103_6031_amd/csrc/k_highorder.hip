@@ -255,11 +255,11 @@ k_ho_sweep(const T* __restrict__ in, T* __restrict__ out, const T* __restrict__ 
         T* rd = own + (P & 1 ? 4 * size : 0);
         T* wr = own + (P & 1 ? 0 : 4 * size);
         const int p = first + s;
-        const bool more = s + 1 < steps, q = (p + y) & 1;
+        const bool q = (p + y) & 1;
         T fr;
         split(nu, p + R, red[N], blk[N]);
         split(nf, p, fr, fb[P]);
-        if (more) {
+        if (s + 1 < steps) {
             nu = load(in, p + R + 1);
             nf = load(f, p + 1);
         }
@@ -1320,6 +1320,145 @@ __global__ __launch_bounds__(kBlock) void k_hoz_half_lds(const double* __restric
     }
 }
 
+// A half-sweep of a patch, marched along x: a block owns tl.yr rows x tl.zp pairs of z-neighbours of tl.cx
+// planes with R rows and ceil(R / 2) pairs on each side, from the ghost layers outside the patch (corners,
+// which no stencil reads, are zero).  As in k_ho_sweep a thread keeps its pair of 2R + 1 planes in
+// registers by colour and the y- and z-neighbours come from LDS by colour, so every value is read
+// once per tile; k_hoz_half_lds reads the 2R x-neighbours of each row from L2, which bounds it (164 MB at
+// 128^3, order 6).  The last tile of a direction ends at the patch's edge and stores only what the tile
+// before it does not.  The operations are those of k_hoz_half in their order: the same bits.
+//
+// Measured (MI355X) against the rows' kernel: order 6 200^3 89 -> 41 us, 128^3 16.1 -> 14.9, 64^3 6.3 -> 8.1; order 4
+// 200^3 69 -> 36, 128^3 14.4 -> 13.4, 64^3 5.5 -> 6.9; order 2 200^3 48 -> 34, 128^3 12.0 -> 12.4.  Hence from 2^21
+// cells, order 2 from 2^22.
+template <int R>
+__global__ void __launch_bounds__(1024)
+k_hoz_half_march(const double* __restrict__ in, double* __restrict__ out, const double* __restrict__ f,
+                 const double* __restrict__ g, HozPatch P, double h2, int colour, HoTile tl) {
+    constexpr int L = 2 * R + 2, J = (R + 1) / 2;
+    extern __shared__ __align__(16) unsigned char hz_smem[];
+    const int n0 = P.n[0], n1 = P.n[1], n2 = P.n[2], n2h = n2 >> 1;
+    const int NP = tl.zp + 2 * J, cells = (tl.yr + 2 * R) * NP;
+    if ((int)(threadIdx.x & ~63u) >= cells) return;     // waves without a pair
+    // each XCD takes a contiguous run of tiles, so that the halos of neighbours are in its own L2
+    const unsigned b = (blockIdx.x % 8) * (gridDim.x / 8) + min(blockIdx.x % 8, gridDim.x % 8) + blockIdx.x / 8;
+    const int ntz = (n2h + tl.zp - 1) / tl.zp, nty = (n1 + tl.yr - 1) / tl.yr;
+    const int zt = (int)(b % (unsigned)ntz), bt = (int)(b / (unsigned)ntz);
+    const int yo = (bt % nty) * tl.yr, xo = (bt / nty) * tl.cx, ko = zt * tl.zp;   // first own row, plane, pair
+    const int y0 = min(yo, n1 - tl.yr), x0 = min(xo, n0 - tl.cx), k0 = min(ko, n2h - tl.zp);
+    const int t = min((int)threadIdx.x, cells - 1), r = t / NP, k = t - r * NP;
+    const bool live = (int)threadIdx.x < cells;
+    const int y = y0 + r - R, z0 = 2 * (k0 + k - J);
+    const bool yin = y >= 0 && y < n1, zin = z0 >= 0 && z0 < n2;
+    const bool mine = live && r >= R + (yo - y0) && r < R + tl.yr && k >= J + (ko - k0) && k < J + tl.zp;
+    // where the pair comes from in a plane of the patch, and the distance between planes
+    const double* from = in;
+    size_t stride = 0;
+    int skip = 0;                                       // 1: both cells absent; z ghosts: see below
+    const int ylay = y < 0 ? -1 - y : y - n1, zs = z0 < 0 ? -1 : 1;
+    if (yin && zin) {
+        from = in + (size_t)y * n2 + z0;
+        stride = (size_t)n1 * n2;
+    } else if (zin) {
+        from = g + hoz_face_off(P.n, R, y < 0 ? 2 : 3) + (size_t)ylay * n0 * n2 + z0;
+        stride = (size_t)n2;
+    } else if (yin) {
+        from = g + hoz_face_off(P.n, R, z0 < 0 ? 4 : 5) + y;
+        stride = (size_t)n1;
+    } else {
+        skip = 1;
+    }
+    // ghost layer of the pair's cells in front of a z face (past the R-th: not read by any stencil)
+    const int la = zs < 0 ? -1 - z0 : z0 - n2, lb = la + zs;
+    const double* xlo = g + hoz_face_off(P.n, R, 0) + (size_t)y * n2 + z0;
+    const double* xhi = g + hoz_face_off(P.n, R, 1) + (size_t)y * n2 + z0;
+    auto load = [&](int p) -> double2 {
+        double2 v = make_double2(0.0, 0.0);
+        if (p < 0 || p >= n0) {
+            const int lay = p < 0 ? -1 - p : p - n0;
+            if (yin && zin) v = *(const double2*)((p < 0 ? xlo : xhi) + (size_t)lay * n1 * n2);
+        } else if (zin && !skip) {
+            v = *(const double2*)(from + p * stride);
+        } else if (!skip) {
+            if (la < R) v.x = from[((size_t)la * n0 + p) * n1];
+            if (lb < R) v.y = from[((size_t)lb * n0 + p) * n1];
+        }
+        return v;
+    };
+    const double* fp = f + (mine ? (size_t)y * n2 + z0 : 0);
+    auto load_f = [&](int p) { return *(const double2*)(fp + (size_t)p * n1 * n2); };
+    auto split = [&](const double2& v, int p, double& own, double& oth) {
+        const bool q = (p + y + colour) & 1;            // the pair's second cell has the colour
+        own = q ? v.y : v.x;
+        oth = q ? v.x : v.y;
+    };
+    double S[L], O[L];                                  // the half-sweep's colour and the other one, plane x0 + d: d mod L
+#pragma unroll
+    for (int i = 0; i < L; ++i) S[i] = O[i] = 0.0;
+    double2 first[2 * R];                               // (all in flight before the first is used)
+#pragma unroll
+    for (int d = -R; d < R; ++d) first[d + R] = load(x0 + d);
+    // loaded two steps ahead of their use
+    double2 nu[2] = {load(x0 + R), load(x0 + R + (tl.cx > 1))}, nf[2] = {load_f(x0), load_f(x0 + (tl.cx > 1))};
+#pragma unroll
+    for (int d = -R; d < R; ++d) split(first[d + R], x0 + d, S[(d + L) % L], O[(d + L) % L]);
+    double* own = (double*)hz_smem + t;
+    if (live) {
+        own[0] = S[0];
+        own[cells] = O[0];
+    }
+    __syncthreads();
+    auto step = [&](int s, auto phase) __attribute__((always_inline)) {
+        constexpr int C = decltype(phase)::value;       // s mod L
+        const double* ls = own + (C & 1 ? 2 * cells : 0);
+        const double* lo = ls + cells;
+        double* wr = own + (C & 1 ? 0 : 2 * cells);
+        const int p = x0 + s;
+        const bool q = (p + y + colour) & 1;
+        split(nu[C & 1], p + R, S[(C + R) % L], O[(C + R) % L]);
+        const double fv = q ? nf[C & 1].y : nf[C & 1].x;
+        if (s + 2 < tl.cx) {
+            nu[C & 1] = load(p + R + 2);
+            nf[C & 1] = load_f(p + 2);
+        }
+        if (mine && p >= xo) {
+            double acc = 0;
+#pragma unroll
+            for (int s2 = 1; s2 <= R; ++s2) {
+                const double *D = s2 & 1 ? O : S, *l = s2 & 1 ? lo : ls;
+                const double px = D[(C - s2 + L) % L] + D[(C + s2) % L];
+                const double py = l[-s2 * NP] + l[s2 * NP];
+                double pz;
+                if (s2 == 1) pz = O[C] + (q ? lo + 1 : lo - 1)[0];
+                else if (s2 == 2) pz = ls[-1] + ls[1];
+                else pz = (q ? lo + 1 : lo)[-2] + (q ? lo + 1 : lo)[1];
+                acc += ho_w<R>(s2) * ((px + py) + pz);
+            }
+            const double v = div_const(h2 * fv - acc, 3.0 * HoW<R>::w0);
+            *(double2*)(out + ((size_t)p * n1 + y) * n2 + z0) = q ? make_double2(O[C], v) : make_double2(v, O[C]);
+        }
+        if (live) {
+            if constexpr (R > 1) wr[0] = S[(C + 1) % L];
+            wr[cells] = O[(C + 1) % L];
+        }
+        __syncthreads();
+    };
+    for (int s = 0; s < tl.cx; s += L) {
+        step(s, std::integral_constant<int, 0>{});
+        if (s + 1 < tl.cx) step(s + 1, std::integral_constant<int, 1>{});
+        if (s + 2 < tl.cx) step(s + 2, std::integral_constant<int, 2>{});
+        if (s + 3 < tl.cx) step(s + 3, std::integral_constant<int, 3>{});
+        if constexpr (L > 4) {
+            if (s + 4 < tl.cx) step(s + 4, std::integral_constant<int, 4>{});
+            if (s + 5 < tl.cx) step(s + 5, std::integral_constant<int, 5>{});
+        }
+        if constexpr (L > 6) {
+            if (s + 6 < tl.cx) step(s + 6, std::integral_constant<int, 6>{});
+            if (s + 7 < tl.cx) step(s + 7, std::integral_constant<int, 7>{});
+        }
+    }
+}
+
 // Steps 3-5 on a patch with 8 lanes per coarse cell (lanes 8k .. 8k + 7 of a wave hold the
 // children (a, b, e) in the order a, b, e): each lane forms one child's residual, reading its
 // neighbours directly where the whole stencil lies inside the patch and through the ghost layers
@@ -1576,10 +1715,56 @@ void launch_hoz_ghost(const double* pu, const double* u, double* g, const HozPat
 #undef HOZ_GH
 }
 
+// The tile of a half-sweep: the least of rounds x steps x time of a step (2.2 + the waves per SIMD), 256 CUs
+// of 16 waves.
+static HoTile hoz_half_tile(const HozPatch& P, int R) {
+    HoTile best{0, 0, 0};
+    double least = 1e30;
+    auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
+    const int n0 = P.n[0], n1 = P.n[1], n2h = P.n[2] / 2, J = (R + 1) / 2;
+    for (int tz = 1; tz <= n2h && tz <= 32; ++tz) {
+        const int zp = cdiv(n2h, tz);
+        if (zp > 32 || cdiv(n2h, zp) != tz) continue;
+        for (int ty = 1; ty <= n1; ++ty) {
+            const int yr = cdiv(n1, ty);
+            if (yr > 48 || cdiv(n1, yr) != ty) continue;
+            if (yr < 8 && ty > 1) break;
+            const int cells = (yr + 2 * R) * (zp + 2 * J), waves = cdiv(cells, 64);
+            if (cells > 1024) continue;
+            const int fit = 16 / waves;
+            for (int k = 1; k <= 8; ++k) {
+                int cx = std::max(4, cdiv(n0, std::max(1, 256 * k / (ty * tz))));
+                cx = std::min(n0, cdiv(n0, cdiv(n0, cx)));
+                const int blocks = ty * tz * cdiv(n0, cx), q = cdiv(blocks, 256), m = std::min(q, fit);
+                const double cost = (double)cdiv(q, fit) * (cx + 4) * (2.2 + cdiv(m * waves, 4));
+                if (cost < least) {
+                    least = cost;
+                    best = HoTile{yr, zp, cx};
+                }
+            }
+        }
+    }
+    return best;
+}
+
 void launch_hoz_half(const double* in, double* out, const double* f, const double* g, const HozPatch& P, int order,
                      int colour, hipStream_t st) {
     const double h2 = P.h * P.h;
     const int R = order / 2;
+    // (below, a half-sweep is a launch and a few memory latencies, and the rows' kernel has more blocks in flight)
+    const size_t n = (size_t)P.n[0] * P.n[1] * P.n[2];
+    const HoTile tl = n >= (size_t)1 << (R > 1 ? 21 : 22) ? hoz_half_tile(P, R) : HoTile{0, 0, 0};
+    const bool marched = tl.cx > 0;
+    if (marched) {
+        auto tiles = [](int n, int t) { return (unsigned)((n + t - 1) / t); };
+        const unsigned cells = (unsigned)((tl.yr + 2 * R) * (tl.zp + 2 * ((R + 1) / 2)));
+        const unsigned grid = tiles(P.n[0], tl.cx) * tiles(P.n[1], tl.yr) * tiles(P.n[2] / 2, tl.zp);
+        const unsigned block = (cells + 63) / 64 * 64, lds = 4 * cells * (unsigned)sizeof(double);
+        HOZ_R(order, (k_hoz_half_march<1><<<grid, block, lds, st>>>(in, out, f, g, P, h2, colour, tl)),
+              (k_hoz_half_march<2><<<grid, block, lds, st>>>(in, out, f, g, P, h2, colour, tl)),
+              (k_hoz_half_march<3><<<grid, block, lds, st>>>(in, out, f, g, P, h2, colour, tl)));
+        return;
+    }
     const size_t lds = (size_t)(kHoTy + 2 * R) * (P.n[2] + 2 * R) * sizeof(double);
     if (lds <= 64u * 1024u) {   // rows staged in LDS (within the default limit: n_z up to 570)
         const unsigned grid = (unsigned)P.n[0] * (unsigned)((P.n[1] + kHoTy - 1) / kHoTy);
