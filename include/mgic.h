@@ -351,8 +351,9 @@ size_t mg_batch_workspace_bytes(int ninst, const int* n, const mg_opts* opts);
  * runs the small-level tails of all of them (one workgroup each).  These launch sequences are
  * captured as HIP graphs on first use for a workspace and batch shape and replayed every cycle
  * (MG_NO_GRAPH: launched directly); converged instances are switched off by a device flag.
- * Other instances are solved one by one in the same call.  The smoother's block size and cells
- * per thread are chosen per level depth by timing candidates once per batch shape and process.
+ * Other instances are solved one by one in the same call.  Where levels are smoothed by half-sweeps, the
+ * block size and cells per thread are chosen per level depth by timing candidates once per batch shape
+ * and process.
  * Synchronises the stream at least once per FP64 correction (mixed) or cycle (FP64).
  * Returns the first failure in instance order (MG_ENOCONV / MG_EDIVERGED; all instances are
  * still solved and their stats filled), or MG_EINVAL / MG_EHIP. */
@@ -381,7 +382,8 @@ int mg_solve_batch_hier(int ninst, const mg_hier* const* hier, const double* con
                         double* const* const* u, const mg_opts* opts, mg_stats* stats, void* workspace,
                         size_t workspace_bytes, void* stream);
 
-/* Autotuning of the batched smoother (block size and cells per thread, per level depth).
+/* Autotuning of the batched half-sweeps (block size and cells per thread, per level depth; levels whose two
+ * sweeps run in one launch have nothing to tune).
  * mg_batch_tune_candidates: the number of candidate shapes.  mg_batch_force_shape(i): every
  * later mg_solve_batch in the process uses candidate i at every depth without timing (i = -1:
  * back to timing; MG_EINVAL out of range); every candidate gives the same bits.

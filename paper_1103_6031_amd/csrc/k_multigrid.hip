@@ -992,6 +992,53 @@ __global__ void k_residual(const T* __restrict__ u, const T* __restrict__ f, con
     if (threadIdx.x == 0) partials[blockIdx.x] = bs;
 }
 
+// k_residual of a colour-split patch, r in the same layout: the neighbours of all kRedV cells of a pass are
+// loaded before the first is used, each from the patch or its face's ghosts (one load from either address;
+// with a branch per neighbour every load waited for the one before it).  Same cells per thread, same
+// operations: the same bits.  Bound by latency; 128^3, FP32 result (MI355X): 15.2 -> 12.6 us.
+template <class T, class R>
+__global__ void k_residual_gh(const T* __restrict__ u, const T* __restrict__ f, const T* __restrict__ g, Lay L, T h2,
+                              CovBox cb, R* __restrict__ rout, double* __restrict__ partials) {
+    const Dims d = L.d;
+    const unsigned n = (unsigned)d.cells(), nzh = (unsigned)d.z >> 1, sy = (unsigned)d.z, sx = (unsigned)d.y * sy;
+    const unsigned fx = sx, fy = (unsigned)d.x * sy, fz = (unsigned)d.x * d.y;   // cells of a face
+    const RedRange rr = red_range(blockIdx.x, gridDim.x, n);
+    double acc = 0.0;
+    for (unsigned b0 = rr.lo + threadIdx.x; b0 < rr.hi; b0 += rr.stride) {
+        T w[kRedV][8];
+        bool cov[kRedV];
+#pragma unroll
+        for (int v = 0; v < kRedV; ++v) {
+            const unsigned i = min(b0 + v * blockDim.x, rr.hi - 1);
+            int x, y, z;
+            ldecode(L, i, x, y, z);
+            const unsigned row = (unsigned)x * sx + (unsigned)y * sy, j = (unsigned)z >> 1;
+            const unsigned o = row + (((x + y + z) & 1) ? 0u : nzh);            // the other colour's half of the row
+            const unsigned yz = (unsigned)(y * d.z + z), xz = (unsigned)(x * d.z + z), xy = (unsigned)(x * d.y + y);
+            w[v][0] = *(x > 0 ? u + (o - sx + j) : g + yz);
+            w[v][1] = *(x < d.x - 1 ? u + (o + sx + j) : g + (fx + yz));
+            w[v][2] = *(y > 0 ? u + (o - sy + j) : g + (2 * fx + xz));
+            w[v][3] = *(y < d.y - 1 ? u + (o + sy + j) : g + (2 * fx + fy + xz));
+            w[v][4] = *(z > 0 ? u + (o + ((unsigned)(z - 1) >> 1)) : g + (2 * (fx + fy) + xy));
+            w[v][5] = *(z < d.z - 1 ? u + (o + ((unsigned)(z + 1) >> 1)) : g + (2 * (fx + fy) + fz + xy));
+            w[v][6] = u[i];
+            w[v][7] = f[i];
+            cov[v] = in_box(cb, x, y, z);
+        }
+#pragma unroll
+        for (int v = 0; v < kRedV; ++v) {
+            const unsigned i = b0 + v * blockDim.x;
+            if (i >= rr.hi) break;
+            const T s = ((w[v][0] + w[v][1]) + (w[v][2] + w[v][3])) + (w[v][4] + w[v][5]);
+            const T r = w[v][7] - (s - T(6) * w[v][6]) / h2;
+            if (!cov[v]) acc += (double)r * (double)r;
+            if (rout) rout[i] = cov[v] ? R(0) : (R)r;
+        }
+    }
+    const double bs = block_sum(acc);
+    if (threadIdx.x == 0) partials[blockIdx.x] = bs;
+}
+
 // the same on a colour-split periodic level, r written in the same layout; neighbour rows are
 // addressed directly (identical arithmetic, so identical bits)
 template <class T, class R>
@@ -1522,7 +1569,9 @@ void launch_residual(const T* u, const T* f, const T* ghosts, Lay L, double h, C
                      double* partials, int* nparts, hipStream_t st) {
     const int g = grid_for(L.d.cells(), kBlock * kRedV, kMaxPartials);
     const T h2 = (T)(h * h);
-    if (ghosts)
+    if (ghosts && L.split && (!rout || LR.split))
+        k_residual_gh<T, R><<<g, kBlock, 0, st>>>(u, f, ghosts, L, h2, cov, rout, partials);
+    else if (ghosts)
         k_residual<T, R, true><<<g, kBlock, 0, st>>>(u, f, ghosts, L, h2, cov, rout, LR, partials);
     else if (L.split && (!rout || LR.split))
         k_residual_split<T, R><<<g, kBlock, 0, st>>>(u, f, L, h2, cov, rout, partials);
