@@ -12,8 +12,8 @@ defect-correction loop); the plain FP64 path is timed beside it.
 
 Prints ONE JSON line.  `value` is cell-updates per second of the headline path (smoother
 cell-updates summed over all levels and both solves, divided by the step time).  `roofline`
-is the finest-level smoother kernel: algorithmic bytes (3 words per cell-update) over its
-average launch duration, timed with HIP events on its own stream inside the timed region;
+is the finest-level smoother kernel (two red-black sweeps per launch): algorithmic bytes (2.5 words
+per cell: one colour of u and f read, both colours written) over its average launch duration, timed with HIP events on its own stream inside the timed region;
 `traffic` is its HBM bytes per launch from the recorded rocprofv3 counter passes (null when the
 kernel sources no longer match the ones the counters were taken on).
 """
@@ -58,7 +58,7 @@ def parse():
 # HBM traffic of the finest-level smoother, from the rocprofv3 FETCH_SIZE / WRITE_SIZE passes
 # recorded under profiles/; it stands only while the kernel sources hash to the recorded value.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_rbgs_vec_f32_256.md")
-KERNEL_SOURCES = ("k_levels.hip", "mg_internal.h", "fastdiv.h", "p2_bodies.h")   # the smoother's sources
+KERNEL_SOURCES = ("k_sweeps.hip", "sweep_bodies.h", "mg_internal.h", "div6.h", "p2_bodies.h")   # the smoother's
 
 
 def kernel_source_hash():
@@ -296,9 +296,8 @@ def time_lla(mg, torch, H, psi1, psi2, reps=10):
 def time_highorder(mg, torch, ft, h, tol, reps=3):
     """The solve with the 4th- and 6th-order Laplacians of Table 1 (13 and 19 points), FP64, on the
     step's density: median of `reps` solves after one warm-up, HIP events on the launch stream,
-    and the finest half-sweep timed by the library's events.  That half-sweep is out of place:
-    per cell it reads the iterate and f and writes every cell, 24 B (the colour-split in-place
-    half-sweep of the 7-point path moves 12 B per cell, its updated half only)."""
+    and the finest sweep (both half-sweeps in one launch) timed by the library's events.  It is out of
+    place: per cell it reads the iterate and f and writes every cell, 24 B."""
     n = ft.shape[0]
     res = dict(workload="periodic %d^3 BBKS, V(2,2) with the order-4 / order-6 Laplacian, tol %g; FP64, and mixed "
                         "(FP32 inner cycles inside FP64 defect correction)" % (n, tol))
@@ -333,9 +332,9 @@ def time_highorder(mg, torch, ft, h, tol, reps=3):
         res["order%d" % order] = dict(ms_per_solve=round(ms, 3), cycles=st["cycles"], rel_res=st["rel_res"],
                                       rel_rms_vs_exact=_rel_zero_mean(torch, u64, exact),
                                       value=round(st["cell_updates"] / (ms * 1e-3) / 1e6, 1),
-                                      unit="Mcell-updates/s", half_sweep_avg_us=round(us, 2),
-                                      half_sweep_launches=kn,
-                                      half_sweep_gbs=round(kb / max(kn, 1) / (us * 1e-6) / 1e9, 1) if kn else None)
+                                      unit="Mcell-updates/s", sweep_avg_us=round(us, 2),
+                                      sweep_launches=kn,
+                                      sweep_gbs=round(kb / max(kn, 1) / (us * 1e-6) / 1e9, 1) if kn else None)
         om = _opts(mg, tol=tol, max_cycles=60, prec="mixed")
         tm = []
         for i in range(reps + 1):
@@ -400,22 +399,22 @@ def time_highorder_zoom(mg, torch, reps=2):
 
 
 def spectral_bytes(n, P, what):
-    """Algorithmic HBM bytes of one call of the three-pass FFT pipeline on an n-cell field
+    """Algorithmic HBM bytes of one call of the three-pass FFT pipeline on an n-cell real field
     transformed on P points per axis (P = n periodic, the padded length isolated): every pass
-    reads and writes each stored complex point once (16 B); the first pass reads the real field
-    (8 B), the last writes real outputs (8 B each, read and written when added).  what: "deconv"
-    (one multiplier, one output) or "hybrid" (two multiplier passes: x+iy and z, added to three
-    outputs)."""
+    reads and writes each stored complex point once (16 B; the modes kz = 0 .. P2 / 2 only); the
+    first pass reads the real field (8 B), the last writes real outputs (8 B each, read and written
+    when added).  what: "deconv" (one multiplier, one output) or "hybrid" (the x pass writes three
+    components, added to three outputs)."""
     n0, n1, n2 = n
     p0, p1, p2 = P
-    w1 = n0 * n1 * p2
-    w2 = n0 * p1 * p2
+    zs = p2 // 2 + 1
+    w1 = 16 * n0 * n1 * zs
+    w2 = 16 * n0 * p1 * zs
     cells = n0 * n1 * n2
-    fwd = 8 * cells + 16 * w1 + 16 * w1 + 16 * w2          # z pass (real in), y pass
-    mid = 16 * w2 + 16 * w2 + 16 * w2 + 16 * w1            # x pass fused, y inverse
+    fwd = 8 * cells + w1 + w1 + w2                         # z pass (real in), y pass
     if what == "deconv":
-        return fwd + mid + 16 * w1 + 8 * cells
-    return fwd + 2 * mid + (16 * w1 + 32 * cells) + (16 * w1 + 16 * cells)
+        return fwd + 2 * w2 + (w2 + w1) + (w1 + 8 * cells)   # x pass fused, y and z inverse
+    return fwd + 4 * w2 + 3 * (w2 + w1) + 3 * (w1 + 16 * cells)
 
 
 def time_spectral(mg, torch, ft, reps=5):

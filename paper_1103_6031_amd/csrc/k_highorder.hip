@@ -15,6 +15,8 @@
 // mixed-precision solve, whose FP64 residual (k_ho_resid32) and correction (k_ho_add32) are
 // separate kernels.  The FP64 arithmetic is the oracle's up to summation order.
 
+#include <hip/hip_ext.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -782,12 +784,13 @@ static void launch_ho_sweep_tile(const T* in, T* out, const T* f, int lg, double
     const int R = order / 2, n = 1 << lg;
     const unsigned grid = (unsigned)((n / tl.yr) * (n / (2 * tl.zp)) * (n / tl.cx)), lds = ho_sweep_lds<T>(tl, R);
     const unsigned block = (unsigned)((tl.yr + 4 * R) * (tl.zp + 2 * R) + 63) / 64 * 64;
-    if (ea) (void)hipEventRecord(ea, st);
-    auto run = [&](auto kernel) { kernel<<<grid, block, lds, st>>>(in, out, f, lg, (T)(h * h), tl); };
+    auto run = [&](auto kernel) {
+        if (ea) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, st, ea, eb, 0, in, out, f, lg, (T)(h * h), tl);
+        else kernel<<<grid, block, lds, st>>>(in, out, f, lg, (T)(h * h), tl);
+    };
     if (R == 1) run(k_ho_sweep<1, T>);
     else if (R == 2) run(k_ho_sweep<2, T>);
     else run(k_ho_sweep<3, T>);
-    if (eb) (void)hipEventRecord(eb, st);
 }
 
 // The tile: the least of rounds x steps x time of a step (2.2 + the waves per SIMD), blocks sharing 256 CUs
