@@ -64,23 +64,19 @@ __device__ __forceinline__ unsigned sidx(int lg, unsigned x, unsigned y, unsigne
     return ((((x << lg) | y) << lg) + (((x + y + z) & 1u) << (lg - 1))) + (z >> 1);
 }
 
-// steps 3-5 for the coarse cell t = (X, Y, Z) (natural order) of a periodic colour-split
-// power-of-two cube of fine edge 2^lg: the 8 children's residuals and values summed in the order
+// steps 3-5 for the coarse cell t = (X, Y, Z) (natural order) of a periodic colour-split cube with half-rows
+// of nzh cells: the 8 children's residuals and values summed in the order
 // (a, b, e), the order of the generic residual-restriction, so the bits are the same.  The
 // children and their neighbours span the fine rows (2X + a, 2Y + b) at z = 2Z - 1 .. 2Z + 2, and
 // the rows one step outside in x and in y at z = 2Z, 2Z + 1; in a row whose even-z cells are
 // colour p, z = 2Z and 2Z + 2 are entries Z and Z + 1 of half p, z = 2Z - 1 and 2Z + 1 entries
-// Z - 1 and Z of the other half.
-template <class T>
-__device__ __forceinline__ void cell_resid_restrict_p2(const T* __restrict__ u, const T* __restrict__ f, int lg, T h2,
-                                                       T* __restrict__ pu, T* __restrict__ pf, T* __restrict__ uold,
-                                                       unsigned t) {
-    const int lc = lg - 1;
-    const unsigned nc = 1u << lc, mc = nc - 1, m = (1u << lg) - 1, nzh = nc;
-    const unsigned X = t >> (2 * lc), Y = (t >> lc) & mc, Z = t & mc;
-    const unsigned x0 = 2 * X, y0 = 2 * Y;
-    const unsigned Zm = (Z - 1) & mc, Zp = (Z + 1) & mc;
-    auto rowb = [&](unsigned x, unsigned y) { return (((x & m) << lg) | (y & m)) << lg; };
+// Z - 1 and Z of the other half.  xs, ys: the fine rows 2X - 1 .. 2X + 2 and 2Y - 1 .. 2Y + 2, wrapped, as are the
+// entries Zm and Zp; rowb(x, y): the position of a row; P: the coarse cell's.
+template <class T, class Row>
+__device__ __forceinline__ void body_resid_restrict(const T* __restrict__ u, const T* __restrict__ f, unsigned nzh,
+                                                    const unsigned (&xs)[4], const unsigned (&ys)[4], unsigned Z,
+                                                    unsigned Zm, unsigned Zp, Row rowb, T h2, T* __restrict__ pu,
+                                                    T* __restrict__ pf, T* __restrict__ uold, unsigned P, unsigned t) {
     auto half = [&](unsigned x, unsigned y, unsigned zpar) {   // offset of the half holding parity zpar
         return ((x + y + zpar) & 1u) * nzh;
     };
@@ -90,7 +86,7 @@ __device__ __forceinline__ void cell_resid_restrict_p2(const T* __restrict__ u, 
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const unsigned x = x0 + a, y = y0 + b, rb = rowb(x, y);
+            const unsigned x = xs[1 + a], y = ys[1 + b], rb = rowb(x, y);
             const unsigned he = half(x, y, 0), ho = half(x, y, 1);
             cm[a][b] = u[rb + ho + Zm];
             c0[a][b] = u[rb + he + Z];
@@ -106,12 +102,12 @@ __device__ __forceinline__ void cell_resid_restrict_p2(const T* __restrict__ u, 
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             {
-                const unsigned x = sd ? x0 + 2 : x0 - 1, y = y0 + k, rb = rowb(x, y);
+                const unsigned x = xs[sd ? 3 : 0], y = ys[1 + k], rb = rowb(x, y);
                 xf[sd][k][0] = u[rb + half(x, y, 0) + Z];
                 xf[sd][k][1] = u[rb + half(x, y, 1) + Z];
             }
             {
-                const unsigned x = x0 + k, y = sd ? y0 + 2 : y0 - 1, rb = rowb(x, y);
+                const unsigned x = xs[1 + k], y = ys[sd ? 3 : 0], rb = rowb(x, y);
                 yf[sd][k][0] = u[rb + half(x, y, 0) + Z];
                 yf[sd][k][1] = u[rb + half(x, y, 1) + Z];
             }
@@ -137,10 +133,36 @@ __device__ __forceinline__ void cell_resid_restrict_p2(const T* __restrict__ u, 
                 su = su + ui;
             }
     const T uc = su * T(0.125);
-    const unsigned P = sidx(lc, X, Y, Z);
     pu[P] = uc;
     pf[P] = sr * T(0.125);
     uold[t] = uc;
+}
+// the same for a power-of-two cube of fine edge 2^lg
+template <class T>
+__device__ __forceinline__ void cell_resid_restrict_p2(const T* __restrict__ u, const T* __restrict__ f, int lg, T h2,
+                                                       T* __restrict__ pu, T* __restrict__ pf, T* __restrict__ uold,
+                                                       unsigned t) {
+    const int lc = lg - 1;
+    const unsigned nc = 1u << lc, mc = nc - 1, m = (1u << lg) - 1;
+    const unsigned X = t >> (2 * lc), Y = (t >> lc) & mc, Z = t & mc;
+    const unsigned xs[4] = {(2 * X - 1) & m, 2 * X, 2 * X + 1, (2 * X + 2) & m};
+    const unsigned ys[4] = {(2 * Y - 1) & m, 2 * Y, 2 * Y + 1, (2 * Y + 2) & m};
+    body_resid_restrict<T>(u, f, nc, xs, ys, Z, (Z - 1) & mc, (Z + 1) & mc,
+                           [&](unsigned x, unsigned y) { return ((x << lg) | y) << lg; }, h2, pu, pf, uold,
+                           sidx(lc, X, Y, Z), t);
+}
+// and for a cube of fine edge n, n divisible by 4 (the coarse level is colour-split too); C: the coarse level
+template <class T>
+__device__ __forceinline__ void cell_resid_restrict_cube(const T* __restrict__ u, const T* __restrict__ f, unsigned n,
+                                                         const Lay& C, T h2, T* __restrict__ pu, T* __restrict__ pf,
+                                                         T* __restrict__ uold, unsigned t) {
+    const unsigned nc = n >> 1, row = C.dz.div(t), Z = t - row * nc, X = C.dy.div(row), Y = row - X * nc;
+    auto edge = [&](unsigned a) { return a == n ? 0u : a; };
+    const unsigned xs[4] = {(X ? 2 * X : n) - 1, 2 * X, 2 * X + 1, edge(2 * X + 2)};
+    const unsigned ys[4] = {(Y ? 2 * Y : n) - 1, 2 * Y, 2 * Y + 1, edge(2 * Y + 2)};
+    body_resid_restrict<T>(u, f, nc, xs, ys, Z, (Z ? Z : nc) - 1, Z + 1 == nc ? 0u : Z + 1,
+                           [&](unsigned x, unsigned y) { return (x * n + y) * n; }, h2, pu, pf, uold,
+                           row * nc + ((X + Y + Z) & 1u) * (nc >> 1) + (Z >> 1), t);
 }
 
 // Step 6 on a whole periodic colour-split power-of-two level (edge 2^lg) for the run ch: the
