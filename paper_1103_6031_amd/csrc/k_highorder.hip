@@ -1725,17 +1725,18 @@ static HoTile hoz_half_tile(const HozPatch& P, int R) {
     double least = 1e30;
     auto cdiv = [](int a, int b) { return (a + b - 1) / b; };
     const int n0 = P.n[0], n1 = P.n[1], n2h = P.n[2] / 2, J = (R + 1) / 2;
-    for (int tz = 1; tz <= n2h && tz <= 32; ++tz) {
+    const int tz0 = cdiv(n2h, 32), ty0 = cdiv(n1, 48);   // (a short search: it runs at every launch)
+    for (int tz = tz0; tz <= n2h && tz <= tz0 + 4; ++tz) {
         const int zp = cdiv(n2h, tz);
-        if (zp > 32 || cdiv(n2h, zp) != tz) continue;
-        for (int ty = 1; ty <= n1; ++ty) {
+        if (cdiv(n2h, zp) != tz) continue;
+        for (int ty = ty0; ty <= ty0 + 12; ++ty) {
             const int yr = cdiv(n1, ty);
-            if (yr > 48 || cdiv(n1, yr) != ty) continue;
-            if (yr < 8 && ty > 1) break;
+            if (cdiv(n1, yr) != ty) continue;
+            if (yr < 8 && ty > ty0) break;
             const int cells = (yr + 2 * R) * (zp + 2 * J), waves = cdiv(cells, 64);
             if (cells > 1024) continue;
             const int fit = 16 / waves;
-            for (int k = 1; k <= 8; ++k) {
+            for (int k = 1; k <= 4; ++k) {
                 int cx = std::max(4, cdiv(n0, std::max(1, 256 * k / (ty * tz))));
                 cx = std::min(n0, cdiv(n0, cdiv(n0, cx)));
                 const int blocks = ty * tz * cdiv(n0, cx), q = cdiv(blocks, 256), m = std::min(q, fit);

@@ -32,6 +32,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <map>
 #include <type_traits>
 
 #include "mg_internal.h"
@@ -176,8 +177,8 @@ __device__ __forceinline__ void body_two_sweeps(const T* __restrict__ u, const T
 // Tiles of up to kSmallCells runs take their LDS at the launch, so that several blocks share a CU; larger
 // ones, one block per CU by their registers, from a fixed array (a launch may ask for 64 KB only, unless
 // the function's attribute is raised, which a stream capture would have to come after).
-constexpr int kSmallCells = 448;
-static_assert(kSlots * kSmallCells * 16 <= 65536 && kSlots * kMaxThreads * 16 <= 160 * 1024, "LDS of a block");
+constexpr int kSmallCells = 448, kManyCells = 256;
+static_assert(kManyCells <= kSmallCells && kSlots * kSmallCells * 16 <= 65536 && kSlots * kMaxThreads * 16 <= 160 * 1024, "LDS of a block");
 extern __shared__ __align__(16) unsigned char sweep_smem[];
 template <class V, bool BIG>
 __device__ __forceinline__ V* sweep_lds() {
@@ -196,8 +197,9 @@ k_two_sweeps(const T* __restrict__ u, const T* __restrict__ f, T* __restrict__ o
     body_two_sweeps<T, MODE>(u, f, out, n, sh, h2, pu, uold, blockIdx.x, gridDim.x, sweep_lds<V16<T>, BIG>());
 }
 
-// the same for the levels of many batched instances: a = {u, f, out, pu, uold}, the tile in C's dims
-template <class T, int MODE, bool BIG>
+// the same for the levels of many batched instances: a = {u, f, out, pu, uold}, the tile in C's dims (tiles of
+// many levels are small)
+template <class T, int MODE>
 __global__ void __launch_bounds__(kMaxThreads)
 kb_two_sweeps(const BSeg* __restrict__ segs, int nseg, const int* __restrict__ active) {
     unsigned lb;
@@ -205,7 +207,7 @@ kb_two_sweeps(const BSeg* __restrict__ segs, int nseg, const int* __restrict__ a
     if (!active[s.inst]) return;
     body_two_sweeps<T, MODE>((const T*)s.a[0], (const T*)s.a[1], (T*)s.a[2], s.L.d.x,
                              SweepShape{s.C.d.x, s.C.d.y, s.C.d.z}, (T)(s.h * s.h), (const T*)s.a[3],
-                             (const T*)s.a[4], lb, s.nblk, sweep_lds<V16<T>, BIG>());
+                             (const T*)s.a[4], lb, s.nblk, sweep_lds<V16<T>, false>());
 }
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -230,18 +232,18 @@ unsigned sweep_blocks(int n, int W, const SweepShape& s) {
 // many: the level is one of many in a launch, so the CUs are full and the time per cell counts; blocks of four
 // waves and at most 16 planes, three to a CU, leave the launch's end short (64 instances of 32^3 - 128^3, FP32,
 // per solve: 9.71 ms; 12 waves 10.56 ms; up to 32 planes 10.00 ms, 8 planes 9.98 ms).
-SweepShape sweep_shape(int n, int W, bool many) {
+static SweepShape find_shape(int n, int W, bool many) {
     SweepShape best;
     double least = 1e30;
     const int nr = n / (2 * W);
-    for (int tz = 1; tz <= nr && tz <= 16; ++tz) {
+    for (int tz = 1; tz <= nr && tz <= 32; ++tz) {
         const int zr = cdiv(nr, tz);
         if (cdiv(nr, zr) != tz) continue;
         for (int yr = 8; yr <= 48 && yr <= n; ++yr) {
             const int ty = cdiv(n, yr);
             if (yr > 8 && cdiv(n, yr - 1) == ty) continue;   // the least rows for ty tiles
             const SweepShape tile{yr, zr, 0};
-            if (sweep_cells(tile) > (many ? 256 : kMaxThreads)) continue;
+            if (sweep_cells(tile) > (many ? kManyCells : kMaxThreads)) continue;
             const int waves = cdiv(sweep_cells(tile), 64), fit = 12 / waves;
             for (int k = 1; k <= 8; ++k) {                   // k blocks per CU
                 int cx = many ? std::min(n, 2 * k) : std::max(4, cdiv(n, std::max(1, 256 * k / (ty * tz))));
@@ -258,6 +260,13 @@ SweepShape sweep_shape(int n, int W, bool many) {
         }
     }
     return best;
+}
+// (the search takes up to 20 us of the host's time: kept per thread for the few sizes there are)
+SweepShape sweep_shape(int n, int W, bool many) {
+    static thread_local std::map<int, SweepShape> found;
+    SweepShape& s = found[(n * 8 + W) * 2 + many];
+    if (!s.yr) s = find_shape(n, W, many);
+    return s;
 }
 
 template <class T>
@@ -280,13 +289,12 @@ void launch_two_sweeps(const T* u, const T* f, T* out, const Lay& L, double h, i
 template <class T>
 void launch_b_two_sweeps(const BSeg* segs, int nseg, unsigned grid, int cells, const int* active, int mode,
                          hipStream_t st) {
-    const bool big = cells > kSmallCells;
-    const unsigned lds = big ? 0u : (unsigned)(kSlots * cells) * 16u;
+    const unsigned lds = (unsigned)(kSlots * cells) * 16u;
     const dim3 block((unsigned)cdiv(cells, 64) * 64u);
     auto run = [&](auto kernel) { kernel<<<grid, block, lds, st>>>(segs, nseg, active); };
-    if (mode == kSweepPlain) big ? run(kb_two_sweeps<T, kSweepPlain, true>) : run(kb_two_sweeps<T, kSweepPlain, false>);
-    else if (mode == kSweepCorr) big ? run(kb_two_sweeps<T, kSweepCorr, true>) : run(kb_two_sweeps<T, kSweepCorr, false>);
-    else big ? run(kb_two_sweeps<T, kSweepRed, true>) : run(kb_two_sweeps<T, kSweepRed, false>);
+    if (mode == kSweepPlain) run(kb_two_sweeps<T, kSweepPlain>);
+    else if (mode == kSweepCorr) run(kb_two_sweeps<T, kSweepCorr>);
+    else run(kb_two_sweeps<T, kSweepRed>);
 }
 
 template void launch_b_two_sweeps<float>(const BSeg*, int, unsigned, int, const int*, int, hipStream_t);
