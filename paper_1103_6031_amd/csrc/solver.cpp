@@ -1244,6 +1244,15 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
             const size_t cells = L.d.cells();
             const Lay C(Dims{L.d.x / 2, L.d.y / 2, L.d.z / 2}, 0);
             BSeg s;
+            // step 6 on the next level, after this one's residual and restriction; a fused level does its own
+            auto step6 = [&] {
+                s = seg0(i, fas_blocks(C, L.pm, (int)sizeof(T)));
+                s.C = C;
+                s.pm = L.pm;
+                s.h = Q.h;
+                s.a[0] = q.u; s.a[1] = q.f;
+                fa.push_back(s);
+            };
             if (fused<T>(P, d)) {
                 s = seg0(i, level_tiles(L.d.x));
                 s.L = L.lay;
@@ -1253,6 +1262,8 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
                 pre.push_back(s);
                 s.a[0] = b.ua; s.a[1] = b.fa; s.a[2] = q.u; s.a[3] = b.uold; s.a[4] = b.u;
                 post.push_back(s);
+                // (the tail below a fused level does its own too: fas0)
+                if (d + 1 < P.tail && !fused<T>(P, d + 1)) step6();
                 continue;
             }
             T* u1 = u;   // where the pre-smoothed u is
@@ -1284,14 +1295,7 @@ static void vcycle_tables(BatchPlan& B, int ti, int par, const std::vector<T*>& 
             s.h = L.h;
             s.a[0] = u1; s.a[1] = b.f; s.a[2] = q.u; s.a[3] = q.f; s.a[4] = b.uold;
             rr.push_back(s);
-            if (!fused<T>(P, d + 1)) {   // a fused level does its own step 6
-                s = seg0(i, fas_blocks(C, L.pm, (int)sizeof(T)));
-                s.C = C;
-                s.pm = L.pm;
-                s.h = Q.h;
-                s.a[0] = q.u; s.a[1] = q.f;
-                fa.push_back(s);
-            }
+            if (!fused<T>(P, d + 1)) step6();
             if (u1 != u) continue;       // the sweeps add the correction
             s = seg0(i, B.P[i].nu2 > 0 ? prolong_black_blocks(L.lay, L.pm, (int)sizeof(T)) : cdiv(cells, kBlock));
             s.L = L.lay;
