@@ -90,6 +90,7 @@ struct Plan {
     int nu1 = 2, nu2 = 2;
     int tail = -1;   // first level of the single-workgroup tail V-cycle (-1: none)
     bool mixed = false;
+    bool pair_e = false;         // the finest level has second arrays for the fused mixed-precision outer step
     double* partials = nullptr;  // kMaxPartials per level segment
     double* scal = nullptr;      // device scalars
 };
@@ -184,6 +185,7 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
         Q.child.lo[0] = L.pm.off[0]; Q.child.lo[1] = L.pm.off[1]; Q.child.lo[2] = L.pm.off[2];
         Q.child.n[0] = L.d.x / 2; Q.child.n[1] = L.d.y / 2; Q.child.n[2] = L.d.z / 2;
     }
+    P.pair_e = P.mixed && P.nh == 1 && P.L[0].lay.split && P.L[0].d.cells() > kTailMaxCells;
     for (int l = 0; l <= P.last; ++l) {
         Level& L = P.L[l];
         const size_t n = L.d.cells();
@@ -199,7 +201,7 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
             L.f32 = cv.take<float>(n);
             if (!L.periodic) L.g32 = cv.take<float>(ghost_cells(L.d));
             if (l < P.last) L.uold32 = cv.take<float>(n / 8);
-            if (l == 0 && P.nh == 1 && L.lay.split && n > kTailMaxCells) {
+            if (P.pair_e && l == 0) {
                 L.ualt = cv.take<double>(n);
                 L.ealt = cv.take<float>(n);
             }
@@ -245,7 +247,7 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
             const size_t c = L.d.cells(), bytes = c * elem + 256;
             if (L.periodic ? L.fusable || c <= kTailMaxCells || !two_sweeps_ok(L.lay, elem) : !patch_sweeps_ok(L.lay, elem))
                 continue;
-            if (P.mixed && L.ealt) L.us32 = L.ealt;
+            if (P.pair_e && l == 0) L.us32 = L.ealt;   // (null in a size query, like every array)
             else if (cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) continue;
             else if (P.mixed) L.us32 = cv.take<float>(c);
             else L.us = cv.take<double>(c);
@@ -735,11 +737,11 @@ static int solve(const mg_hier* H, const double* const* f, double* const* u, con
     int rc = build_plan(H, o, size_cv, u, P);
     if (rc) return rc;
     const size_t need = size_cv.off;
-    // a workspace (or the static scratch array) without room for the fused levels that are no power
-    // of two runs them as one-step launches (same bits)
+    // a workspace (or the static scratch array) without room for the second arrays runs half-sweeps, and the
+    // fused levels that are no power of two, or all of them, as one-step launches (same bits)
     Fuse fuse = kFuseAll;
-    if (ws_bytes < need) {
-        fuse = kFuseP2;
+    while (ws_bytes < size_cv.off && fuse != kFuseNone) {
+        fuse = fuse == kFuseAll ? kFuseP2 : kFuseNone;
         size_cv = Carver(nullptr);
         build_plan(H, o, size_cv, u, P, fuse);
     }
