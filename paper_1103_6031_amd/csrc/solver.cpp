@@ -76,8 +76,9 @@ struct Level {
     bool fusable = false;
     double *ua = nullptr, *fa = nullptr;
     float *ua32 = nullptr, *fa32 = nullptr;
-    // second u of a level smoothed by k_two_sweeps (between its pre and post smoothing); where the fused
-    // outer step's second e is free, that
+    // second u of a level smoothed by k_two_sweeps or k_patch_sweeps, between its pre and post smoothing: the
+    // fused outer step's second e, the first u of the level above, or an array of its own (build_plan)
+    bool swept = false;
     double* us = nullptr;
     float* us32 = nullptr;
     SweepShape sweep;   // its tile, chosen at the first use
@@ -238,8 +239,11 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
         }
     P.partials = cv.take<double>((size_t)kMaxPartials * (P.nh + 1));
     P.scal = cv.take<double>(S_COUNT);
-    // the second u of patches and the other periodic levels, for smoothing in one launch; a plan that fits the static
-    // scratch array keeps fitting it, without the arrays that do not
+    // The second u of patches and the other periodic levels, for smoothing in one launch.  Between its pre and its
+    // post smoothing a level's iterate is in its second u, and nothing reads its first: a level that is no
+    // larger than the swept one above it takes that array (not the finest level's of the mixed outer step,
+    // whose pair changes places).  A plan that fits the static scratch array keeps fitting it, without the
+    // arrays that do not.
     if (fuse == kFuseAll)
         for (int l = 0; l < P.last; ++l) {
             Level& L = P.L[l];
@@ -247,10 +251,20 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
             const size_t c = L.d.cells(), bytes = c * elem + 256;
             if (L.periodic ? L.fusable || c <= kTailMaxCells || !two_sweeps_ok(L.lay, elem) : !patch_sweeps_ok(L.lay, elem))
                 continue;
-            if (P.pair_e && l == 0) L.us32 = L.ealt;   // (null in a size query, like every array)
-            else if (cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) continue;
-            else if (P.mixed) L.us32 = cv.take<float>(c);
-            else L.us = cv.take<double>(c);
+            const Level* Q = l > 0 ? &P.L[l - 1] : nullptr;
+            if (P.pair_e && l == 0) {
+                L.us32 = L.ealt;
+            } else if (Q && Q->swept && !(P.pair_e && l == 1) && Q->d.cells() >= c) {
+                if (P.mixed) L.us32 = Q->u32;
+                else L.us = Q->u;
+            } else if (cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) {
+                continue;
+            } else if (P.mixed) {
+                L.us32 = cv.take<float>(c);
+            } else {
+                L.us = cv.take<double>(c);
+            }
+            L.swept = true;
         }
     return MG_OK;
 }
