@@ -136,9 +136,10 @@ static int validate_hier(const mg_hier* H) {
     return MG_OK;
 }
 
-// which small coarsenings get the second arrays of the fused tile kernels: none, the power-of-two
-// cubes, or every one that fits those kernels
-enum Fuse { kFuseNone, kFuseP2, kFuseAll };
+// which second arrays a plan has.  Of the fused tile kernels: none, the power-of-two cubes', or those of every
+// coarsening that fits the kernels (kFuseAll and kFuseEvery); of the sweeps in one launch: with kFuseAll those that
+// leave a plan that fits the static scratch array within it, with kFuseEvery all
+enum Fuse { kFuseNone, kFuseP2, kFuseAll, kFuseEvery };
 
 // Build the level list and carve buffers.  u_user / f_user may be null (size query).
 static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* const* u_user, Plan& P,
@@ -242,9 +243,10 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
     // The second u of patches and the other periodic levels, for smoothing in one launch.  Between its pre and its
     // post smoothing a level's iterate is in its second u, and nothing reads its first: a level that is no
     // larger than the swept one above it takes that array (not the finest level's of the mixed outer step,
-    // whose pair changes places).  A plan that fits the static scratch array keeps fitting it, without the
-    // arrays that do not.
-    if (fuse == kFuseAll)
+    // whose pair changes places).  The size that the query gives (kFuseAll) stays within the static scratch array
+    // where the plan without these arrays fits it, so that it still says whether the allocation-free call
+    // takes the problem; a caller with more room gets them all.
+    if (fuse >= kFuseAll)
         for (int l = 0; l < P.last; ++l) {
             Level& L = P.L[l];
             const size_t elem = P.mixed ? sizeof(float) : sizeof(double);
@@ -257,7 +259,7 @@ static int build_plan(const mg_hier* H, const mg_opts* o, Carver& cv, double* co
             } else if (Q && Q->swept && !(P.pair_e && l == 1) && Q->d.cells() >= c) {
                 if (P.mixed) L.us32 = Q->u32;
                 else L.us = Q->u;
-            } else if (cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) {
+            } else if (fuse == kFuseAll && cv.off <= MG_SCRATCH_BYTES && cv.off + bytes > MG_SCRATCH_BYTES) {
                 continue;
             } else if (P.mixed) {
                 L.us32 = cv.take<float>(c);
@@ -748,16 +750,16 @@ static int solve(const mg_hier* H, const double* const* f, double* const* u, con
     }
     Plan P;
     Carver size_cv(nullptr);
-    int rc = build_plan(H, o, size_cv, u, P);
-    if (rc) return rc;
-    const size_t need = size_cv.off;
     // a workspace (or the static scratch array) without room for the second arrays runs half-sweeps, and the
     // fused levels that are no power of two, or all of them, as one-step launches (same bits)
-    Fuse fuse = kFuseAll;
-    while (ws_bytes < size_cv.off && fuse != kFuseNone) {
-        fuse = fuse == kFuseAll ? kFuseP2 : kFuseNone;
+    int rc = MG_OK;
+    size_t need = 0;
+    Fuse fuse = kFuseEvery;
+    for (;; fuse = (Fuse)(fuse - 1)) {
         size_cv = Carver(nullptr);
-        build_plan(H, o, size_cv, u, P, fuse);
+        if ((rc = build_plan(H, o, size_cv, u, P, fuse))) return rc;
+        if (fuse == kFuseAll) need = size_cv.off;
+        if (ws_bytes >= size_cv.off || fuse == kFuseNone) break;
     }
     if (!ws || ws_bytes < size_cv.off) return fail(MG_EINVAL, "workspace too small: need " + std::to_string(need));
     if (((uintptr_t)ws) & 255) return fail(MG_EINVAL, "workspace must be 256-byte aligned");
@@ -1680,11 +1682,13 @@ static int solve_batch(int ninst, const int* n, const double* h, const double* c
         if (!f[i] || !u[i]) return fail(MG_EINVAL, "instance pointer is NULL");
     BatchPlan B;
     std::vector<size_t> slice, sbytes;
-    const size_t need = batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes);
-    if (!need) return MG_EINVAL;   // build_plan reported the reason
-    // a workspace without room for the fused levels' second arrays runs one-step launches (same bits)
-    const Fuse fuse = ws_bytes < need ? kFuseNone : kFuseAll;
-    const size_t least = fuse == kFuseAll ? need : batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes, fuse);
+    // a workspace without room for the second arrays runs one-step launches (same bits); one with more room
+    // than the query's gets them all
+    Fuse fuse = kFuseEvery;
+    size_t least = batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes, fuse), need = least;
+    if (!least) return MG_EINVAL;   // build_plan reported the reason
+    if (ws_bytes < least) need = least = batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes, fuse = kFuseAll);
+    if (ws_bytes < least) least = batch_layout(ninst, n, h, o, nullptr, B, slice, sbytes, fuse = kFuseNone);
     if (!ws || ws_bytes < least) return fail(MG_EINVAL, "workspace too small: need " + std::to_string(need));
     if (((uintptr_t)ws) & 255) return fail(MG_EINVAL, "workspace must be 256-byte aligned");
     if (int rc = refuse_capture(st, "the batched solve (it uploads tables and reads flags back)")) return rc;

@@ -46,3 +46,27 @@ def test_shared_arrays_match_the_half_sweeps(case, prec):
         assert stats["cycles"] == st.cycles
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+def test_more_room_than_the_query_asks_for_gives_every_second_array():
+    """FP64 160^3: with a second u of the finest level the plan would pass the static scratch array, so the query
+    leaves it out and the finest level takes half-sweeps; a workspace with room for it takes two sweeps a launch."""
+    import torch
+    from paper_1103_6031_amd import mgic
+    n, cycles = 160, 3
+    f = to_dev(np.random.default_rng(3).standard_normal((n,) * 3))
+    o = mgic.make_opts(fixed_cycles=True, max_cycles=cycles)
+    need = mgic.mg_workspace_bytes(mgic.Hier(n, 1.0), o)
+    got, launches = [], []
+    for room in (0, 8 * n ** 3 + 4096):
+        note("more room than the query: %d" % room)
+        mgic.mg_kprof_enable(1)
+        got.append(mgic.mg_solve_level(f, 1.0, opts=o, workspace=mgic.Workspace(need + room))[0])
+        launches.append(mgic.mg_kprof_read()[1])
+        mgic.mg_kprof_enable(0)
+    assert launches == [8 * cycles, 2 * cycles]
+    assert torch.equal(got[0], got[1])
+    note("more room than the query: batch")
+    ws = mgic.Workspace(mgic.mg_batch_workspace_bytes([n, n], o) + 2 * (8 * n ** 3 + 4096))
+    for u in mgic.mg_solve_batch([f, f], [1.0, 1.0], opts=o, workspace=ws)[0]:
+        assert torch.equal(u, got[0])
