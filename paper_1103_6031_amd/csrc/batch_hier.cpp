@@ -25,6 +25,8 @@
 namespace mgic {
 
 int report_error(int code, const char* msg);
+size_t plain_bytes(const mg_hier* H, const mg_opts* o);
+size_t plain_batch_bytes(int ninst, const int* n, const mg_opts* o);
 int solve_batch_codes(int ninst, const int* n, const double* h, const double* const* f, double* const* u,
                       const mg_opts* o, mg_stats* stats, int* codes, void* ws, size_t ws_bytes, hipStream_t st);
 
@@ -128,8 +130,10 @@ int check_opts(const mg_opts* o) {
     return MG_OK;
 }
 
-// sizes of every part; 0 (with the reason recorded) when an instance is invalid
-size_t layout(int ninst, const mg_hier* const* hier, const mg_opts* o, Layout& L) {
+// sizes of every part (plain: without the second arrays); 0 (with the reason recorded) when an instance is
+// invalid
+size_t layout(int ninst, const mg_hier* const* hier, const mg_opts* o, Layout& L, bool plain = false) {
+    L = Layout();
     if (ninst < 1 || !hier) {
         report_error(MG_EINVAL, "no instances");
         return 0;
@@ -154,12 +158,13 @@ size_t layout(int ninst, const mg_hier* const* hier, const mg_opts* o, Layout& L
         // a single-level description must be a valid hierarchy too (cubic base, positive h)
         for (int i : L.single)
             if (mg_workspace_bytes(hier[i], o) == 0) return 0;
-        L.batch_bytes = mg_batch_workspace_bytes((int)L.single.size(), L.n.data(), o);
+        const int k = (int)L.single.size();
+        L.batch_bytes = plain ? plain_batch_bytes(k, L.n.data(), o) : mg_batch_workspace_bytes(k, L.n.data(), o);
         if (!L.batch_bytes) return 0;
         off = up256(L.batch_bytes);
     }
     for (int i : L.multi) {
-        const size_t b = mg_workspace_bytes(hier[i], o);
+        const size_t b = plain ? plain_bytes(hier[i], o) : mg_workspace_bytes(hier[i], o);
         if (!b) {
             const std::string why = mg_last_error();
             report_error(MG_EINVAL, ("instance " + std::to_string(i) + ": " + why).c_str());
@@ -192,8 +197,10 @@ int solve_batch_hier(int ninst, const mg_hier* const* hier, const double* const*
             if (!f[i][p] || !u[i][p])
                 return report_error(MG_EINVAL, ("instance " + std::to_string(i) + ": level pointer is NULL").c_str());
     }
-    if (!ws || ws_bytes < need)
-        return report_error(MG_EINVAL, ("workspace too small: need " + std::to_string(need)).c_str());
+    // A workspace without room for the second arrays runs every part's plan without them (same bits).  A size within
+    // one unit of the carving (256 bytes) of the query's is a slip in the caller's rounding and is refused.
+    const bool fits = ws_bytes >= need || (ws_bytes + 256 <= need && layout(ninst, hier, o, L, true) <= ws_bytes);
+    if (!ws || !fits) return report_error(MG_EINVAL, ("workspace too small: need " + std::to_string(need)).c_str());
     if (((uintptr_t)ws) & 255) return report_error(MG_EINVAL, "workspace must be 256-byte aligned");
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) return report_error(MG_EHIP, "stream query failed");

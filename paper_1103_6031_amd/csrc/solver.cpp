@@ -2058,15 +2058,24 @@ int solve_batch_codes(int ninst, const int* n, const double* h, const double* co
     return solve_batch(ninst, n, h, f, u, o, stats, ws, ws_bytes, st, codes);
 }
 
-static size_t batch_bytes(int ninst, const int* n, const mg_opts* o) {
+static size_t batch_bytes(int ninst, const int* n, const mg_opts* o, Fuse fuse = kFuseAll) {
     if (ninst < 1 || !n) return 0;
     BatchPlan B;
     std::vector<double> h(ninst, 1.0);
     std::vector<size_t> slice, sbytes;
     mg_opts oo{};
     if (o) oo = *o;
-    return batch_layout(ninst, n, h.data(), o ? &oo : nullptr, nullptr, B, slice, sbytes);
+    return batch_layout(ninst, n, h.data(), o ? &oo : nullptr, nullptr, B, slice, sbytes, fuse);
 }
+
+// the sizes without the second arrays of the sweeps in one launch (and of the fused levels that are no power of
+// two; in a batch of any): what solves run in where there is no room for more, with the same bits
+size_t plain_bytes(const mg_hier* H, const mg_opts* o) {
+    Plan P;
+    Carver cv(nullptr);
+    return build_plan(H, o, cv, nullptr, P, kFuseP2) ? 0 : cv.off;
+}
+size_t plain_batch_bytes(int ninst, const int* n, const mg_opts* o) { return batch_bytes(ninst, n, o, kFuseNone); }
 
 }  // namespace mgic
 
