@@ -262,7 +262,8 @@ __device__ __forceinline__ bool line_at(const FftPass& A, long long L, int& a, i
 // One pass over lines of length N = 2^LGN, field blockIdx.y.  OP: kFftForward, kFftInverse; kFftRe
 // forward with the real part stored into a table; kFftFwdSymInv forward, multiply, inverse in one
 // launch; kFftHybrid the same with the three components of the hybrid correction, from one input
-// into fields 0, 1, 2 (the spectrum stays in registers between them).
+// into fields 0, 1, 2 (the spectrum stays in registers between them); kFftHybridOne with one of them, into a
+// field of its own.
 template <int LGN, int OP, int SYM>
 __global__ __launch_bounds__(kFftThreads<LGN>) void k_fft_lines(FftPass A) {
     constexpr int T = kFftThreads<LGN>, LGNL = kFftLgLines<LGN>, NL = 1 << LGNL, N = 1 << LGN;
@@ -333,8 +334,10 @@ __global__ __launch_bounds__(kFftThreads<LGN>) void k_fft_lines(FftPass A) {
                 rk[s] = -A.sym_scale / k2;
                 rl[s] = -A.sym_scale / ((A.tab_x[px + i] + A.tab_y[py + la[t]]) + A.tab_z[pz + lb[t]]);
             });
+            constexpr int kComps = OP == kFftHybrid ? 3 : 1;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
+            for (int k = 0; k < kComps; ++k) {
+                const int c = kComps == 3 ? k : A.comp;
                 each_point<LGN, LGNL, true, false, kLast, true, T>([&](int s, int l, int i) {
                     const int t = slot_line(s);
                     if (!ok[t]) return;
@@ -345,7 +348,7 @@ __global__ __launch_bounds__(kFftThreads<LGN>) void k_fft_lines(FftPass A) {
                     v[s] = make_double2(-f[s].y * m, f[s].x * m);
                 });
                 fft_regs<LGN, LGNL, true, true, T>(v, lds, twl);
-                store((double2*)A.out + (long long)c * A.fs);
+                store((double2*)A.out + (long long)k * A.fs);
             }
         }
     }
@@ -724,6 +727,7 @@ hipError_t launch_fft_lines(const FftPass& A, int op, int sym, hipStream_t st) {
     if (op == kFftInverse) return lines_of_length<kFftInverse, 0>(A, st);
     if (op == kFftRe) return lines_of_length<kFftRe, 0>(A, st);
     if (op == kFftHybrid) return lines_of_length<kFftHybrid, 0>(A, st);
+    if (op == kFftHybridOne) return lines_of_length<kFftHybridOne, 0>(A, st);
     if (op != kFftFwdSymInv) return hipErrorInvalidValue;
     switch (sym) {
         case kSymSeparable: return lines_of_length<kFftFwdSymInv, kSymSeparable>(A, st);

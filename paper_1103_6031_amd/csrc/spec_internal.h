@@ -10,7 +10,7 @@ namespace mgic {
 // ---- three-dimensional FFTs of real fields (k_fft.hip) ------------------------------------------
 constexpr int kFftMaxLgN = 10;                       // transforms of length 2 .. 1024
 constexpr int kFftMaxFields = 3;                     // fields transformed together
-enum { kFftForward = 0, kFftInverse = 1, kFftFwdSymInv = 2, kFftRe = 3, kFftHybrid = 4 };
+enum { kFftForward = 0, kFftInverse = 1, kFftFwdSymInv = 2, kFftRe = 3, kFftHybrid = 4, kFftHybridOne = 5 };
 enum { kSymSeparable = 1, kSymTable = 2, kSymReplace = 5, kSymInvLap = 6 };
 enum { kSpecFv = 1, kSpecSg = 2, kSpecHybrid = 3, kSpecReplace = 4, kSpecPoisson = 5 };
 // one pass of batched 1-D transforms over nf fields fs complex points apart in the spectrum buffer.
@@ -40,6 +40,7 @@ struct FftPass {
     const double2* csp = nullptr;   // kSymReplace: the coarse region's spectrum, cn[0] x cn[1] x csp_zs
     int cn[3] = {0, 0, 0};
     int csp_zs = 0;
+    int comp = 0;                   // kFftHybridOne: the component
     double sym_scale = 1.0;
     double fine_scale = 1.0;        // kSymReplace: the scale of the modes that are kept
 };
@@ -109,6 +110,7 @@ struct SpecMul {
     const double2* csp = nullptr;          // kSymReplace: the coarse spectrum on the grid `coarse`
     const SpecGrid* coarse = nullptr;
     double fine_scale = 1.0;
+    int comp = 0;                          // kFftHybridOne
 };
 hipError_t spec_x_pass(const SpecGrid& S, int op, const SpecMul& m, const SpecField& in, const SpecField& out,
                        hipStream_t st);

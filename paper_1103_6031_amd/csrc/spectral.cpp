@@ -97,6 +97,7 @@ bool by_pairs(const SpecField& f, const double* p) {
 
 struct SpecPlan {
     SpecGrid G;
+    int fields = kFftMaxFields;   // that the hybrid correction has room for
     size_t bytes = 0;
 };
 
@@ -109,13 +110,14 @@ int spec_plan(const int* n, int isolated, void* ws, SpecPlan& S) {
     off = align256(off);
     S.G.W = ws ? (double2*)((char*)ws + off) : nullptr;
     const SpecGrid& G = S.G;
-    const size_t used = kFftMaxFields * sizeof(double2) * G.field();   // the hybrid correction's components
-    // the size that callers reserve stays that of one n0 x n1 x P2 and two n0 x P1 x P2 complex arrays
-    // where these are more
+    // the size that callers reserve stays that of one n0 x n1 x P2 and two n0 x P1 x P2 complex arrays.  The hybrid
+    // correction's components take three fields of it; where rows of two modes (one cell along z, isolated)
+    // leave room for two only, it forms them one after the other from the spectrum kept in the first
     const size_t w1 = sizeof(double2) * (size_t)G.n[0] * G.n[1] * G.P[2];
     const size_t w2 = sizeof(double2) * (size_t)G.n[0] * G.P[1] * G.P[2];
-    const size_t full = align256(w1) + align256(w2) + w2;
-    off += std::max(used, full);
+    const size_t full = align256(w1) + align256(w2) + w2, field = sizeof(double2) * G.field();
+    S.fields = kFftMaxFields * field <= full ? kFftMaxFields : 2;
+    off += std::max(S.fields * field, full);
     S.bytes = align256(off);
     return MG_OK;
 }
@@ -199,10 +201,12 @@ hipError_t spec_x_spectrum(const SpecGrid& S, int op, void* out, hipStream_t st)
 
 // x pass in place: forward from the field's planes `in`, multiply, inverse to the planes of `out`
 // (op kFftFwdSymInv; kFftHybrid: into the three components of the correction, W and the two fields
-// after it)
+// after it; kFftHybridOne: component m.comp, into the field after W)
 hipError_t spec_x_pass(const SpecGrid& S, int op, const SpecMul& m, const SpecField& in, const SpecField& out,
                        hipStream_t st) {
     FftPass x = pass_x(S);
+    x.comp = m.comp;
+    if (op == kFftHybridOne) x.out = S.W + S.field();
     x.in_lo = in.lo[0];
     x.in_hi = in.hi[0];
     x.out_lo = out.lo[0];
@@ -326,8 +330,18 @@ int lpt_hybrid_correction(const int n[3], double h, int isolated, int lap_order,
     m.scale = scale * h;
     const SpecField F(G.n);
     SP_HIP(spec_forward_zy(G, f, F, nullptr, st));
-    SP_HIP(spec_x_pass(G, kFftHybrid, m, F, F, st));
-    SP_HIP(spec_inverse_yz(G, out3, 3, F, true, st));
+    if (S.fields == kFftMaxFields) {
+        SP_HIP(spec_x_pass(G, kFftHybrid, m, F, F, st));
+        SP_HIP(spec_inverse_yz(G, out3, 3, F, true, st));
+        return MG_OK;
+    }
+    SpecGrid second = G;
+    second.W += G.field();
+    for (int c = 0; c < 3; ++c) {
+        m.comp = c;
+        SP_HIP(spec_x_pass(G, kFftHybridOne, m, F, F, st));
+        SP_HIP(spec_inverse_yz(second, out3 + c, 1, F, true, st));
+    }
     return MG_OK;
 }
 
