@@ -117,6 +117,10 @@ typedef struct {
 /* Workspace bytes for mg_solve_level / mg_solve_hierarchy / mg_solve_batch member, exact. */
 size_t mg_workspace_bytes(const mg_hier* hier, const mg_opts* opts);
 
+/* The same without the second arrays that let a level's sweeps run in one launch: a solve in a workspace with
+ * less than mg_workspace_bytes takes the half-sweeps one by one, to the same bits. */
+size_t mg_plain_workspace_bytes(const mg_hier* hier, const mg_opts* opts);
+
 /* Graph replay (mg_solve_level, mg_solve_hierarchy): the launch sequences a solve repeats - a
  * V-cycle with its residual norm, an outer step of the mixed-precision loop, the source
  * preparation and the final gauge - are captured as HIP graphs the second time one is met for a

@@ -2762,6 +2762,8 @@ size_t mg_workspace_bytes(const mg_hier* hier, const mg_opts* opts) {
     return cv.off;
 }
 
+size_t mg_plain_workspace_bytes(const mg_hier* hier, const mg_opts* opts) { return plain_bytes(hier, opts); }
+
 int mg_solve_level(int n, double h, const double* f, double* u, const mg_opts* opts, mg_stats* stats,
                    void* workspace, size_t workspace_bytes, void* stream) {
     mg_hier H = single_level(n, h);

@@ -62,6 +62,7 @@ _sz = ctypes.c_size_t
 
 _sig = {
     "mg_workspace_bytes": (_sz, [ctypes.POINTER(mg_hier), ctypes.POINTER(mg_opts)]),
+    "mg_plain_workspace_bytes": (_sz, [ctypes.POINTER(mg_hier), ctypes.POINTER(mg_opts)]),
     "mg_solve_level": (ctypes.c_int, [ctypes.c_int, ctypes.c_double, _P, _P, ctypes.POINTER(mg_opts),
                                       ctypes.POINTER(mg_stats), _P, _sz, _P]),
     "mg_solve_hierarchy": (ctypes.c_int, [ctypes.POINTER(mg_hier), _PP, _PP, ctypes.POINTER(mg_opts),
@@ -236,14 +237,31 @@ def mg_workspace_bytes(hier: Hier, opts=None) -> int:
     return n
 
 
+def mg_plain_workspace_bytes(hier: Hier, opts=None) -> int:
+    """The least of a solve's workspaces that keeps its fused levels: sweeps run as half-sweeps, to the same bits."""
+    H = hier.c_struct()
+    o = opts or make_opts()
+    n = _lib.mg_plain_workspace_bytes(ctypes.byref(H), ctypes.byref(o))
+    if n == 0:
+        raise MGError(MG_EINVAL, _lib.mg_last_error().decode())
+    return n
+
+
+def _solve_ws(ws, hier, opts):
+    """The caller's workspace where it holds the plain plan, else a new one of the full size."""
+    need = mg_workspace_bytes(hier, opts)
+    if ws is not None and not ws.fits(need) and ws.fits(mg_plain_workspace_bytes(hier, opts)):
+        return ws
+    return _ws(ws, need)
+
+
 def mg_solve_level(f, h, u=None, opts=None, workspace=None, stream=None, check=True):
     """Periodic solve of L u = f - mean(f).  Returns (u, stats dict)."""
     n = f.shape[0]
     o = opts or make_opts()
     if u is None:
         u = torch.empty_like(f)
-    need = mg_workspace_bytes(Hier(n, h), o)
-    ws = _ws(workspace, need)
+    ws = _solve_ws(workspace, Hier(n, h), o)
     st = mg_stats()
     rc = _lib.mg_solve_level(n, h, _dev(f, "f"), _dev(u, "u"), ctypes.byref(o), ctypes.byref(st),
                              ctypes.c_void_p(ws.ptr), ws.nbytes, _stream(stream))
@@ -285,8 +303,7 @@ def mg_solve_hierarchy(hier: Hier, f: Sequence[torch.Tensor], u=None, opts=None,
     if u is None:
         u = [torch.empty_like(x) for x in f]
     H = hier.c_struct()
-    need = mg_workspace_bytes(hier, o)
-    ws = _ws(workspace, need)
+    ws = _solve_ws(workspace, hier, o)
     fp, _fa = _ptr_array([_dev(x, "f") for x in f])
     up, _ua = _ptr_array([_dev(x, "u") for x in u])
     st = mg_stats()

@@ -6,7 +6,8 @@ order (solve + gradient) or second order (+ tau, second solve, gradient).  The s
 
 * admits a request as soon as a worker slot is free and its device-memory footprint (the
   library's exact workspace sizes plus the request's input and output fields) fits in what is
-  left of the memory budget; admission is first come, first served;
+  left of the memory budget, if need be with the smaller workspace in which its solves run
+  without their second arrays (to the same bits); admission is first come, first served;
 * runs each admitted request on its own HIP stream (one stream per slot, default priority), so
   requests that arrive while others are running overlap with them on the device; the library's
   entry points release the interpreter lock while they run;
@@ -26,7 +27,7 @@ import queue
 import threading
 import time
 from collections import deque
-from dataclasses import dataclass, field
+from dataclasses import dataclass, field, replace
 from typing import Callable, Dict, List, Optional, Tuple
 
 
@@ -38,6 +39,7 @@ class Request:
     patches: List[Tuple[Tuple[int, int, int], Tuple[int, int, int]]] = field(default_factory=list)
     order: int = 1                # 1: first-order LPT; 2: second order
     scale: float = 1.0            # amplitude factor of this request's density
+    plain: bool = False           # solve in the workspace without the sweeps' second arrays
 
 
 @dataclass
@@ -72,11 +74,13 @@ class Server:
     """Admission by slots and memory budget, one worker thread (and stream) per slot."""
 
     def __init__(self, executor: Callable, footprint: Callable[[Request], int], slots: int = 4,
-                 budget_bytes: int = 16 << 30, clock: Callable[[], float] = time.perf_counter):
+                 budget_bytes: int = 16 << 30, clock: Callable[[], float] = time.perf_counter,
+                 plain_footprint: Optional[Callable[[Request], int]] = None):
         if slots < 1:
             raise ValueError("slots must be >= 1")
         self.executor = executor
         self.footprint = footprint
+        self.plain_footprint = plain_footprint or footprint   # of a request run with plain=True
         self.slots = slots
         self.budget = int(budget_bytes)
         self.clock = clock
@@ -88,9 +92,12 @@ class Server:
         recs = {r.id: Record(r.id, r.t) for r in reqs}
         for r in reqs:
             recs[r.id].footprint = int(self.footprint(r))
-            if recs[r.id].footprint > self.budget:
+            least = recs[r.id].footprint
+            if least > self.budget:
+                least = int(self.plain_footprint(r))
+            if least > self.budget:
                 raise ValueError("request %d needs %d bytes, more than the whole budget %d"
-                                 % (r.id, recs[r.id].footprint, self.budget))
+                                 % (r.id, least, self.budget))
         work: "queue.Queue" = queue.Queue()
         done: "queue.Queue" = queue.Queue()
         t0 = self.clock()
@@ -124,10 +131,15 @@ class Server:
                     if free_slots == 0:
                         head.waited_for_slot = True
                         break
+                    r = pending[0]
                     if head.footprint > free_mem:
-                        head.waited_for_memory = True
-                        break
-                    r = pending.popleft()
+                        plain = int(self.plain_footprint(r))
+                        if plain > free_mem:
+                            head.waited_for_memory = True
+                            break
+                        if plain < head.footprint:
+                            head.footprint, r = plain, replace(r, plain=True)
+                    pending.popleft()
                     free_slots -= 1
                     free_mem -= recs[r.id].footprint
                     inflight += 1
@@ -186,16 +198,17 @@ def hier_of(req: Request):
     return mgic.Hier(req.N0, inputs.BOX / req.N0, [(tuple(n), tuple(o)) for n, o in req.patches])
 
 
-def footprint_bytes(req: Request, prec="mixed") -> int:
+def footprint_bytes(req: Request, prec="mixed", plain=False) -> int:
     """Device bytes one request holds while it runs: solve and LPT workspaces plus its fields
     (density, potential, 3 displacement components per level; for second order also tau, the
-    second potential and its 3 displacement components)."""
+    second potential and its 3 displacement components).  plain: with the solves' smaller workspace."""
     from . import mgic
     H = hier_of(req)
     o = mgic.make_opts(prec=prec)
     cells = sum(int(H.dims(p)[0]) * int(H.dims(p)[1]) * int(H.dims(p)[2]) for p in range(H.nlev))
     fields = 5 + (5 if req.order == 2 else 0)
-    ws = mgic.mg_workspace_bytes(H, o) + mgic.lpt_workspace_bytes(H, req.order)
+    solve = mgic.mg_plain_workspace_bytes(H, o) if plain else mgic.mg_workspace_bytes(H, o)
+    ws = solve + mgic.lpt_workspace_bytes(H, req.order)
     return int(ws + 8 * fields * cells + (1 << 20) * H.nlev)
 
 
@@ -223,14 +236,15 @@ class GpuExecutor:
         st = self.streams[slot]
         H = hier_of(req)
         with torch.cuda.stream(st):
+            ws = mg.Workspace(mg.mg_plain_workspace_bytes(H, self.opts)) if req.plain else None
             f = [x * req.scale for x in self.fields[shape_key(req)]]
-            phi, s1 = mg.mg_solve_hierarchy(H, f, opts=self.opts, stream=st)
+            phi, s1 = mg.mg_solve_hierarchy(H, f, opts=self.opts, workspace=ws, stream=st)
             psi = mg.lpt_displacements(H, phi, scale=-1.0, stream=st)
             ups = s1["cell_updates"]
             out = [phi, psi]
             if req.order == 2:
                 tau = mg.lpt2_source(H, phi, stream=st)
-                phi2, s2 = mg.mg_solve_hierarchy(H, tau, opts=self.opts, stream=st)
+                phi2, s2 = mg.mg_solve_hierarchy(H, tau, opts=self.opts, workspace=ws, stream=st)
                 psi2 = mg.lpt_displacements(H, phi2, scale=-3.0 / 7.0, stream=st)
                 ups += s2["cell_updates"]
                 out += [phi2, psi2]
@@ -292,7 +306,8 @@ def serve_trace(reqs: List[Request], slots=4, budget_gb=16.0, prec="mixed", work
     # first launches (function attributes, code loading) happen outside the measured run
     w = min(reqs, key=lambda r: (r.N0, len(r.patches)))
     ex(Request(-1, 0.0, w.N0, w.patches, 2, 1.0), 0)
-    srv = Server(ex, lambda r: footprint_bytes(r, prec), slots=slots, budget_bytes=int(budget_gb * 2 ** 30))
+    srv = Server(ex, lambda r: footprint_bytes(r, prec), slots=slots, budget_bytes=int(budget_gb * 2 ** 30),
+                 plain_footprint=lambda r: footprint_bytes(r, prec, plain=True))
     recs = srv.run(reqs)
     return summarize(recs, srv), recs, ex
 
