@@ -44,13 +44,3 @@ def test_a_hierarchy_asks_for_one_second_array(prec, word):
     # one patch more: u, f, the coarse copy, ghosts and their parents' parts, and the FP32 counterparts
     level = 17 * c + 24 * faces + (8 * c + c // 2 + 4 * faces if prec == "mixed" else 0)
     assert 0 <= need[1] - need[0] - level <= SLACK
-
-
-@pytest.mark.parametrize("shape", [(1, 1, 1), (16, 1, 1), (4, 2, 1), (64, 32, 1), (5, 247, 1), (452, 244, 1), (33, 17, 5)])
-def test_an_isolated_spectral_call_asks_for_three_complex_arrays(shape):
-    """One of n0 x n1 x P2 and two of n0 x P1 x P2 points, with tables of a few values per point of an axis."""
-    from paper_1103_6031_amd import mgic
-    P = [1 << (2 * n - 1).bit_length() for n in shape]
-    arrays = 16 * shape[0] * P[2] * (shape[1] + 2 * P[1])
-    need = mgic.spec_workspace_bytes(shape, isolated=True)
-    assert arrays <= need <= arrays + 16 * max(P) + 32 * sum(P) + 8 * 256
