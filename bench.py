@@ -446,7 +446,7 @@ def time_spectral(mg, torch, ft, reps=5):
     ms = clock(lambda: mg.lpt_hybrid_correction(ft, h, out, workspace=ws))
     b = spectral_bytes(ft.shape, ft.shape, "hybrid")
     res["hybrid_periodic_%d" % n] = dict(ms=round(ms, 3), gbs=round(b / (ms * 1e-3) / 1e9, 1),
-                                         algorithmic_bytes=b, transforms="1 forward + 2 inverse complex %d^3" % n)
+                                         algorithmic_bytes=b, transforms="1 forward + 3 inverse of real %d^3 fields" % n)
     patch = ft[64:192, 64:192, 64:192].contiguous()
     outp = [torch.zeros_like(patch) for _ in range(3)]
     wsp = mg.Workspace(mg.spec_workspace_bytes(patch.shape, isolated=True))

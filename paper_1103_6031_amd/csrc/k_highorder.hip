@@ -187,8 +187,10 @@ __global__ __launch_bounds__(kBlock) void k_ho_half_lds(const T* __restrict__ in
 // Bound: HBM at 512^3 (3 words per cell at 3.8 TB/s), the recomputed halos and the latency of a step below.
 // Measured (MI355X) against two half-sweeps, FP64 / FP32: order 4 512^3 1747 -> 891 us, 256^3 180 -> 104 / 73 -> 41,
 // 128^3 22 -> 14 / 15 -> 10, 64^3 7.0 -> 6.5 / 6.1 -> 5.5; order 6 256^3 208 -> 108 / 89 -> 50, 128^3 25 -> 18 /
-// 18 -> 14, 64^3 7.4 -> 8.3; order 2 256^3 158 -> 77 / 66 -> 39, 64^3 6.8 -> 4.7.  Hence order 6 from 128^3, the
-// others from 32^3.  (With the pairs kept as read, a select by parity for each neighbour: order 6 256^3 135 us.)
+// 18 -> 14, 64^3 7.4 -> 8.3; order 2 256^3 158 -> 77 / 66 -> 39, 64^3 6.8 -> 4.7.  Replayed from a graph, at the
+// line: order 6 64^3 6.3 -> 7.3 / 6.1 -> 6.0, 32^3 4.5 -> 5.6 / 4.6 -> 5.2; order 4 64^3 5.7 -> 5.8 / 5.6 -> 4.8, 32^3
+// 4.4 -> 4.4 / 4.4 -> 4.0; order 2 32^3 4.3 -> 3.6 / 4.3 -> 3.4.  Hence order 6 from 128^3, the others from 32^3, in
+// both precisions.  (With the pairs kept as read, a select by parity for each neighbour: order 6 256^3 135 us.)
 struct HoTile { int yr, zp, cx; };   // rows, pairs, planes: powers of two
 
 constexpr int ho_sweep_threads(int R, size_t elem) { return R >= 2 && elem == 8 ? 768 : 1024; }
@@ -493,8 +495,8 @@ __global__ __launch_bounds__(kBlock) void k_ho_fill(T* __restrict__ a, unsigned 
 // between two barriers; a half-sweep forms its values from the cells before it in registers and then
 // writes them in place.  Every value is formed by the operations of the one-step kernels in their
 // order (same bits).  u: the iterate of level lgt, in and out; f: its right-hand side (fas: the
-// restricted residual, L u is added as k_ho_fas does).  From 16^3 down the pyramid takes 80 KB of
-// LDS in FP64.  Measured (MI355X, order 4): one launch of 38 us in FP64, where a solve spent 60 us
+// restricted residual, L u is added as k_ho_fas does).  From 16^3 down the pyramid takes
+// 112 416 bytes of LDS in FP64 (three arrays per level; the top one's uold is not used).  Measured (MI355X, order 4): one launch of 38 us in FP64, where a solve spent 60 us
 // (256^3, the host ahead of the device) to 120 us (16^3 - 64^3) per V-cycle: solves to 1e-10 of
 // 16^3 1557 -> 480 us, 64^3 2363 -> 1277 us, 128^3 3026 -> 2185 us, 256^3 11.28 -> 10.78 ms.
 constexpr int kHoTailLg = 4;

@@ -676,7 +676,7 @@ __device__ __forceinline__ T tail_nsum(const T* u, unsigned x, unsigned y, unsig
     const T zm = u[tail_pos<N>(x, y, dn(z))], zp = u[tail_pos<N>(x, y, up(z))];
     return ((xm + xp) + (ym + yp)) + (zm + zp);
 }
-// threads of a tail that starts at N^3: one or two cells of a colour each, no more waves than that
+// threads of a tail that starts at N^3: up to three cells of a colour each, no more waves than that
 // takes (every barrier waits for all of them)
 constexpr int tail_threads(int N) { return N <= 4 ? 64 : (N <= 6 ? 128 : (N <= 10 ? 256 : (N <= 14 ? 512 : 1024))); }
 

@@ -1,5 +1,5 @@
 // Two red-black sweeps of the smoother (Section 3.2, steps 2 and 9) in one launch, for periodic
-// colour-split levels of at least 64^3 cells.
+// colour-split levels of 16^3 to 1024^3 cells (two_sweeps_ok; below 17^3 the single-workgroup tail takes them).
 //
 // As four launches the sweeps move 6 words per cell (every half-sweep reads the other colour, f and
 // writes its own).  One pass needs 2.5: the black half of u (the first red half-sweep reads nothing
@@ -231,7 +231,9 @@ unsigned sweep_blocks(int n, int W, const SweepShape& s) {
 // the shapes of 32^3 .. 256^3 in either precision the choice is within 5 % of the fastest one measured.
 // many: the level is one of many in a launch, so the CUs are full and the time per cell counts; blocks of four
 // waves and at most 16 planes, three to a CU, leave the launch's end short (64 instances of 32^3 - 128^3, FP32,
-// per solve: 9.71 ms; 12 waves 10.56 ms; up to 32 planes 10.00 ms, 8 planes 9.98 ms).
+// per solve: 9.71 ms; 12 waves 10.56 ms; up to 32 planes 10.00 ms, 8 planes 9.98 ms).  A batch of few instances takes
+// the same tiles, which leave CUs idle there, and still gains on half-sweeps: one 256^3 box FP64 5.24 -> 4.71 ms,
+// mixed 3.48 -> 2.82; two of 64^3 1.24 -> 1.10 and 1.25 -> 1.10; eight of 32^3 no change.
 static SweepShape find_shape(int n, int W, bool many) {
     SweepShape best;
     double least = 1e30;

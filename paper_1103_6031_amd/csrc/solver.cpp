@@ -1391,7 +1391,8 @@ static size_t batch_layout(int ninst, const int* n, const double* h, const mg_op
     // The fused legs recompute their tiles' halos (4.7 times the updates in the pre leg), which pays
     // while a depth's levels are bound by launches.  Measured for 64 instances of 32^3 - 128^3, FP32,
     // per cycle: 1353 tiles at depth 2 take 47 us fused and 69 us by one-step launches, 11279 tiles
-    // at depth 1 243 us and 160 us; the line lies between, at 8 tiles per CU.
+    // at depth 1 243 us and 160 us; the line lies between, at 8 tiles per CU.  (A depth is counted by itself: a
+    // fused one may lie above one that is not, whose step 6 then has its own launch.)
     for (int d = 1; d < B.D; ++d) {
         unsigned tiles = 0;
         for (auto& P : B.P)
